@@ -99,7 +99,7 @@ def parse():
                          "dirty cache lines cost the next one)")
     ap.add_argument("--tiles", type=int, default=0, choices=[0, 1, 2],
                     help="GEMM tiles: 0 the library's choice per product, 1 256x256 "
-                         "only (also fp32), 2 128x128 only (bf16; two workgroups per CU)")
+                         "only (also fp32), 2 128-column tiles only (bf16; two workgroups per CU)")
     ap.add_argument("--dx-weight-copy", type=int, default=0, choices=[0, 1, 2],
                     help="bf16 dX operand: 0 the library's choice, 1 W1/W3 read K-major, "
                          "2 from a transposed copy made in the backward")
@@ -790,7 +790,7 @@ def main():
                    "capacity": f"{cap_rule[0]} {cap_rule[1]}/{cap_rule[2]}",
                    "rows": args.rows, "pass": "fwd+bwd" if wl.backward else "fwd",
                    "row_align": L.row_align, "parallelism": "single GPU",
-                   "gemm_tiles": ["auto", "256x256", "128x128"][args.tiles],
+                   "gemm_tiles": ["auto", "256x256", "mid"][args.tiles],
                    "dx_weight_copy": ["auto", "off", "on"][args.dx_weight_copy]},
         "roofline": roof,
         "cpu_baseline": None,

@@ -8,10 +8,11 @@
 // bank-conflict free.
 //  * bf16 layers: 4 wavefronts on v_mfma_f32_16x16x32_bf16, two barriers
 //    per K step, loads and fragment reads issued one at a time between the
-//    MFMAs (ffn_gemm16_kernel), on 256x256 tiles (waves of 128x128, one
-//    workgroup per CU) or, for products with few tiles per CU, 128x128
-//    tiles (waves of 64x64, two workgroups per CU); both add every output's
-//    products in the same order.
+//    MFMAs: on 256x256 tiles (waves of 128x128, one workgroup per CU;
+//    ffn_gemm16_kernel) or, for products with few tiles per CU, on tiles of
+//    32 to 192 rows and 128 columns (two workgroups per CU;
+//    ffn_gemm16_mid_kernel), whose heights the schedule chooses; both add
+//    every output's products in the same order.
 //  * fp32 layers: 8 wavefronts of 128x64 on v_mfma_f32_32x32x2f32 in two
 //    ping-pong teams, one team's MFMAs overlapping the other's LDS reads
 //    (ffn_gemm_f32_kernel); the forward of small fp32 layers instead runs
@@ -54,7 +55,12 @@ constexpr int kStripBytes = kStripRows * kStripPitch * 4;
 constexpr int kStripsPerArray = kTileBytes / kStripBytes;
 static_assert(3 * kStripsPerArray >= 16, "two staging strips per wave in three operand buffers");
 
-constexpr int BM_S = 128;       // M tile of the two-workgroups-per-CU bf16 kernel
+// Tiles of the two-workgroups-per-CU bf16 kernel: kMidN columns, and 1 to
+// kMidMaxH units of kMidUnit rows, chosen per tile.
+constexpr int kMidUnit = 32;
+constexpr int kMidMaxH = 6;
+constexpr int kMidN = 128;
+constexpr int kMidDwM = 128;    // its rows in the weight-gradient products
 constexpr int kGroupM = 4;      // M tiles per scheduling group
 constexpr int kXcds = 8;
 constexpr int kSplitFloor = 512;  // smallest K chunk of a split dW product
@@ -71,7 +77,7 @@ enum Act { ACT_RELU = 0, ACT_GELU = 1, ACT_SWIGLU = 2 };
 // Device-side schedule written by schedule_kernel.
 struct Sched {
   int n_mtiles;    // (expert, m0) tiles of BM rows
-  int n_mtiles_s;  // (expert, m0) tiles of BM_S rows (the 128x128-tile kernel)
+  int n_mid[2];    // tiles of the two-workgroups-per-CU kernel, per list
   int n_segs;      // (expert, k range) segments of the dW products
   int kc;          // split chunk (rows)
   int n_slots;     // partial-sum slots used
@@ -160,89 +166,193 @@ __device__ __forceinline__ float sigm(float h) { return rcp_fast(1.f + exp_fast(
 // schedule
 // ---------------------------------------------------------------------------
 // Inclusive prefix sum over the 64 lanes of a wavefront.
-__device__ __forceinline__ int64_t wave_incl_scan(int64_t v) {
+__device__ __forceinline__ int wave_incl_scan(int v) {
   const int lane = threadIdx.x & 63;
 #pragma unroll
   for (int o = 1; o < 64; o <<= 1) {
-    const int64_t u = __shfl_up(v, o, 64);
+    const int u = __shfl_up(v, o, 64);
     if (lane >= o) v += u;
   }
   return v;
 }
 
-// One wavefront, lane g = expert g.  Clamps every expert's rows to its region
-// and to rows_alloc, and the tile count to the host bound the workspace was
-// sized for, so no later kernel can index out of bounds.  The weight-gradient
-// products split an expert's rows into K segments only when few experts
-// carry most rows (about 512 work items over all of them).  The experts'
-// tiles and segments are numbered in expert order by prefix sums; should a
-// bound be exceeded (inconsistent offsets), lane 0 instead walks the experts
-// in order and cuts the lists where the bounds stop them.
-__global__ __launch_bounds__(64) void schedule_kernel(
-    const int32_t* __restrict__ offsets, const int32_t* __restrict__ rows, int E,
-    int64_t rows_alloc, int max_mtiles, int max_mtiles_s, int max_segs, int tmn_min,
-    int max_slots, Sched* __restrict__ s, int2* __restrict__ mtile, int2* __restrict__ mtile_s,
+// Entry of a mid tile list: tile i of the n tiles an expert's `rows` rows are
+// spread over: x = expert | height in units << 8, y = first row.
+__device__ __forceinline__ int2 mid_tile(int rows, int n, int i, int e) {
+  const int units = (rows + kMidUnit - 1) / kMidUnit;
+  const int h = units / n, more = units - h * n;
+  return make_int2(e | ((h + (i < more ? 1 : 0)) << 8), (i * h + min(i, more)) * kMidUnit);
+}
+
+// Time (ns) of the two-workgroups-per-CU kernel on `tiles` tiles of at most h
+// units of rows and `steps` K steps each: rounds of `slots` tiles, each as
+// long as its K steps and its prologue and epilogue, which the other
+// workgroup of the CU overlaps in part.  Measured on 1024- to 8192-row
+// products (K = 512 .. 8192): a K step of both workgroups of a CU takes 0.87
+// us at h = 4 and 1.21 us at h = 6 with operands in the caches, about a tenth
+// more in a layer; a round of K = 512 at h = 4 takes 3.2 us more than its 8
+// steps.  A last round that leaves at least one of the two places of every
+// CU empty takes about 0.65 of a full one.
+__host__ __device__ inline int64_t mid_time(int64_t tiles, int h, int slots, int steps) {
+  const int64_t full = tiles / slots, rem = tiles - full * slots;
+  return (20 * full + (rem == 0 ? 0 : 2 * rem <= slots ? 13 : 20)) *
+         (static_cast<int64_t>(steps) * (210 + 185 * h) + 3200) / 20;
+}
+
+// First index g < E whose inclusive prefix exceeds t.
+__device__ __forceinline__ int find_expert(const int* incl, int E, int t) {
+  int lo = 0, hi = E - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi) >> 1;
+    if (incl[mid] > t) hi = mid;
+    else lo = mid + 1;
+  }
+  return lo;
+}
+
+// Clamps every expert's rows to its region and to rows_alloc, and the tile
+// counts to the host bounds the workspace was sized for, so no later kernel
+// can index out of bounds.  Lane g of every wavefront is expert g; the
+// wavefronts number the experts' tiles and segments in expert order by prefix
+// sums, one list each, and then all threads write the lists, each entry
+// finding its expert by bisection.
+//  * mtile: 256-row tiles (wavefront kMidMaxH).  mtile_mid[i], i = 0, 1 (the
+//    products with N = f and with N = d columns): the tiles of the
+//    two-workgroups-per-CU kernel.  Its rounds on the persistent grid decide
+//    their height: for each largest height h (wavefront h - 1) the experts
+//    need ceil(units / h) tiles of at most h units, and the h whose rounds
+//    take the least time wins, so a few rows more than a whole number of
+//    tiles make tiles a little higher rather than one more round of tiles.
+//    An expert's units are spread evenly over its tiles.
+//  * the weight-gradient products (last wavefront) split an expert's rows
+//    into K segments only when few experts carry most rows (about 512 work
+//    items over all of them).
+// Should a bound be exceeded (inconsistent offsets), one thread instead walks
+// the experts in order and cuts the lists where the bounds stop them.
+struct SchedArgs {
+  int E;
+  int64_t rows_alloc;
+  int max_mtiles, max_mid, max_segs, tmn_min, max_slots;
+  int nt[2], steps[2];   // column tiles and K steps of the products of the two mid lists
+  int slots_mid;         // workgroups of the mid kernel's persistent grid
+};
+constexpr int kSchedWaves = kMidMaxH + 2;
+
+__global__ __launch_bounds__(64 * kSchedWaves) void schedule_kernel(
+    const int32_t* __restrict__ offsets, const int32_t* __restrict__ rows, const SchedArgs A,
+    Sched* __restrict__ s, int2* __restrict__ mtile, int2* __restrict__ mtile_mid,
     int4* __restrict__ seg) {
-  const int g = threadIdx.x;
+  __shared__ int ti[kMaxE], si[kMaxE], mid_incl[kMidMaxH][kMaxE], rw[kMaxE], q0s[kMaxE];
+  __shared__ int64_t cost[2][kMidMaxH];
+  __shared__ int kc_s, fit_rows, fit_segs;
+  const int E = A.E;
+  const int g = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
   // rows of expert g, clamped to its region and to rows_alloc
-  int64_t m = 0;
+  int m = 0;
   if (g < E) {
     const int64_t off = offsets[g];
-    m = rows[g];
-    if (off < 0 || off >= rows_alloc) m = 0;
-    m = min(m, static_cast<int64_t>(offsets[g + 1]) - off);
-    m = min(m, rows_alloc - off);
-    m = max(m, int64_t(0));
+    int64_t r = rows[g];
+    if (off < 0 || off >= A.rows_alloc) r = 0;
+    r = min(r, static_cast<int64_t>(offsets[g + 1]) - off);
+    r = min(r, A.rows_alloc - off);
+    m = static_cast<int>(max(r, int64_t(0)));
   }
-  const int64_t tiles = (m + BM - 1) / BM;
-  const int64_t tiles_incl = wave_incl_scan(tiles);
-  const int64_t tiles_total = __shfl(tiles_incl, 63, 64);
-  const int64_t tiles_s = (m + BM_S - 1) / BM_S;
-  const int64_t tiles_s_incl = wave_incl_scan(tiles_s);
-  const int64_t tiles_s_total = __shfl(tiles_s_incl, 63, 64);
-  const int64_t kw = (m + kKc - 1) / kKc * kKc;
-  const int64_t kwork = __shfl(wave_incl_scan(kw), 63, 64);
-  int64_t kc = (kwork * tmn_min + 511) / 512;
-  kc = (kc + kKc - 1) / kKc * kKc;
-  kc = max(kc, static_cast<int64_t>(kSplitFloor));
-  const int64_t nsp = g < E ? (m > kc ? (m + kc - 1) / kc : 1) : 0;
-  const int64_t segs_incl = wave_incl_scan(nsp);
-  const int64_t slots_incl = wave_incl_scan(nsp > 1 ? nsp : 0);
-  // totals read from lane 63 while every lane is active
-  const int64_t segs_total = __shfl(segs_incl, 63, 64);
-  const int64_t slots_total = __shfl(slots_incl, 63, 64);
-  const bool fits = tiles_total <= max_mtiles && tiles_s_total <= max_mtiles_s &&
-                    segs_total <= max_segs && slots_total <= max_slots;
-  if (fits) {
-    if (g < E) {
-      const int mi = static_cast<int>(m);
-      s->rows[g] = mi;
-      const int t0 = static_cast<int>(tiles_incl - tiles);
-      for (int i = 0; i < static_cast<int>(tiles); ++i) mtile[t0 + i] = make_int2(g, i * BM);
-      const int t0s = static_cast<int>(tiles_s_incl - tiles_s);
-      for (int i = 0; i < static_cast<int>(tiles_s); ++i) mtile_s[t0s + i] = make_int2(g, i * BM_S);
-      const int n = static_cast<int>(nsp);
-      const int s0 = static_cast<int>(segs_incl - nsp);
-      const int q0 = static_cast<int>(slots_incl - (n > 1 ? n : 0));
-      s->nsplit[g] = n;
-      s->slot0[g] = n > 1 ? q0 : -1;
-      for (int i = 0; i < n; ++i) {
-        const int k0 = static_cast<int>(min(static_cast<int64_t>(i) * kc, m));
-        const int k1 = static_cast<int>(min(static_cast<int64_t>(i + 1) * kc, m));
-        seg[s0 + i] = make_int4(g, n > 1 ? k0 : 0, n > 1 ? k1 : mi, n > 1 ? q0 + i : -1);
-      }
+  if (wave < kMidMaxH) {
+    const int h = wave + 1;
+    const int units = (m + kMidUnit - 1) / kMidUnit;
+    const int n = (units + h - 1) / h;
+    int hm = n ? (units + n - 1) / n : 0;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) hm = max(hm, __shfl_xor(hm, o, 64));
+    const int incl = wave_incl_scan(n);
+    const int tot = __shfl(incl, 63, 64);
+    mid_incl[wave][g] = incl;
+    if (g < 2)
+      cost[g][wave] = mid_time(static_cast<int64_t>(tot) * A.nt[g], hm, A.slots_mid, A.steps[g]);
+  } else if (wave == kMidMaxH) {
+    ti[g] = wave_incl_scan((m + BM - 1) / BM);
+    rw[g] = m;
+    // the rows of consistent regions add up to at most rows_alloc; then no
+    // 32-bit sum here overflows
+    int64_t sum = m;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+    if (g == 0) fit_rows = sum <= A.rows_alloc;
+  } else {
+    const int64_t kw = (static_cast<int64_t>(m) + kKc - 1) / kKc * kKc;
+    int64_t kwork = kw;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) kwork += __shfl_xor(kwork, o, 64);
+    int64_t kc = (kwork * A.tmn_min + 511) / 512;
+    kc = (kc + kKc - 1) / kKc * kKc;
+    const int kci = static_cast<int>(min(max(kc, static_cast<int64_t>(kSplitFloor)),
+                                         static_cast<int64_t>(0x7FFFFFC0)));
+    const int nsp = g < E ? (m > kci ? (m - 1) / kci + 1 : 1) : 0;
+    const int segs_incl = wave_incl_scan(nsp);
+    const int slots_incl = wave_incl_scan(nsp > 1 ? nsp : 0);
+    const int slots_total = __shfl(slots_incl, 63, 64);
+    si[g] = segs_incl;
+    q0s[g] = nsp > 1 ? slots_incl - nsp : -1;
+    if (g == 63) {
+      fit_segs = segs_incl <= A.max_segs && slots_total <= A.max_slots;
+      kc_s = kci;
+      s->n_slots = slots_total;
     }
-    if (g == 0) {
-      s->n_mtiles = static_cast<int>(tiles_total);
-      s->n_mtiles_s = static_cast<int>(tiles_s_total);
-      s->n_segs = static_cast<int>(segs_total);
-      s->n_slots = static_cast<int>(slots_total);
-      s->kc = static_cast<int>(kc);
+  }
+  __syncthreads();
+  // the heights: the least time, the larger height on a tie
+  int best[2];
+#pragma unroll
+  for (int l = 0; l < 2; ++l) {
+    best[l] = 0;
+#pragma unroll
+    for (int h = 1; h < kMidMaxH; ++h)
+      if (cost[l][h] <= cost[l][best[l]]) best[l] = h;
+  }
+  const int* mi2[2] = {mid_incl[best[0]], mid_incl[best[1]]};
+  const bool fits = fit_rows && fit_segs && ti[E - 1] <= A.max_mtiles &&
+                    mi2[0][E - 1] <= A.max_mid && mi2[1][E - 1] <= A.max_mid;
+  const int max_mtiles = A.max_mtiles, max_mid = A.max_mid, max_segs = A.max_segs,
+            max_slots = A.max_slots, tmn_min = A.tmn_min;
+  const int64_t rows_alloc = A.rows_alloc;
+  const int tid = threadIdx.x, nthreads = 64 * kSchedWaves;
+  if (fits) {
+    if (tid < E) {
+      s->rows[tid] = rw[tid];
+      s->nsplit[tid] = si[tid] - (tid ? si[tid - 1] : 0);
+      s->slot0[tid] = q0s[tid];
+    }
+    if (tid == 0) {
+      s->n_mtiles = ti[E - 1];
+      s->n_mid[0] = mi2[0][E - 1];
+      s->n_mid[1] = mi2[1][E - 1];
+      s->n_segs = si[E - 1];
+      s->kc = kc_s;
+    }
+    for (int t = tid; t < ti[E - 1]; t += nthreads) {
+      const int e = find_expert(ti, E, t);
+      mtile[t] = make_int2(e, (t - (e ? ti[e - 1] : 0)) * BM);
+    }
+#pragma unroll
+    for (int l = 0; l < 2; ++l)
+      for (int t = tid; t < mi2[l][E - 1]; t += nthreads) {
+        const int e = find_expert(mi2[l], E, t);
+        const int first = e ? mi2[l][e - 1] : 0;
+        mtile_mid[l * max_mid + t] = mid_tile(rw[e], mi2[l][e] - first, t - first, e);
+      }
+    for (int t = tid; t < si[E - 1]; t += nthreads) {
+      const int e = find_expert(si, E, t);
+      const int first = e ? si[e - 1] : 0, n = si[e] - first, i = t - first;
+      const int64_t k0 = static_cast<int64_t>(i) * kc_s, k1 = k0 + kc_s;
+      seg[t] = make_int4(e, n > 1 ? static_cast<int>(k0) : 0,
+                         n > 1 ? static_cast<int>(min(k1, static_cast<int64_t>(rw[e]))) : rw[e],
+                         n > 1 ? q0s[e] + i : -1);
     }
     return;
   }
-  if (g != 0) return;
-  int nm = 0, nms = 0;
+  if (tid != 0) return;
+  int nm = 0, nmid = 0;
   int64_t kwork_c = 0;
   for (int e = 0; e < E; ++e) {
     const int64_t off = offsets[e];
@@ -252,15 +362,17 @@ __global__ __launch_bounds__(64) void schedule_kernel(
     me = min(me, rows_alloc - off);
     me = max(me, int64_t(0));
     me = min(me, static_cast<int64_t>(max_mtiles - nm) * BM);
-    me = min(me, static_cast<int64_t>(max_mtiles_s - nms) * BM_S);
+    me = min(me, static_cast<int64_t>(max_mid - nmid) * kMidMaxH * kMidUnit);
     const int mi = static_cast<int>(me);
     s->rows[e] = mi;
     for (int m0 = 0; m0 < mi; m0 += BM) mtile[nm++] = make_int2(e, m0);
-    for (int m0 = 0; m0 < mi; m0 += BM_S) mtile_s[nms++] = make_int2(e, m0);
+    const int n = (mi + kMidMaxH * kMidUnit - 1) / (kMidMaxH * kMidUnit);
+    for (int i = 0; i < n; ++i, ++nmid)
+      mtile_mid[nmid] = mtile_mid[max_mid + nmid] = mid_tile(mi, n, i, e);
     kwork_c += (mi + kKc - 1) / kKc * kKc;
   }
   s->n_mtiles = nm;
-  s->n_mtiles_s = nms;
+  s->n_mid[0] = s->n_mid[1] = nmid;
   int64_t kcc = (kwork_c * tmn_min + 511) / 512;
   kcc = (kcc + kKc - 1) / kKc * kKc;
   kcc = max(kcc, static_cast<int64_t>(kSplitFloor));
@@ -618,6 +730,7 @@ struct GemmParams {
   const Sched* sched;
   const int2* mtile;
   const int4* seg;
+  int mid_list;       // two-workgroups-per-CU kernel: its tile list
 };
 
 // tile order: groups of kGroupM M-tiles, N-major inside a group
@@ -1296,35 +1409,43 @@ __device__ __forceinline__ void mainloop16(const TileOps& op, char* la0, char* l
 }
 
 // ---------------------------------------------------------------------------
-// bf16 products on 128x128 tiles, two workgroups per CU
+// bf16 products on tiles of 32 to 192 rows, two workgroups per CU
 // ---------------------------------------------------------------------------
 // The 256x256 kernel holds one wavefront per SIMD (256 accumulation
-// registers), so a tile's prologue and epilogue leave the matrix cores idle:
-// on short K (a few K steps per tile), few tiles per CU, or an epilogue heavy
-// in VALU work, that idle time is a large share.  This variant computes
-// 128x128 tiles with 4 wavefronts of 64x64 (64 accumulation registers,
-// under 256 registers in all) and 64 KB of LDS, so two workgroups share each
-// CU and one's epilogue overlaps the other's MFMAs.  It reads twice the
-// operand bytes per flop of the 256x256 tile, which is why large products
-// keep the big tile.  The K loop has the same structure: two stages of K 64,
-// two barriers per step, and loads and fragment reads issued one at a time
-// between the MFMAs.
+// registers), so a tile's prologue and epilogue leave the matrix cores idle,
+// and its tiles are so large that the last round of them often leaves many
+// CUs idle: on short K, few tiles per CU, or an epilogue heavy in VALU work
+// that idle time is a large share.  This kernel computes tiles of 128
+// columns and RB units of 32 rows (RB = 1 .. 6, per tile) with 4 wavefronts
+// of 16 RB x 64 (16 RB accumulation registers, under 256 registers in all)
+// and 80 KB of LDS, so two workgroups share each CU and one's epilogue
+// overlaps the other's MFMAs.  The heights let the schedule spread an
+// expert's rows evenly over just as many tiles as fill whole rounds.  It
+// reads more operand bytes per flop than the 256x256 tile, which is why
+// large products keep the big tile.  The K loop has the same structure: two
+// stages of K 64, two barriers per step, loads and fragment reads issued one
+// at a time between the MFMAs.
 //
-// Wave w owns tile rows 64 (w >> 1) .. +63 and columns 64 (w & 1) .. +63
+// Wave w owns tile rows 16 RB (w >> 1) .. and columns 64 (w & 1) .. +63
 // (gated forward: hidden units 32 (w & 1) .. +31 of W1, then the same units
-// of W3).  KC LDS tiles are 128 rows of 128 bytes with the swizzle of the
-// big tile; KM tiles are 64 k-rows of 128 elements (256 bytes) with the
-// same XOR of 32-element segments by k mod 4.
-template <int ALAY, int BLAY, bool GATED, bool FULL>
-__device__ __forceinline__ void mainloop16s(const TileOps& op, char* la0, char* lb0, char* la1,
-                                            char* lb1, floatx4 (&acc)[4][4], int zt) {
+// of W3).  KC LDS tiles are rows of 128 bytes with the swizzle of the big
+// tile; KM tiles are 64 k-rows of 128 elements (256 bytes) with the same XOR
+// of 32-element segments by k mod 4 (KM A operands: RB = 4 only).
+constexpr int wait_vm_lgkm0(int vm) { return (vm & 15) | ((vm >> 4) << 14) | 0x70; }
+constexpr int wait_vm(int vm) { return (vm & 15) | ((vm >> 4) << 14) | 0xF70; }
+
+template <int RB, int ALAY, int BLAY, bool GATED>
+__device__ __forceinline__ void mainloop_mid(const TileOps& op, char* la0, char* lb0, char* la1,
+                                             char* lb1, floatx4 (&acc)[RB][4], int zt) {
+  static_assert(ALAY == L_KC || RB == 4, "K-major A tiles are 128 columns wide");
   constexpr int KSTEP = 64;
   constexpr int KMROW = 256;           // bytes per k-row of a KM tile
+  constexpr int NM = 4 * RB;           // MFMAs per k-half
   const int lane = (static_cast<int>(threadIdx.x) & 63) + zt;
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
   const int wm = wave >> 1, wn = wave & 1;
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < RB; ++i)
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
   const int K = op.K;
@@ -1334,93 +1455,90 @@ __device__ __forceinline__ void mainloop16s(const TileOps& op, char* la0, char* 
 
   // ---- loads: 1 KB blocks (8 rows of a KC tile: lane l -> row l >> 3,
   // physical chunk l & 7; or 4 k-rows of a KM tile: lane l -> k-row l >> 4,
-  // physical elements 8 (l & 15) .. +7); wave w loads blocks 4w .. 4w+3 of
-  // A (g = 0..3) and of B (g = 4..7) of every stage.
+  // physical elements 8 (l & 15) .. +7); of every stage, wave w loads blocks
+  // 4i + w of A (i < RB) and of B (i < 4).  A lane's offset within a block
+  // has bit 31 set (out of range, reads zeros) where the block's row or
+  // column is past the valid ones; past K and past the last step the bit is
+  // or-ed in per step.
   const int l3 = lane >> 3;
-  const int co0 = ((lane & 7) ^ swz(l3)) * 16, co1 = ((lane & 7) ^ swz(l3 + 8)) * 16;
+  const int co = ((lane & 7) ^ swz(l3 + (wave & 1) * 8)) * 16;   // block 4i + w: rows 8(4i + w) + l3
   const int kr = lane >> 4;            // KM: k-row within the block (= k mod 4)
   const int pe = (lane & 15) * 8;      // KM: physical element within the k-row
   const int km_col = (((pe >> 5) ^ kr) << 5) + (pe & 31);
   const __amdgpu_buffer_rsrc_t ra_t = tile_rsrc(op.a.base);
   const __amdgpu_buffer_rsrc_t rb_t = tile_rsrc(op.b.base);
   const __amdgpu_buffer_rsrc_t rb3_t = tile_rsrc(GATED ? op.b.base2 : op.b.base);
+  const int lda = static_cast<int>(op.a.ld), ldb = static_cast<int>(op.b.ld);
+  auto bad = [](bool b) { return static_cast<uint32_t>(b) << 31; };
+  uint32_t offa[ALAY == L_KC ? RB : 1], offb[BLAY == L_KC ? 4 : 1];
+  if constexpr (ALAY == L_KC) {
+#pragma unroll
+    for (int i = 0; i < RB; ++i)
+      offa[i] = static_cast<uint32_t>(l3 * lda + co) | bad((4 * i + wave) * 8 + l3 >= op.a.rows);
+  } else {
+    offa[0] = static_cast<uint32_t>(kr * lda + km_col * 2) | bad(km_col >= op.a.rows);
+  }
+  // gated: block 4i + w holds rows (hidden units) 32 (i >> 1) + 8w .. +7 of
+  // W1 (i even) or W3 (i odd)
+  auto brow = [&](int i) { return GATED ? (i >> 1) * 32 + wave * 8 : (4 * i + wave) * 8; };
+  if constexpr (BLAY == L_KC) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      offb[i] = static_cast<uint32_t>(l3 * ldb + co) | bad(brow(i) + l3 >= op.b.rows);
+  } else {
+    offb[0] = static_cast<uint32_t>(kr * ldb + km_col * 2) | bad(km_col >= op.b.rows);
+  }
   auto km_rsrc = [&](const Operand& o, int kt, bool second) {
     const int64_t k = static_cast<int64_t>(kt) * KSTEP - (second ? o.split : 0);
     return tile_rsrc((second ? o.base2 : o.base) + k * o.ld);
   };
+  // what the loads of one K step share: resources of K-major operands, and
+  // for K-contiguous ones the lane's K-tail bit
   struct StepLd {
-    __amdgpu_buffer_rsrc_t ra, ra2, rb, rb2;
+    __amdgpu_buffer_rsrc_t ra, rb, rb2;
+    uint32_t kbad;
     int kt;
-    bool kfull, kany;
   };
   auto step_ld = [&](int kt) {
     StepLd s;
     s.kt = kt;
-    s.kfull = (kt + 1) * KSTEP <= K;
-    s.kany = kt * KSTEP < K;
-    s.ra = ra_t; s.ra2 = ra_t; s.rb = rb_t; s.rb2 = rb3_t;
-    if constexpr (ALAY == L_KM) {
-      s.ra = km_rsrc(op.a, kt, false);
-      s.ra2 = op.a.base2 ? km_rsrc(op.a, kt, true) : s.ra;
-    }
+    s.ra = ra_t; s.rb = rb_t; s.rb2 = rb3_t;
+    s.kbad = bad(kt * kRowBytes + co >= K * 2);
+    if constexpr (ALAY == L_KM) s.ra = km_rsrc(op.a, kt, false);
     if constexpr (BLAY == L_KM) {
       s.rb = km_rsrc(op.b, kt, false);
       s.rb2 = op.b.base2 ? km_rsrc(op.b, kt, true) : s.rb;
     }
     return s;
   };
-  auto load_blk = [&](auto lay, const Operand& o, const __amdgpu_buffer_rsrc_t& rs,
-                      const __amdgpu_buffer_rsrc_t& rs2, char* dst, int blk, const StepLd& s,
-                      bool gated) {
-    constexpr int LAY = decltype(lay)::value;
-    const int ld = static_cast<int>(o.ld);
-    uint32_t off;
-    int soff;
-    bool second = false;
-    if constexpr (LAY == L_KC) {
-      const int co = (blk & 1) ? co1 : co0;
-      // gated forward: 32-row groups alternate W1 / W3 rows of 32 hidden units
-      const int row0 = gated ? (blk >> 3) * 32 + (blk & 3) * 8 : blk * 8;
-      second = gated && ((blk >> 2) & 1);
-      off = static_cast<uint32_t>(l3 * ld) + co;
-      soff = row0 * ld + s.kt * kRowBytes;
-      if (!FULL || !s.kfull) {
-        const bool ok = (FULL || row0 + l3 < o.rows) && (s.kfull || s.kt * kRowBytes + co < K * 2);
-        if (!ok) off = kOob;
-      }
-    } else {
-      const int krel = 4 * blk;                  // first k-row of the block in the step
-      const int kabs = s.kt * KSTEP + krel;
-      second = kabs >= o.split;                  // split is a multiple of 8: no block straddles it
-      off = static_cast<uint32_t>(kr * ld + km_col * 2);
-      soff = krel * ld;
-      if (!FULL || !s.kfull) {
-        const bool ok = (FULL || km_col < o.rows) && (s.kfull || kabs + kr < K);
-        if (!ok) off = kOob;
-      }
-    }
-    if (!s.kany) off = kOob;
-    if (second)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs2, MOE_LDS(dst + blk * 1024), 16, off, soff, 0, 0);
-    else
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, MOE_LDS(dst + blk * 1024), 16, off, soff, 0, 0);
+  auto issue = [&](const __amdgpu_buffer_rsrc_t& rs, char* dst, uint32_t off, int soff) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, MOE_LDS(dst), 16, off, soff, 0, 0);
   };
-  using KC_ = std::integral_constant<int, L_KC>;
-  using KM_ = std::integral_constant<int, L_KM>;
-  auto load1 = [&](const StepLd& s, char* sa, char* sb, int g) {
-    const int blk = wave * 4 + (g & 3);
-    if (g < 4) {
-      if constexpr (ALAY == L_KC) load_blk(KC_{}, op.a, s.ra, s.ra2, sa, blk, s, false);
-      else load_blk(KM_{}, op.a, s.ra, s.ra2, sa, blk, s, false);
+  auto load_a = [&](const StepLd& s, char* sa, int i) {
+    const int blk = 4 * i + wave;
+    if constexpr (ALAY == L_KC)
+      issue(s.ra, sa + blk * 1024, offa[i] | s.kbad, blk * 8 * lda + s.kt * kRowBytes);
+    else
+      issue(s.ra, sa + blk * 1024, offa[0] | bad(s.kt * KSTEP + 4 * blk + kr >= K), 4 * blk * lda);
+  };
+  auto load_b = [&](const StepLd& s, char* sb, int i) {
+    const int blk = 4 * i + wave;
+    if constexpr (BLAY == L_KC) {
+      if (GATED && (i & 1))
+        issue(s.rb2, sb + blk * 1024, offb[i] | s.kbad, brow(i) * ldb + s.kt * kRowBytes);
+      else
+        issue(s.rb, sb + blk * 1024, offb[i] | s.kbad, brow(i) * ldb + s.kt * kRowBytes);
     } else {
-      if constexpr (BLAY == L_KC) load_blk(KC_{}, op.b, s.rb, s.rb2, sb, blk, s, GATED);
-      else load_blk(KM_{}, op.b, s.rb, s.rb2, sb, blk, s, false);
+      const int kabs = s.kt * KSTEP + 4 * blk;   // split is a multiple of 8: no block straddles it
+      const uint32_t off = offb[0] | bad(kabs + kr >= K);
+      if (kabs >= op.b.split) issue(s.rb2, sb + blk * 1024, off, 4 * blk * ldb);
+      else issue(s.rb, sb + blk * 1024, off, 4 * blk * ldb);
     }
   };
 
   // ---- fragments (as in the 256x256 kernel; KM k-rows are 256 bytes)
   const int c16 = lane & 15, G = lane >> 4;
-  const int fa_kc = (wm * 64 + c16) * kRowBytes, fb_kc = (wn * 64 + c16) * kRowBytes;
+  const int fa_kc = (wm * 16 * RB + c16) * kRowBytes, fb_kc = (wn * 64 + c16) * kRowBytes;
   auto km_frag = [&](const char* st, int cb, int h) -> uint4 {
     const int phys = (((cb >> 5) ^ (c16 >> 2)) << 5) + (cb & 31) + 4 * (c16 & 3);
     const char* p0 = st + (32 * h + 8 * G + (c16 >> 2)) * KMROW + phys * 2;
@@ -1428,58 +1546,62 @@ __device__ __forceinline__ void mainloop16s(const TileOps& op, char* la0, char* 
     const uint2 hi = read_tr(p0 + 4 * KMROW);
     return make_uint4(lo.x, lo.y, hi.x, hi.y);
   };
-  // fragment g of half h: A sub-block g (g < 4) or B sub-block g - 4
-  auto read1 = [&](const char* sa, const char* sb, int h, uint4 (&fa)[4], uint4 (&fb)[4], int g) {
+  auto read_a = [&](const char* sa, int h, uint4 (&fa)[RB], int i) {
     const int sw = ((4 * h + G) ^ (c16 >> 1)) << 4;
-    if (g < 4) {
-      if constexpr (ALAY == L_KC)
-        fa[g] = *reinterpret_cast<const uint4*>(sa + fa_kc + g * 16 * kRowBytes + sw);
-      else
-        fa[g] = km_frag(sa, wm * 64 + g * 16, h);
-    } else {
-      if constexpr (BLAY == L_KC)
-        fb[g - 4] = *reinterpret_cast<const uint4*>(sb + fb_kc + (g - 4) * 16 * kRowBytes + sw);
-      else
-        fb[g - 4] = km_frag(sb, wn * 64 + (g - 4) * 16, h);
-    }
+    if constexpr (ALAY == L_KC)
+      fa[i] = *reinterpret_cast<const uint4*>(sa + fa_kc + i * 16 * kRowBytes + sw);
+    else
+      fa[i] = km_frag(sa, wm * 64 + i * 16, h);
   };
-  uint4 f0a[4], f0b[4], f1a[4], f1b[4];
+  auto read_b = [&](const char* sb, int h, uint4 (&fb)[4], int j) {
+    const int sw = ((4 * h + G) ^ (c16 >> 1)) << 4;
+    if constexpr (BLAY == L_KC)
+      fb[j] = *reinterpret_cast<const uint4*>(sb + fb_kc + j * 16 * kRowBytes + sw);
+    else
+      fb[j] = km_frag(sb, wn * 64 + j * 16, h);
+  };
+  uint4 f0a[RB], f0b[4], f1a[RB], f1b[4];
 
   // One K step from stage (ca, cb), the next stage in (na, nb); the loads of
-  // step kt + 2 go into (ca, cb).  MFMAs in groups of two (m -> block
-  // m >> 2, m & 3); the first quarter reads the A fragments of k-half 1, the
-  // second the B fragments and issues the A loads, the second half reads the
-  // next stage's k-half 0 and issues the B loads.
+  // step kt + 2 go into (ca, cb).  MFMA m is block (m >> 2, m & 3).  The
+  // first quarter reads the A fragments of k-half 1, the second the B
+  // fragments and issues the A loads, the second half reads the next stage's
+  // k-half 0 and issues the B loads.
   auto step = [&](int kt, char* ca, char* cb, const char* na, const char* nb) {
     const StepLd s = step_ld(kt + 2);
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      read1(ca, cb, 1, f1a, f1b, g);
+    for (int i = 0; i < RB; ++i) {
+      read_a(ca, 1, f1a, i);
 #pragma unroll
-      for (int m = 2 * g; m < 2 * g + 2; ++m) mfma16(acc[m >> 2][m & 3], f0a[m >> 2], f0b[m & 3]);
+      for (int m = 2 * i; m < 2 * i + 2; ++m) mfma16(acc[m >> 2][m & 3], f0a[m >> 2], f0b[m & 3]);
       __builtin_amdgcn_sched_barrier(0);
     }
     __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int g = 4; g < 8; ++g) {
-      load1(s, ca, cb, g - 4);
-      read1(ca, cb, 1, f1a, f1b, g);
+    for (int q = 0; q < 2 * RB; ++q) {
+      if ((q & 1) == 0) load_a(s, ca, q >> 1);
+      // B fragments spread over the quarter (RB = 1: two per MFMA)
 #pragma unroll
-      for (int m = 2 * g; m < 2 * g + 2; ++m) mfma16(acc[m >> 2][m & 3], f0a[m >> 2], f0b[m & 3]);
+      for (int j = 4 * q / (2 * RB); j < 4 * (q + 1) / (2 * RB); ++j) read_b(cb, 1, f1b, j);
+      const int m = 2 * RB + q;
+      mfma16(acc[m >> 2][m & 3], f0a[m >> 2], f0b[m & 3]);
       __builtin_amdgcn_sched_barrier(0);
     }
-    // stage kt + 1 has landed (only the 4 A loads just issued may be pending)
-    __builtin_amdgcn_s_waitcnt(0x0074);   // vmcnt(4) lgkmcnt(0)
+    // stage kt + 1 has landed (only the RB A loads just issued may be pending)
+    __builtin_amdgcn_s_waitcnt(wait_vm_lgkm0(RB));
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int g = 0; g < 8; ++g) {
-      if ((g & 1) == 0) load1(s, ca, cb, 4 + (g >> 1));
-      read1(na, nb, 0, f0a, f0b, g);
+    for (int m = 0; m < NM; ++m) {
+      if (m % RB == 0) load_b(s, cb, m / RB);
 #pragma unroll
-      for (int m = 2 * g; m < 2 * g + 2; ++m) mfma16(acc[m >> 2][m & 3], f1a[m >> 2], f1b[m & 3]);
+      for (int r = (RB + 4) * m / NM; r < (RB + 4) * (m + 1) / NM; ++r) {
+        if (r < RB) read_a(na, 0, f0a, r);
+        else read_b(nb, 0, f0b, r - RB);
+      }
+      mfma16(acc[m >> 2][m & 3], f1a[m >> 2], f1b[m & 3]);
       __builtin_amdgcn_sched_barrier(0);
     }
   };
@@ -1487,14 +1609,20 @@ __device__ __forceinline__ void mainloop16s(const TileOps& op, char* la0, char* 
   {
     const StepLd s0 = step_ld(0), s1 = step_ld(1);
 #pragma unroll
-    for (int g = 0; g < 8; ++g) load1(s0, la0, lb0, g);
+    for (int i = 0; i < RB; ++i) load_a(s0, la0, i);
 #pragma unroll
-    for (int g = 0; g < 8; ++g) load1(s1, la1, lb1, g);
+    for (int i = 0; i < 4; ++i) load_b(s0, lb0, i);
+#pragma unroll
+    for (int i = 0; i < RB; ++i) load_a(s1, la1, i);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) load_b(s1, lb1, i);
   }
-  __builtin_amdgcn_s_waitcnt(0x0F78);   // vmcnt(8): this wave's stage-0 loads landed
+  __builtin_amdgcn_s_waitcnt(wait_vm(RB + 4));   // this wave's stage-0 loads landed
   __builtin_amdgcn_s_barrier();
 #pragma unroll
-  for (int g = 0; g < 8; ++g) read1(la0, lb0, 0, f0a, f0b, g);
+  for (int i = 0; i < RB; ++i) read_a(la0, 0, f0a, i);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) read_b(lb0, 0, f0b, j);
   for (int kt = 0; kt < nk2; kt += 2) {
     step(kt, la0, lb0, la1, lb1);
     step(kt + 1, la1, lb1, la0, lb0);
@@ -1504,22 +1632,20 @@ __device__ __forceinline__ void mainloop16s(const TileOps& op, char* la0, char* 
   asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" ::: "memory");
 }
 
-// Wave-block shapes of the two bf16 kernels: RB x CB blocks of 16x16 per
-// wave, 2 x 2 waves per workgroup.
-template <int RB_, int CB_, int MINB_> struct Tile16 {
+// A wave's block of RB x CB blocks of 16x16, 2 x 2 waves per workgroup.
+template <int RB_, int CB_> struct Tile16 {
   static constexpr int RB = RB_, CB = CB_;
   static constexpr int WR = 16 * RB, WC = 16 * CB;      // wave block
   static constexpr int TM = 2 * WR, TN = 2 * WC;        // workgroup tile
   static constexpr int kP = WC + 4;                     // strip pitch (floats): rows 4 apart
                                                         // fall 16 banks apart
   static constexpr int kStripBytes = 16 * kP * 4;
-  static constexpr int kStageBytes = TM * kRowBytes;    // one operand of one stage
-  static constexpr int kMinBlocks = MINB_;              // workgroups per CU
-  static_assert(2 * kStripBytes <= kStageBytes, "two staging strips per operand buffer");
 };
-using TileBig = Tile16<8, 8, 1>;
-using TileSmall = Tile16<4, 4, 2>;
-static_assert(TileBig::TM == BM && TileBig::TN == BN && TileSmall::TM == BM_S, "tile sizes");
+using TileBig = Tile16<8, 8>;
+static_assert(TileBig::TM == BM && TileBig::TN == BN, "tile size");
+static_assert(2 * TileBig::kStripBytes <= kTileBytes, "two staging strips per operand buffer");
+static_assert(2 * Tile16<1, 4>::kStripBytes <= kMidN * kRowBytes, "two staging strips per buffer");
+static_assert(Tile16<1, 4>::TN == kMidN && Tile16<1, 4>::TM == kMidUnit, "mid tile size");
 
 // Stage rows 16i .. 16i+15 of the wave's accumulators as fp32, row pitch C::kP.
 template <typename C>
@@ -1532,15 +1658,213 @@ __device__ __forceinline__ void stage16(float* strip, const floatx4 (&acc)[C::RB
     for (int q = 0; q < 4; ++q) strip[(4 * G + q) * C::kP + 16 * j + c16] = acc[i][j][q];
 }
 
-template <int MODE, int PASS, typename C>
-__global__ __launch_bounds__(kThreads16, C::kMinBlocks) void ffn_gemm16_kernel(const GemmParams p) {
-  __shared__ __attribute__((aligned(16))) char la0[C::kStageBytes];
-  __shared__ __attribute__((aligned(16))) char lb0[C::kStageBytes];
-  __shared__ __attribute__((aligned(16))) char la1[C::kStageBytes];
-  __shared__ __attribute__((aligned(16))) char lb1[C::kStageBytes];
-  constexpr bool SMALL = C::RB == 4;
-  constexpr int TM = C::TM, TN = C::TN, WR = C::WR, WC = C::WC, kP = C::kP;
+// Epilogue of one wave's block (RB x CB blocks of C): 16 accumulator rows at
+// a time go through the wave's LDS strip; a lane then finishes 8 consecutive
+// columns of a row and writes them as one vector (bf16) or two (fp32 weight
+// gradients).  el: the lane index, derived like the strip address from an
+// opaque zero the caller produces after its K loop, so nothing the epilogue
+// computes per lane is hoisted and held in registers across the K loop.
+// empty: a weight-gradient tile with no rows to contract over.
+template <int MODE, typename C>
+__device__ __forceinline__ void epilogue16(const GemmParams& p,
+                                           const floatx4 (&acc)[C::RB][C::CB], float* strip,
+                                           int el, int wm, int wn, int g, int slot, int row0,
+                                           int m_valid, int n0, bool empty) {
+  constexpr int WR = C::WR, WC = C::WC, kP = C::kP;
   using T = uint16_t;
+  constexpr int ES = 2;
+  const int wr0 = wm * WR;                      // the wave's first tile row
+  // weight gradients: where the fp32 result of tile row orow, column gc goes
+  // (a split partial-sum slot, or the first or second gradient array)
+  auto dw_dst = [&](int orow, int gc) -> float* {
+    if (slot >= 0)
+      return p.partial + static_cast<int64_t>(slot) * p.slot_elems +
+             static_cast<int64_t>(orow) * p.N + gc;
+    if (orow < p.split_row)
+      return p.dwA + static_cast<int64_t>(g) * p.dw_gstride + static_cast<int64_t>(orow) * p.N + gc;
+    return p.dwB + static_cast<int64_t>(g) * p.dw_gstride +
+           static_cast<int64_t>(orow - p.split_row) * p.N + gc;
+  };
+  if constexpr (MODE == M_DW) {
+    if (empty) {
+      // no rows to contract over (an expert without rows): the tile is
+      // zero; each lane stores 8 zeros per row pass straight to memory,
+      // with no staging, so the tile costs only its stores.  Every wave
+      // of the workgroup takes this path, and none touched the LDS.
+      constexpr int LR = WC / 8, RG = 64 / LR;
+      const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 4
+      for (int r = 0; r < WR; r += RG) {
+        const int lm = wr0 + r + el / LR, gc = n0 + wn * WC + (el % LR) * 8;
+        if (lm < m_valid && gc < p.N) {
+          float* dst = dw_dst(row0 + lm, gc);
+          *reinterpret_cast<float4*>(dst) = zero;
+          *reinterpret_cast<float4*>(dst + 4) = zero;
+        }
+      }
+      return;
+    }
+  }
+  // ReLU / GELU layers: the epilogue is specialised on the activation, one
+  // uniform branch per tile instead of one per element
+  auto epilogue = [&](auto act_c) {
+  constexpr int ACT = decltype(act_c)::value;
+  if constexpr (MODE == M_FWD1_SWIGLU) {
+    // strip columns [0,U): H1, [U,2U): H3 of hidden units n0 + U wn + u, U =
+    // WC / 2; LU lanes cover a row's U units, 8 each
+    constexpr int U = WC / 2, LU = U / 8, RU = 64 / LU;
+#pragma unroll
+    for (int i = 0; i < C::RB; ++i) {
+      stage16<C>(strip, acc, i, el);
+#pragma unroll
+      for (int it = 0; it < 16 / RU; ++it) {
+        const int r = it * RU + el / LU, u8 = (el % LU) * 8;
+        const int lm = wr0 + 16 * i + r;
+        const int gc = n0 + wn * U + u8;
+        if (lm < m_valid && gc < p.N) {
+          // H1 and H3 rounded to bf16 once: the packed bits are stored and
+          // their values feed the activation
+          float h1[8], h3[8], a[8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            h1[e] = strip[r * kP + u8 + e];
+            h3[e] = strip[r * kP + U + u8 + e];
+          }
+          const uint4 b1 = pack8(h1), b3 = pack8(h3);
+          unpack8(b1, h1);
+          unpack8(b3, h3);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) a[e] = h1[e] * sigm(h1[e]) * h3[e];
+          const int64_t grow = row0 + lm;
+          if (p.H1) {
+            *reinterpret_cast<uint4*>(p.H1 + grow * p.ldh + static_cast<int64_t>(gc) * ES) = b1;
+            *reinterpret_cast<uint4*>(p.H3 + grow * p.ldh + static_cast<int64_t>(gc) * ES) = b3;
+          }
+          store_vec<T>(p.C + grow * p.ldc + static_cast<int64_t>(gc) * ES, a);
+        }
+      }
+    }
+  } else if constexpr (MODE == M_BWD_DA || MODE == M_BWD_DA_SWIGLU) {
+    // dH = dA act'(H): (row block, row group) iterations, each reading 8
+    // saved pre-activations (two planes for SwiGLU) per lane, issued kPf
+    // iterations ahead of their use into a ring of kPf + 1 registers.  LR
+    // lanes cover a row of the wave block, RG rows form a group, GB groups
+    // a 16-row block.
+    constexpr bool SW = MODE == M_BWD_DA_SWIGLU;
+    constexpr int LR = WC / 8, RG = 64 / LR, GB = 16 / RG;
+    constexpr int kIt = C::RB * GB, kPf = 4, kRing = kPf + 1;
+    Raw8<T> q1[kRing], q3[kRing];
+    auto pos = [&](int n, int& lm, int& gc) {
+      lm = wr0 + 16 * (n / GB) + RG * (n % GB) + el / LR;
+      gc = n0 + wn * WC + (el % LR) * 8;
+    };
+    auto issue = [&](int n) {
+      int lm, gc;
+      pos(n, lm, gc);
+      const bool ok = lm < m_valid && gc < p.N;
+      // out-of-tile lanes read the tile's first valid element instead
+      const int64_t o = static_cast<int64_t>(row0 + (ok ? lm : 0)) * p.ldh +
+                        static_cast<int64_t>(ok ? gc : n0) * ES;
+      q1[n % kRing].load(p.H1 + o);
+      if constexpr (SW) q3[n % kRing].load(p.H3 + o);
+    };
+#pragma unroll
+    for (int n = 0; n < kPf; ++n) issue(n);
+#pragma unroll
+    for (int n = 0; n < kIt; ++n) {
+      if (n + kPf < kIt) issue(n + kPf);
+      if (n % GB == 0) stage16<C>(strip, acc, n / GB, el);
+      int lm, gc;
+      pos(n, lm, gc);
+      if (lm < m_valid && gc < p.N) {
+        const int r = RG * (n % GB) + el / LR, c8 = (el % LR) * 8;
+        const int64_t grow = row0 + lm;
+        float h1[8], g1[8];
+        q1[n % kRing].to_f(h1);
+        if constexpr (SW) {
+          float h3[8], g3[8];
+          q3[n % kRing].to_f(h3);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            // d silu(h1) h3 / dh1 = h3 sg (1 + h1 (1 - sg)), d / dh3 = h1 sg
+            const float da = strip[r * kP + c8 + e];
+            const float sg = sigm(h1[e]);
+            const float t = da * sg, u = t * h3[e];
+            g1[e] = __builtin_fmaf(u, __builtin_fmaf(-h1[e], sg, h1[e]), u);
+            g3[e] = t * h1[e];
+          }
+          store_vec<T>(p.C + grow * p.ldc + static_cast<int64_t>(gc) * ES, g1);
+          store_vec<T>(p.C + grow * p.ldc + static_cast<int64_t>(p.f + gc) * ES, g3);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            g1[e] = strip[r * kP + c8 + e] * act_grad_f(h1[e], ACT);
+          store_vec<T>(p.C + grow * p.ldc + static_cast<int64_t>(gc) * ES, g1);
+        }
+      }
+    }
+  } else {
+    constexpr int LR = WC / 8, RG = 64 / LR;   // lanes per row, rows per pass
+#pragma unroll
+    for (int i = 0; i < C::RB; ++i) {
+      stage16<C>(strip, acc, i, el);
+#pragma unroll
+      for (int it = 0; it < 16 / RG; ++it) {
+        const int r = RG * it + el / LR, c8 = (el % LR) * 8;
+        const int lm = wr0 + 16 * i + r;
+        const int gc = n0 + wn * WC + c8;
+        if (lm < m_valid && gc < p.N) {
+          const float* sp = strip + r * kP + c8;
+          if constexpr (MODE == M_DW) {
+            float* dst = dw_dst(row0 + lm, gc);
+            *reinterpret_cast<float4*>(dst) = make_float4(sp[0], sp[1], sp[2], sp[3]);
+            *reinterpret_cast<float4*>(dst + 4) = make_float4(sp[4], sp[5], sp[6], sp[7]);
+          } else {
+            float v[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = sp[e];
+            const int64_t grow = row0 + lm;
+            if constexpr (MODE == M_FWD1) {
+              if constexpr (ACT == ACT_RELU) {
+                // ReLU commutes with the rounding to bf16 (round(max(h, 0)) =
+                // max(round(h), 0)), and ReLU layers keep A alone
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[e] = fmaxf(v[e], 0.f);
+              } else {
+                // H rounded to bf16 once: the packed bits are stored and
+                // their values feed the activation
+                const uint4 hb = pack8(v);
+                float hh[8];
+                unpack8(hb, hh);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[e] = act_f(hh[e], ACT);
+                if (p.H1)
+                  *reinterpret_cast<uint4*>(p.H1 + grow * p.ldh + static_cast<int64_t>(gc) * ES) = hb;
+              }
+            }
+            store_vec<T>(p.C + grow * p.ldc + static_cast<int64_t>(gc) * ES, v);
+          }
+        }
+      }
+    }
+  }
+  };
+  if constexpr (MODE == M_FWD1 || MODE == M_BWD_DA) {
+    if (p.act == ACT_RELU) epilogue(std::integral_constant<int, ACT_RELU>{});
+    else epilogue(std::integral_constant<int, ACT_GELU>{});
+  } else {
+    epilogue(std::integral_constant<int, ACT_SWIGLU>{});
+  }
+}
+
+template <int MODE, int PASS>
+__global__ __launch_bounds__(kThreads16, 1) void ffn_gemm16_kernel(const GemmParams p) {
+  __shared__ __attribute__((aligned(16))) char la0[kTileBytes];
+  __shared__ __attribute__((aligned(16))) char lb0[kTileBytes];
+  __shared__ __attribute__((aligned(16))) char la1[kTileBytes];
+  __shared__ __attribute__((aligned(16))) char lb1[kTileBytes];
+  using C = TileBig;
+  constexpr int TM = C::TM, TN = C::TN;
   constexpr int ES = 2;
   constexpr bool VARK = MODE == M_DW;
   constexpr bool GATED = MODE == M_FWD1_SWIGLU;
@@ -1549,7 +1873,7 @@ __global__ __launch_bounds__(kThreads16, C::kMinBlocks) void ffn_gemm16_kernel(c
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
   const int wm = wave >> 1, wn = wave & 1;
   const Sched& sc = *p.sched;
-  const int n_mt = SMALL ? sc.n_mtiles_s : sc.n_mtiles;
+  const int n_mt = sc.n_mtiles;
   const int n_items = VARK ? sc.n_segs * p.mtiles_out * p.ntiles : n_mt * p.ntiles;
   const int G = gridDim.x;
   const int lbase = (blockIdx.x % kXcds) * (G / kXcds) + blockIdx.x / kXcds;
@@ -1611,205 +1935,115 @@ __global__ __launch_bounds__(kThreads16, C::kMinBlocks) void ffn_gemm16_kernel(c
     asm volatile("s_mov_b32 %0, 0" : "=s"(zt));
     floatx4 acc[C::RB][C::CB];
     const bool full = op.a.rows >= TM && op.b.rows >= (GATED ? TN / 2 : TN);
-    if constexpr (SMALL) {
-      if (full) mainloop16s<ALAY, BLAY, GATED, true>(op, la0, lb0, la1, lb1, acc, zt);
-      else mainloop16s<ALAY, BLAY, GATED, false>(op, la0, lb0, la1, lb1, acc, zt);
-    } else {
-      if (full) mainloop16<ALAY, BLAY, GATED, true>(op, la0, lb0, la1, lb1, acc, zt);
-      else mainloop16<ALAY, BLAY, GATED, false>(op, la0, lb0, la1, lb1, acc, zt);
-    }
+    if (full) mainloop16<ALAY, BLAY, GATED, true>(op, la0, lb0, la1, lb1, acc, zt);
+    else mainloop16<ALAY, BLAY, GATED, false>(op, la0, lb0, la1, lb1, acc, zt);
 
-    // Epilogue, wave by wave: 16 accumulator rows at a time go through the
-    // wave's LDS strip; a lane then finishes 8 consecutive columns of a row
-    // and writes them as one vector (bf16) or two (fp32 weight gradients).
-    // The lane index and the strip address are derived from an opaque zero
-    // produced here, so nothing the epilogue computes per lane is hoisted
-    // and held in registers across the K loop.
     int z;
     asm volatile("s_mov_b32 %0, 0" : "=s"(z));
-    const int el = lane + z;
     float* strip = reinterpret_cast<float*>((wave < 2 ? la0 : lb0) + (wave & 1) * C::kStripBytes + z);
-    const int wr0 = wm * WR;                      // the wave's first tile row
-    // weight gradients: where the fp32 result of tile row orow, column gc goes
-    // (a split partial-sum slot, or the first or second gradient array)
-    auto dw_dst = [&](int orow, int gc) -> float* {
-      if (slot >= 0)
-        return p.partial + static_cast<int64_t>(slot) * p.slot_elems +
-               static_cast<int64_t>(orow) * p.N + gc;
-      if (orow < p.split_row)
-        return p.dwA + static_cast<int64_t>(g) * p.dw_gstride + static_cast<int64_t>(orow) * p.N + gc;
-      return p.dwB + static_cast<int64_t>(g) * p.dw_gstride +
-             static_cast<int64_t>(orow - p.split_row) * p.N + gc;
+    epilogue16<MODE, C>(p, acc, strip, lane + z, wm, wn, g, slot, row0, m_valid, n0,
+                        VARK && op.K == 0);
+    __syncthreads();   // strips are free before the next tile's loads
+  }
+}
+
+// The two-workgroups-per-CU kernel: var-M tiles of the heights the schedule
+// chose, weight-gradient tiles of kMidDwM rows.
+template <int MODE, int PASS>
+__global__ __launch_bounds__(kThreads16, 2) void ffn_gemm16_mid_kernel(const GemmParams p) {
+  constexpr bool VARK = MODE == M_DW;
+  constexpr int kRowsA = VARK ? kMidDwM : kMidMaxH * kMidUnit;
+  __shared__ __attribute__((aligned(16))) char la0[kRowsA * kRowBytes];
+  __shared__ __attribute__((aligned(16))) char lb0[kMidN * kRowBytes];
+  __shared__ __attribute__((aligned(16))) char la1[kRowsA * kRowBytes];
+  __shared__ __attribute__((aligned(16))) char lb1[kMidN * kRowBytes];
+  constexpr int ES = 2;
+  constexpr bool GATED = MODE == M_FWD1_SWIGLU;
+  constexpr int ALAY = a_layout(PASS), BLAY = b_layout(PASS);
+  constexpr int TN = kMidN;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  const Sched& sc = *p.sched;
+  const int n_mt = VARK ? 0 : sc.n_mid[p.mid_list];
+  const int n_items = VARK ? sc.n_segs * p.mtiles_out * p.ntiles : n_mt * p.ntiles;
+  const int G = gridDim.x;
+  const int lbase = (blockIdx.x % kXcds) * (G / kXcds) + blockIdx.x / kXcds;
+
+  for (int round = 0;; ++round) {
+    const int L = round * G + lbase;
+    if (L >= n_items) break;
+    TileOps op;
+    int g, row0, m_valid, n0, h;
+    int slot = -1, mt, nt;
+    if constexpr (!VARK) {
+      int mti;
+      decode_banded(L, n_mt, p.ntiles, mti, nt);
+      const int2 tm = p.mtile[mti];
+      g = tm.x & 255;
+      h = tm.x >> 8;
+      row0 = p.offsets[g] + tm.y;
+      m_valid = min(h * kMidUnit, sc.rows[g] - tm.y);
+      op.a = {p.A + static_cast<int64_t>(row0) * p.lda, nullptr, p.lda, m_valid, 0};
+      op.K = p.K;
+      const char* bg = p.B + static_cast<int64_t>(g) * p.b_gstride;
+      if constexpr (GATED) {
+        n0 = nt * (TN / 2);
+        op.b = {bg + static_cast<int64_t>(n0) * p.ldb,
+                p.B2 + static_cast<int64_t>(g) * p.b_gstride + static_cast<int64_t>(n0) * p.ldb,
+                p.ldb, min(TN / 2, p.N - n0), 0};
+      } else if constexpr (BLAY == L_KC) {
+        n0 = nt * TN;
+        op.b = {bg + static_cast<int64_t>(n0) * p.ldb, nullptr, p.ldb, min(TN, p.N - n0), 0};
+      } else {
+        n0 = nt * TN;
+        op.b = {bg + static_cast<int64_t>(n0) * ES,
+                p.B2 ? p.B2 + static_cast<int64_t>(g) * p.b_gstride + static_cast<int64_t>(n0) * ES
+                     : nullptr,
+                p.ldb, min(TN, p.N - n0), p.B2 ? p.kmsplit : 0x7FFFFFFF};
+      }
+    } else {
+      const int tmn = p.mtiles_out * p.ntiles;
+      const int si = L / tmn;
+      decode_banded(L - si * tmn, p.mtiles_out, p.ntiles, mt, nt);
+      const int4 sg = p.seg[si];
+      g = sg.x;
+      h = kMidDwM / kMidUnit;
+      slot = sg.w;
+      const int k1 = min(sg.z, sc.rows[g]);
+      const int64_t krow = static_cast<int64_t>(p.offsets[g]) + sg.y;
+      row0 = mt * kMidDwM;
+      n0 = nt * TN;
+      m_valid = min(kMidDwM, p.M_out - row0);
+      op.a = {p.A + krow * p.lda + static_cast<int64_t>(row0) * ES, nullptr, p.lda, m_valid,
+              0x7FFFFFFF};
+      op.b = {p.B + krow * p.ldb + static_cast<int64_t>(n0) * ES, nullptr, p.ldb,
+              min(TN, p.N - n0), 0x7FFFFFFF};
+      op.K = max(0, k1 - sg.y);
+    }
+    auto run = [&](auto hc) {
+      constexpr int RB = decltype(hc)::value;
+      using C = Tile16<RB, 4>;
+      int zt, z;   // opaque zeros: see ffn_gemm16_kernel
+      asm volatile("s_mov_b32 %0, 0" : "=s"(zt));
+      floatx4 acc[RB][4];
+      mainloop_mid<RB, ALAY, BLAY, GATED>(op, la0, lb0, la1, lb1, acc, zt);
+      asm volatile("s_mov_b32 %0, 0" : "=s"(z));
+      float* strip = reinterpret_cast<float*>((wave < 2 ? lb0 : lb1) + (wave & 1) * C::kStripBytes + z);
+      epilogue16<MODE, C>(p, acc, strip, lane + z, wm, wn, g, slot, row0, m_valid, n0,
+                          VARK && op.K == 0);
     };
     if constexpr (VARK) {
-      if (op.K == 0) {
-        // no rows to contract over (an expert without rows): the tile is
-        // zero; each lane stores 8 zeros per row pass straight to memory,
-        // with no staging, so the tile costs only its stores.  Every wave
-        // of the workgroup takes this path, and none touched the LDS.
-        constexpr int LR = WC / 8, RG = 64 / LR;
-        const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll 4
-        for (int r = 0; r < WR; r += RG) {
-          const int lm = wr0 + r + el / LR, gc = n0 + wn * WC + (el % LR) * 8;
-          if (lm < m_valid && gc < p.N) {
-            float* dst = dw_dst(row0 + lm, gc);
-            *reinterpret_cast<float4*>(dst) = zero;
-            *reinterpret_cast<float4*>(dst + 4) = zero;
-          }
-        }
-        continue;
-      }
-    }
-    // ReLU / GELU layers: the epilogue is specialised on the activation, one
-    // uniform branch per tile instead of one per element
-    auto epilogue = [&](auto act_c) {
-    constexpr int ACT = decltype(act_c)::value;
-    if constexpr (MODE == M_FWD1_SWIGLU) {
-      // strip columns [0,U): H1, [U,2U): H3 of hidden units n0 + U wn + u, U =
-      // WC / 2; LU lanes cover a row's U units, 8 each
-      constexpr int U = WC / 2, LU = U / 8, RU = 64 / LU;
-#pragma unroll
-      for (int i = 0; i < C::RB; ++i) {
-        stage16<C>(strip, acc, i, el);
-#pragma unroll
-        for (int it = 0; it < 16 / RU; ++it) {
-          const int r = it * RU + el / LU, u8 = (el % LU) * 8;
-          const int lm = wr0 + 16 * i + r;
-          const int gc = n0 + wn * U + u8;
-          if (lm < m_valid && gc < p.N) {
-            // H1 and H3 rounded to bf16 once: the packed bits are stored and
-            // their values feed the activation
-            float h1[8], h3[8], a[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-              h1[e] = strip[r * kP + u8 + e];
-              h3[e] = strip[r * kP + U + u8 + e];
-            }
-            const uint4 b1 = pack8(h1), b3 = pack8(h3);
-            unpack8(b1, h1);
-            unpack8(b3, h3);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) a[e] = h1[e] * sigm(h1[e]) * h3[e];
-            const int64_t grow = row0 + lm;
-            if (p.H1) {
-              *reinterpret_cast<uint4*>(p.H1 + grow * p.ldh + static_cast<int64_t>(gc) * ES) = b1;
-              *reinterpret_cast<uint4*>(p.H3 + grow * p.ldh + static_cast<int64_t>(gc) * ES) = b3;
-            }
-            store_vec<T>(p.C + grow * p.ldc + static_cast<int64_t>(gc) * ES, a);
-          }
-        }
-      }
-    } else if constexpr (MODE == M_BWD_DA || MODE == M_BWD_DA_SWIGLU) {
-      // dH = dA act'(H): (row block, row group) iterations, each reading 8
-      // saved pre-activations (two planes for SwiGLU) per lane, issued kPf
-      // iterations ahead of their use into a ring of kPf + 1 registers.  LR
-      // lanes cover a row of the wave block, RG rows form a group, GB groups
-      // a 16-row block.
-      constexpr bool SW = MODE == M_BWD_DA_SWIGLU;
-      constexpr int LR = WC / 8, RG = 64 / LR, GB = 16 / RG;
-      constexpr int kIt = C::RB * GB, kPf = 4, kRing = kPf + 1;
-      Raw8<T> q1[kRing], q3[kRing];
-      auto pos = [&](int n, int& lm, int& gc) {
-        lm = wr0 + 16 * (n / GB) + RG * (n % GB) + el / LR;
-        gc = n0 + wn * WC + (el % LR) * 8;
-      };
-      auto issue = [&](int n) {
-        int lm, gc;
-        pos(n, lm, gc);
-        const bool ok = lm < m_valid && gc < p.N;
-        // out-of-tile lanes read the tile's first valid element instead
-        const int64_t o = static_cast<int64_t>(row0 + (ok ? lm : 0)) * p.ldh +
-                          static_cast<int64_t>(ok ? gc : n0) * ES;
-        q1[n % kRing].load(p.H1 + o);
-        if constexpr (SW) q3[n % kRing].load(p.H3 + o);
-      };
-#pragma unroll
-      for (int n = 0; n < kPf; ++n) issue(n);
-#pragma unroll
-      for (int n = 0; n < kIt; ++n) {
-        if (n + kPf < kIt) issue(n + kPf);
-        if (n % GB == 0) stage16<C>(strip, acc, n / GB, el);
-        int lm, gc;
-        pos(n, lm, gc);
-        if (lm < m_valid && gc < p.N) {
-          const int r = RG * (n % GB) + el / LR, c8 = (el % LR) * 8;
-          const int64_t grow = row0 + lm;
-          float h1[8], g1[8];
-          q1[n % kRing].to_f(h1);
-          if constexpr (SW) {
-            float h3[8], g3[8];
-            q3[n % kRing].to_f(h3);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-              // d silu(h1) h3 / dh1 = h3 sg (1 + h1 (1 - sg)), d / dh3 = h1 sg
-              const float da = strip[r * kP + c8 + e];
-              const float sg = sigm(h1[e]);
-              const float t = da * sg, u = t * h3[e];
-              g1[e] = __builtin_fmaf(u, __builtin_fmaf(-h1[e], sg, h1[e]), u);
-              g3[e] = t * h1[e];
-            }
-            store_vec<T>(p.C + grow * p.ldc + static_cast<int64_t>(gc) * ES, g1);
-            store_vec<T>(p.C + grow * p.ldc + static_cast<int64_t>(p.f + gc) * ES, g3);
-          } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-              g1[e] = strip[r * kP + c8 + e] * act_grad_f(h1[e], ACT);
-            store_vec<T>(p.C + grow * p.ldc + static_cast<int64_t>(gc) * ES, g1);
-          }
-        }
-      }
+      run(std::integral_constant<int, kMidDwM / kMidUnit>{});
     } else {
-      constexpr int LR = WC / 8, RG = 64 / LR;   // lanes per row, rows per pass
-#pragma unroll
-      for (int i = 0; i < C::RB; ++i) {
-        stage16<C>(strip, acc, i, el);
-#pragma unroll
-        for (int it = 0; it < 16 / RG; ++it) {
-          const int r = RG * it + el / LR, c8 = (el % LR) * 8;
-          const int lm = wr0 + 16 * i + r;
-          const int gc = n0 + wn * WC + c8;
-          if (lm < m_valid && gc < p.N) {
-            const float* sp = strip + r * kP + c8;
-            if constexpr (MODE == M_DW) {
-              float* dst = dw_dst(row0 + lm, gc);
-              *reinterpret_cast<float4*>(dst) = make_float4(sp[0], sp[1], sp[2], sp[3]);
-              *reinterpret_cast<float4*>(dst + 4) = make_float4(sp[4], sp[5], sp[6], sp[7]);
-            } else {
-              float v[8];
-#pragma unroll
-              for (int e = 0; e < 8; ++e) v[e] = sp[e];
-              const int64_t grow = row0 + lm;
-              if constexpr (MODE == M_FWD1) {
-                if constexpr (ACT == ACT_RELU) {
-                  // ReLU commutes with the rounding to bf16 (round(max(h, 0)) =
-                  // max(round(h), 0)), and ReLU layers keep A alone
-#pragma unroll
-                  for (int e = 0; e < 8; ++e) v[e] = fmaxf(v[e], 0.f);
-                } else {
-                  // H rounded to bf16 once: the packed bits are stored and
-                  // their values feed the activation
-                  const uint4 hb = pack8(v);
-                  float hh[8];
-                  unpack8(hb, hh);
-#pragma unroll
-                  for (int e = 0; e < 8; ++e) v[e] = act_f(hh[e], ACT);
-                  if (p.H1)
-                    *reinterpret_cast<uint4*>(p.H1 + grow * p.ldh + static_cast<int64_t>(gc) * ES) = hb;
-                }
-              }
-              store_vec<T>(p.C + grow * p.ldc + static_cast<int64_t>(gc) * ES, v);
-            }
-          }
-        }
+      switch (h) {
+        case 1: run(std::integral_constant<int, 1>{}); break;
+        case 2: run(std::integral_constant<int, 2>{}); break;
+        case 3: run(std::integral_constant<int, 3>{}); break;
+        case 4: run(std::integral_constant<int, 4>{}); break;
+        case 5: run(std::integral_constant<int, 5>{}); break;
+        default: run(std::integral_constant<int, 6>{}); break;
       }
-    }
-    };
-    if constexpr (MODE == M_FWD1 || MODE == M_BWD_DA) {
-      if (p.act == ACT_RELU) epilogue(std::integral_constant<int, ACT_RELU>{});
-      else epilogue(std::integral_constant<int, ACT_GELU>{});
-    } else {
-      epilogue(std::integral_constant<int, ACT_SWIGLU>{});
     }
     __syncthreads();   // strips are free before the next tile's loads
   }
@@ -1937,10 +2171,10 @@ struct FfnPlan {
   int E, d, f, F;            // F = f (relu/gelu) or 2f (swiglu)
   int64_t rows_alloc;
   size_t es;
-  int max_mtiles, max_mtiles_s, max_segs, max_slots, tmn_min;
+  int max_mtiles, max_mid, max_segs, max_slots, tmn_min;
   int64_t slot_elems;
   // byte offsets inside the workspace
-  size_t o_sched, o_mtile, o_mtile_s, o_seg, o_end_sched;
+  size_t o_sched, o_mtile, o_mid, o_seg, o_end_sched;
   size_t o_abuf, o_dh, o_part, o_wt13, total_fwd, total_bwd, total_bwd_wt;
 };
 
@@ -1957,7 +2191,7 @@ bool make_plan(moe_dtype dt, moe_act act, int E, int d, int f, int64_t rows_allo
   const int64_t max_ld = static_cast<int64_t>(pl.es) * (2 * static_cast<int64_t>(f) > d ? 2 * static_cast<int64_t>(f) : d);
   if (max_ld > kMaxOperandRowBytes) return false;
   pl.max_mtiles = cdiv(rows_alloc, BM) + E;
-  pl.max_mtiles_s = cdiv(rows_alloc, BM_S) + E;
+  pl.max_mid = cdiv(rows_alloc, kMidUnit) + E;
   const int tmn2 = cdiv(d, BM) * cdiv(f, BN);
   const int tmn13 = cdiv(pl.F, BM) * cdiv(d, BN);
   pl.tmn_min = tmn2 < tmn13 ? tmn2 : tmn13;
@@ -1971,7 +2205,7 @@ bool make_plan(moe_dtype dt, moe_act act, int E, int d, int f, int64_t rows_allo
   size_t o = 0;
   pl.o_sched = o; o = align_up(o + sizeof(Sched), 256);
   pl.o_mtile = o; o = align_up(o + sizeof(int2) * pl.max_mtiles, 256);
-  pl.o_mtile_s = o; o = align_up(o + sizeof(int2) * pl.max_mtiles_s, 256);
+  pl.o_mid = o; o = align_up(o + 2 * sizeof(int2) * pl.max_mid, 256);
   pl.o_seg = o;   o = align_up(o + sizeof(int4) * pl.max_segs, 256);
   pl.o_end_sched = o;
   const size_t es = pl.es;
@@ -1990,13 +2224,17 @@ bool make_plan(moe_dtype dt, moe_act act, int E, int d, int f, int64_t rows_allo
   return true;
 }
 
+// nt0, nt1: column tiles (of kMidN columns) of the call's products with N = f
+// (K = d) and with N = d (K = k1), for the heights of the two mid tile lists.
 moe_status launch_schedule(hipStream_t s, const FfnPlan& pl, const int32_t* offsets,
-                           const int32_t* rows, char* ws) {
+                           const int32_t* rows, int nt0, int nt1, int k1, char* ws) {
   MOE_TIMED("ffn_schedule", s);
-  schedule_kernel<<<1, 64, 0, s>>>(
-      offsets, rows, pl.E, pl.rows_alloc, pl.max_mtiles, pl.max_mtiles_s, pl.max_segs, pl.tmn_min,
-      pl.max_slots, reinterpret_cast<Sched*>(ws + pl.o_sched),
-      reinterpret_cast<int2*>(ws + pl.o_mtile), reinterpret_cast<int2*>(ws + pl.o_mtile_s),
+  const SchedArgs a = {pl.E, pl.rows_alloc, pl.max_mtiles, pl.max_mid, pl.max_segs, pl.tmn_min,
+                       pl.max_slots, {nt0, nt1}, {cdiv(pl.d, 64), cdiv(k1, 64)},
+                       2 * persistent_grid()};
+  schedule_kernel<<<1, 64 * kSchedWaves, 0, s>>>(
+      offsets, rows, a, reinterpret_cast<Sched*>(ws + pl.o_sched),
+      reinterpret_cast<int2*>(ws + pl.o_mtile), reinterpret_cast<int2*>(ws + pl.o_mid),
       reinterpret_cast<int4*>(ws + pl.o_seg));
   MOE_LAUNCH_CHECK();
   return MOE_OK;
@@ -2013,39 +2251,46 @@ GemmParams base_params(const FfnPlan& pl, const int32_t* offsets, char* ws) {
 }
 
 // Tile choice of the bf16 products (moe_set_gemm_tiles: 0 automatic, 1 the
-// 256x256 kernel only, 2 the 128x128 kernel only).
+// 256x256 kernel only, 2 the two-workgroups-per-CU kernel only).
 int g_tile_mode = 0;
 
-// The 128x128 kernel runs two workgroups per CU, so one's prologue and
-// epilogue overlap the other's MFMAs, but it reads twice the operand bytes
-// per flop: on products that fill every CU for many rounds it takes about
-// 1.3 times as long per flop as the 256x256 kernel.  It pays off where the
-// 256x256 tiles leave CUs idle, mostly in the last round.  The host knows
-// N, K and the row budget, not the per-expert rows, so it estimates both
-// kernels' tile counts as if each expert held rows_alloc / E rows, counts
-// the rounds of the persistent grids (one 256x256 tile or two 128x128
-// tiles per CU at a time), and takes the 128x128 kernel when its rounds,
-// each worth about 0.65 of a 256x256 round, take less time.  With K of 512
-// or less (8 K steps per tile) a 256x256 tile's unoverlapped prologue and
-// epilogue weigh more, and a 128x128 round is worth about 0.55 of one
-// (measured on 512 x 2048 products of 1000-row experts).  K = 0: not known
-// on the host (weight gradients).
-bool use_small_tiles(const FfnPlan& pl, moe_dtype dt, bool vark, bool gated, int N, int M_out,
-                     int K) {
+// The two-workgroups-per-CU kernel's smaller tiles leave fewer CUs idle in
+// the last round and overlap one tile's prologue and epilogue with the
+// other's MFMAs, but read more operand bytes per flop.  The host knows N, K
+// and the row budget, not the per-expert rows, so it takes every expert to
+// hold rows_alloc / E rows and half a tile's raggedness, and compares the two
+// kernels' estimated times: rounds of 256x256 tiles of 1.4 us per K step
+// (1.2 where at most half the CUs have one) and 10 us of prologue and
+// epilogue, 13 with an activation, against the least mid_time over the
+// heights.  (Whole products, big against mid, us, same box: 16 experts of
+// 1024 +- 30 rows, 512 -> 2048 84 / 60, 2048 -> 512 61 / 45; 16 of 512 +- 20
+// rows, 1024 -> 4096 104 / 93, 4096 -> 1024 110 / 87; 32 of 2048, 2048 ->
+// 8192 1885 / 2089, 8192 -> 2048 1773 / 2105.)  Weight gradients (K not known
+// on the host) compare rounds, a round of 128x128 tiles taking 0.65 of one of
+// 256x256 tiles.
+bool use_mid_tiles(const FfnPlan& pl, moe_dtype dt, bool vark, bool gated, bool act, int N,
+                   int M_out, int K) {
   if (dt != MOE_BF16) return false;
   if (g_tile_mode == 1) return false;
   if (g_tile_mode == 2) return true;
+  const int G = persistent_grid();
+  if (vark) {
+    const int64_t big = static_cast<int64_t>(pl.E) * cdiv(M_out, BM) * cdiv(N, BN);
+    const int64_t mid = static_cast<int64_t>(pl.E) * cdiv(M_out, kMidDwM) * cdiv(N, kMidN);
+    return 13 * ((mid + 2 * G - 1) / (2 * G)) < 20 * ((big + G - 1) / G);
+  }
+  const int steps = cdiv(K, 64);
   const int64_t per = cdiv(pl.rows_alloc, pl.E);
-  auto tiles = [&](int tm, int tn) -> int64_t {
-    const int64_t nt = cdiv(N, gated ? tn / 2 : tn);
-    return vark ? static_cast<int64_t>(pl.E) * cdiv(M_out, tm) * nt
-                : static_cast<int64_t>(pl.E) * cdiv(per, tm) * nt;
-  };
-  const int64_t G = persistent_grid();
-  const int64_t rounds_big = (tiles(BM, BN) + G - 1) / G;
-  const int64_t rounds_small = (tiles(BM_S, BM_S) + 2 * G - 1) / (2 * G);
-  const int64_t w = K > 0 && K <= 512 ? 11 : 13;
-  return w * rounds_small < 20 * rounds_big;
+  const int64_t big = pl.E * (2 * per + BM) / (2 * BM) * cdiv(N, gated ? BN / 2 : BN);
+  const int64_t t_big = (big + G - 1) / G * ((2 * big <= G ? 1200 : 1400) * static_cast<int64_t>(steps) +
+                                             (act ? 13000 : 10000));
+  int64_t t_mid = 0;
+  for (int h = 1; h <= kMidMaxH; ++h) {
+    const int64_t n = (2 * per + kMidUnit + 2 * kMidUnit * h - 1) / (2 * kMidUnit * h);
+    const int64_t t = mid_time(n * pl.E * cdiv(N, gated ? kMidN / 2 : kMidN), h, 2 * G, steps);
+    if (h == 1 || t < t_mid) t_mid = t;
+  }
+  return t_mid < t_big;
 }
 
 // dX with a transposed copy of [W1; W3] (moe_set_dx_weight_copy: 0
@@ -2074,17 +2319,20 @@ const char* pass_name(int pass) {
 template <int MODE, int PASS>
 moe_status launch_gemm(hipStream_t s, moe_dtype dt, const FfnPlan& pl, char* ws, GemmParams p) {
   constexpr bool VARK = MODE == M_DW, GATED = MODE == M_FWD1_SWIGLU;
-  const bool small = use_small_tiles(pl, dt, VARK, GATED, p.N, p.M_out, VARK ? 0 : p.K);
-  const int tm = small ? BM_S : BM, tn = small ? BM_S : BN;
+  constexpr bool ACTIVE = MODE != M_STORE && MODE != M_DW;
+  const bool mid = use_mid_tiles(pl, dt, VARK, GATED, ACTIVE, p.N, p.M_out, VARK ? 0 : p.K);
+  const int tm = mid ? kMidDwM : BM, tn = mid ? kMidN : BN;
   p.ntiles = cdiv(p.N, GATED ? tn / 2 : tn);
   if (VARK) p.mtiles_out = cdiv(p.M_out, tm);
-  if (small) p.mtile = reinterpret_cast<const int2*>(ws + pl.o_mtile_s);
+  // tile list 0: the products with N = f (H, dA); list 1: N = d (Y, dX)
+  p.mid_list = PASS == P_FWD_H || PASS == P_BWD_DA ? 0 : 1;
+  if (mid) p.mtile = reinterpret_cast<const int2*>(ws + pl.o_mid) + p.mid_list * static_cast<int64_t>(pl.max_mid);
   // the persistent grid, or fewer workgroups (a multiple of 8, for the XCD
   // mapping) when even the most tiles the schedule can list are fewer
   const int64_t max_items = VARK ? static_cast<int64_t>(pl.max_segs) * p.mtiles_out * p.ntiles
-                                 : static_cast<int64_t>(small ? pl.max_mtiles_s : pl.max_mtiles) *
+                                 : static_cast<int64_t>(mid ? pl.max_mid : pl.max_mtiles) *
                                        p.ntiles;
-  const int64_t full = (small ? 2 : 1) * static_cast<int64_t>(persistent_grid());
+  const int64_t full = (mid ? 2 : 1) * static_cast<int64_t>(persistent_grid());
   const int grid = static_cast<int>(std::min(full, std::max<int64_t>(kXcds, (max_items + kXcds - 1) / kXcds * kXcds)));
   if constexpr ((MODE == M_FWD1 || MODE == M_FWD1_SWIGLU || MODE == M_STORE) &&
                 (PASS == P_FWD_H || PASS == P_FWD_Y)) {
@@ -2100,10 +2348,10 @@ moe_status launch_gemm(hipStream_t s, moe_dtype dt, const FfnPlan& pl, char* ws,
     }
   }
   MOE_TIMED(pass_name(PASS), s);
-  if (dt == MOE_BF16 && small)
-    ffn_gemm16_kernel<MODE, PASS, TileSmall><<<grid, kThreads16, 0, s>>>(p);
+  if (dt == MOE_BF16 && mid)
+    ffn_gemm16_mid_kernel<MODE, PASS><<<grid, kThreads16, 0, s>>>(p);
   else if (dt == MOE_BF16)
-    ffn_gemm16_kernel<MODE, PASS, TileBig><<<grid, kThreads16, 0, s>>>(p);
+    ffn_gemm16_kernel<MODE, PASS><<<grid, kThreads16, 0, s>>>(p);
   else
     ffn_gemm_f32_kernel<MODE, PASS><<<grid, kThreads, 0, s>>>(p);
   MOE_LAUNCH_CHECK();
@@ -2192,7 +2440,8 @@ extern "C" moe_status moe_expert_ffn_fwd(void* stream, moe_dtype dt, moe_act act
   if (!workspace || workspace_bytes < pl.total_fwd || !aligned16(workspace)) return MOE_EWORKSPACE;
   hipStream_t s = static_cast<hipStream_t>(stream);
   char* ws = static_cast<char*>(workspace);
-  MOE_TRY(launch_schedule(s, pl, offsets, rows, ws));
+  MOE_TRY(launch_schedule(s, pl, offsets, rows, cdiv(f, act == MOE_SWIGLU ? kMidN / 2 : kMidN),
+                          cdiv(d, kMidN), f, ws));
   const int64_t es = static_cast<int64_t>(pl.es);
   const int64_t plane = rows_alloc * f * es;   // one [rows_alloc, f] plane of h_save
   const bool sw = act == MOE_SWIGLU;
@@ -2253,7 +2502,7 @@ extern "C" moe_status moe_expert_ffn_bwd(void* stream, moe_dtype dt, moe_act act
   if (!workspace || workspace_bytes < pl.total_bwd || !aligned16(workspace)) return MOE_EWORKSPACE;
   hipStream_t s = static_cast<hipStream_t>(stream);
   char* ws = static_cast<char*>(workspace);
-  MOE_TRY(launch_schedule(s, pl, offsets, rows, ws));
+  MOE_TRY(launch_schedule(s, pl, offsets, rows, cdiv(f, kMidN), cdiv(d, kMidN), pl.F, ws));
   const int64_t es = static_cast<int64_t>(pl.es);
   const bool sw = act == MOE_SWIGLU;
   const int F = pl.F;

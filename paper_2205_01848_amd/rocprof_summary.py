@@ -43,14 +43,12 @@ def source_hash() -> str:
 
 
 def short_name(name: str) -> str:
-    # bf16 products: ffn_gemm16_kernel<MODE, PASS, Tile16<RB, CB, MINB>> (the
-    # 128x128-tile instances, Tile16<4, 4, 2>, named with a _t128 suffix);
-    # fp32: ffn_gemm_f32_kernel<MODE, PASS>
-    m = re.search(r"ffn_gemm(16|_f32)_kernel<(\d+), (\d+)[,>]", name)
+    # bf16 products: ffn_gemm16_kernel<MODE, PASS> (256x256 tiles) and
+    # ffn_gemm16_mid_kernel<MODE, PASS> (128-column tiles, suffix _mid); fp32:
+    # ffn_gemm_f32_kernel<MODE, PASS>
+    m = re.search(r"ffn_gemm(16|16_mid|_f32)_kernel<(\d+), (\d+)[,>]", name)
     if m:
-        small = re.search(r"Tile16<4, 4, 2>", name) is not None
-        return (PASS_NAMES[int(m.group(3))] + ("_f32" if m.group(1) == "_f32" else "")
-                + ("_t128" if small else ""))
+        return PASS_NAMES[int(m.group(3))] + {"16": "", "16_mid": "_mid", "_f32": "_f32"}[m.group(1)]
     # fp32 forward of small layers: ffn_gemm_f32_tiny_kernel<MODE> (modes 0, 1:
     # the first product, 2: the second)
     m = re.search(r"ffn_gemm_f32_tiny_kernel<(\d+)>", name)

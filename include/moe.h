@@ -164,6 +164,26 @@ moe_status moe_dispatch(void* stream, moe_dtype dt, int T, int d, int E, int k,
                         int32_t* status, void* workspace,
                         size_t workspace_bytes);
 
+/* Workspace bytes of moe_route. [host] */
+size_t moe_route_workspace_bytes(int T, int E, int k);
+
+/*
+ * moe_route - the load count, the capacities and the dispatch of one batch in
+ * one call: dynamic != 0: moe_count, moe_update_capacity with those counts,
+ * moe_dispatch; dynamic == 0: moe_update_capacity with counts = NULL (Eq. 4),
+ * moe_dispatch.  The same results and errors, in one to four launches.
+ *   num, den, cap_min, row_align as moe_update_capacity
+ *   capacity [E], offsets [E+1] out; the other arguments as moe_dispatch
+ *   workspace moe_route_workspace_bytes(T,E,k) bytes.
+ */
+moe_status moe_route(void* stream, moe_dtype dt, int T, int d, int E, int k,
+                     const void* x, const int32_t* ids, int dynamic, int num,
+                     int den, int cap_min, int row_align, int64_t rows_alloc,
+                     int32_t* capacity, int32_t* offsets, int32_t* counts,
+                     int32_t* fill, int32_t* dest_row, int32_t* src,
+                     void* x_disp, int32_t* status, void* workspace,
+                     size_t workspace_bytes);
+
 /*
  * moe_dispatch_noalloc - moe_dispatch for callers that cannot allocate
  * device memory (code under HIP graph capture, tight serving loops,

@@ -33,6 +33,10 @@ SIGNATURES = {
     "moe_dispatch_workspace_bytes": (_c_size, [_c_int, _c_int, _c_int]),
     "moe_dispatch": (_c_int, [_p, _c_int, _c_int, _c_int, _c_int, _c_int, _p, _p, _p, _p,
                               _c_i64, _p, _p, _p, _p, _p, _p, _p, _c_size]),
+    "moe_route_workspace_bytes": (_c_size, [_c_int, _c_int, _c_int]),
+    "moe_route": (_c_int, [_p, _c_int, _c_int, _c_int, _c_int, _c_int, _p, _p, _c_int, _c_int,
+                           _c_int, _c_int, _c_int, _c_i64, _p, _p, _p, _p, _p, _p, _p, _p, _p,
+                           _c_size]),
     "moe_dispatch_noalloc": (_c_int, [_p, _c_int, _c_int, _c_int, _c_int, _c_int, _p, _p, _p,
                                       _p, _c_i64, _p, _p, _p, _p, _p, _p]),
     "moe_dispatch_noalloc_max_assignments": (_c_size, []),
@@ -216,6 +220,27 @@ def moe_dispatch(x, ids, E, capacity, offsets, rows_alloc, counts, fill, dest_ro
                               _ptr(offsets), rows_alloc, _ptr(counts), _ptr(fill),
                               _ptr(dest_row), _ptr(src), _ptr(x_disp), _ptr(status), _ptr(ws),
                               _nbytes(ws)), "moe_dispatch")
+
+
+def moe_route_workspace_bytes(T, E, k) -> int:
+    return lib().moe_route_workspace_bytes(T, E, k)
+
+
+def moe_route(x, ids, E, dynamic, num, den, cap_min, rows_alloc, capacity, offsets, counts, fill,
+              dest_row, src, x_disp, status, ws, row_align=1):
+    """moe_count (dynamic), moe_update_capacity and moe_dispatch in one call."""
+    T, d = x.shape
+    k = ids.shape[1]
+    _need(ids, T * k, "ids", _I32)
+    for t, n, name in ((capacity, E, "capacity"), (offsets, E + 1, "offsets"),
+                       (counts, E, "counts"), (fill, E, "fill"), (dest_row, T * k, "dest_row"),
+                       (src, rows_alloc, "src"), (status, 1, "status")):
+        _need(t, n, name, _I32)
+    _need(x_disp, rows_alloc * d, "x_disp", x.dtype)
+    _check(lib().moe_route(_stream(), _dt(x), T, d, E, k, _ptr(x), _ptr(ids), int(dynamic), num,
+                           den, cap_min, row_align, rows_alloc, _ptr(capacity), _ptr(offsets),
+                           _ptr(counts), _ptr(fill), _ptr(dest_row), _ptr(src), _ptr(x_disp),
+                           _ptr(status), _ptr(ws), _nbytes(ws)), "moe_route")
 
 
 def moe_dispatch_noalloc_max_assignments() -> int:

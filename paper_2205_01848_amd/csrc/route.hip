@@ -13,6 +13,7 @@
 // one wavefront per token, 16-byte vector loads/stores along the row, so x
 // is read once even when k rows are written.
 
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 
@@ -65,40 +66,57 @@ __global__ __launch_bounds__(256) void count_kernel(const int32_t* __restrict__ 
   if (threadIdx.x < E && h[threadIdx.x]) atomicAdd(&counts[threadIdx.x], h[threadIdx.x]);
 }
 
-// Eq. 4 / dynamic capacity factors, exact 64-bit integer ceil, + offsets:
-// expert e's region starts at the sum of the earlier capacities, each
-// rounded up to a multiple of row_align rows.
+// The capacity rule of a call: Eq. 4 (num / den = alpha) or, when dynamic,
+// ceil(num / den * count), in exact 64-bit integer arithmetic, clamped to
+// [cap_min, T]; regions start at multiples of align rows.
+struct CapRule {
+  int dynamic, num, den, cap_min, align;
+};
+__device__ __forceinline__ int capacity_of(const CapRule& c, int T, int k, int E, int count) {
+  int64_t v;
+  if (c.dynamic) {
+    const uint64_t n = static_cast<uint64_t>(c.num) * static_cast<uint32_t>(max(count, 0)) +
+                       static_cast<uint32_t>(c.den - 1);
+    v = n >> 32 ? static_cast<int64_t>(n / static_cast<uint32_t>(c.den))
+                : static_cast<int64_t>(static_cast<uint32_t>(n) / static_cast<uint32_t>(c.den));
+  } else {
+    v = (static_cast<int64_t>(c.num) * T * k + static_cast<int64_t>(c.den) * E - 1) /
+        (static_cast<int64_t>(c.den) * E);
+  }
+  v = max(v, static_cast<int64_t>(c.cap_min));
+  return static_cast<int>(min(v, static_cast<int64_t>(T)));
+}
+
+// First row of expert lane's region (lanes below E of one wavefront, their
+// capacities in cap): the sum of the earlier capacities, each rounded up to
+// a multiple of the alignment; `total` gets the end of the last region.
+__device__ __forceinline__ int region_start(const CapRule& c, int cap, int E, int& total) {
+  const int lane = threadIdx.x & 63;
+  const int mine = lane < E ? (cap + c.align - 1) / c.align * c.align : 0;
+  int v = mine;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int u = __shfl_up(v, o, 64);
+    if (lane >= o) v += u;
+  }
+  total = __shfl(v, 63, 64);
+  return v - mine;
+}
+
 __global__ __launch_bounds__(64) void capacity_kernel(int T, int k, int E,
                                                       const int32_t* __restrict__ counts,
-                                                      int num, int den, int cap_min,
-                                                      int row_align,
+                                                      const CapRule rule,
                                                       int32_t* __restrict__ capacity,
                                                       int32_t* __restrict__ offsets) {
-  __shared__ int64_t c[kMaxE];
   const int e = threadIdx.x;
+  const int cap = e < E ? capacity_of(rule, T, k, E, counts ? counts[e] : 0) : 0;
+  int total;
+  const int off = region_start(rule, cap, E, total);
   if (e < E) {
-    int64_t v;
-    if (counts) {
-      const int64_t cnt = max(counts[e], 0);
-      v = (static_cast<int64_t>(num) * cnt + den - 1) / den;
-    } else {
-      v = (static_cast<int64_t>(num) * T * k + static_cast<int64_t>(den) * E - 1) /
-          (static_cast<int64_t>(den) * E);
-    }
-    v = max(v, static_cast<int64_t>(cap_min));
-    v = min(v, static_cast<int64_t>(T));
-    c[e] = v;
-    capacity[e] = static_cast<int32_t>(v);
+    capacity[e] = cap;
+    offsets[e] = off;
   }
-  __syncthreads();
-  if (e == 0) {
-    int64_t run = 0;
-    for (int i = 0; i < E; ++i) {
-      offsets[i] = static_cast<int32_t>(run);
-      run += (c[i] + row_align - 1) / row_align * row_align;
-    }
-    offsets[E] = static_cast<int32_t>(run);
-  }
+  if (e == 0) offsets[E] = total;
 }
 
 // Dispatch step 1: chunk histograms; also initialises src[] to -1.
@@ -123,6 +141,12 @@ __global__ __launch_bounds__(256) void route_hist_kernel(
   if (threadIdx.x < E) hist[static_cast<size_t>(blockIdx.x) * E + threadIdx.x] = h[threadIdx.x];
 }
 
+// Usable rows of a region of `cap` rows that starts at row `off` of a buffer
+// of rows_alloc.
+__device__ __forceinline__ int own_room(int cap, int off, int64_t rows_alloc) {
+  return static_cast<int>(max(int64_t(0), min(static_cast<int64_t>(cap), rows_alloc - off)));
+}
+
 // Usable rows of expert e's region: its capacity, clamped to the region the
 // offsets give it and to rows_alloc (0 for a region starting out of range).
 __device__ __forceinline__ int64_t region_room(const int32_t* __restrict__ capacity,
@@ -140,14 +164,16 @@ __device__ __forceinline__ int64_t region_room(const int32_t* __restrict__ capac
 }
 
 // Dispatch step 2: per-expert exclusive scan over chunks, counts, the usable
-// capacity of each region, fill.
+// capacity of each region, fill.  OWN: the capacities and offsets follow from
+// the counts just summed, and are written too.
+template <bool OWN>
 __global__ __launch_bounds__(64) void route_scan_kernel(
-    const int32_t* __restrict__ hist, int nblk, int E, const int32_t* __restrict__ capacity,
-    const int32_t* __restrict__ offsets, int64_t rows_alloc, int32_t* __restrict__ base,
-    int32_t* __restrict__ cap_eff, int32_t* __restrict__ counts, int32_t* __restrict__ fill,
-    int32_t* status) {
-  const int e = threadIdx.x;
-  if (e >= E) return;
+    const int32_t* __restrict__ hist, int nblk, int T, int k, int E, const CapRule rule,
+    int32_t* __restrict__ capacity, int32_t* __restrict__ offsets, int64_t rows_alloc,
+    int32_t* __restrict__ base, int32_t* __restrict__ cap_eff, int32_t* __restrict__ counts,
+    int32_t* __restrict__ fill, int32_t* status) {
+  const int lane = threadIdx.x;
+  const int e = min(lane, E - 1);   // lanes past E repeat expert E - 1 (same values written)
   int run = 0;
   int b = 0;
   for (; b + 8 <= nblk; b += 8) {   // loads of 8 chunks issued before their adds
@@ -164,9 +190,25 @@ __global__ __launch_bounds__(64) void route_scan_kernel(
     base[static_cast<size_t>(b) * E + e] = run;
     run += hist[static_cast<size_t>(b) * E + e];
   }
+  int64_t room;
+  int cap;
+  if constexpr (OWN) {
+    cap = capacity_of(rule, T, k, E, run);
+    int total;
+    const int off = region_start(rule, cap, E, total);
+    room = own_room(cap, off, rows_alloc);
+    if (lane < E) {
+      capacity[e] = cap;
+      offsets[e] = off;
+    }
+    if (lane == 0) offsets[E] = total;
+  } else {
+    cap = capacity[e];
+    room = region_room(capacity, offsets, rows_alloc, e);
+  }
+  if (lane >= E) return;
   counts[e] = run;
-  const int64_t room = region_room(capacity, offsets, rows_alloc, e);
-  if (room < capacity[e]) atomicOr(status, MOE_STATUS_REGION);
+  if (room < cap) atomicOr(status, MOE_STATUS_REGION);
   cap_eff[e] = static_cast<int32_t>(room);
   fill[e] = static_cast<int32_t>(min(static_cast<int64_t>(run), room));
 }
@@ -175,15 +217,17 @@ __global__ __launch_bounds__(64) void route_scan_kernel(
 // SCAN: small batches (at most kScanChunks chunks) skip step 2; every
 // workgroup sums the histograms of the chunks before its own, and workgroup
 // 0 writes counts, fill and the region status bit.
+// OWN (with SCAN): every workgroup also derives the capacities and offsets
+// from the counts, and workgroup 0 writes them.
 constexpr int kScanChunks = 64;
-template <bool SCAN>
+template <bool SCAN, bool OWN>
 __global__ __launch_bounds__(256) void route_rank_kernel(
     const int32_t* __restrict__ ids, int T, int E, int k, const int32_t* __restrict__ base,
-    const int32_t* __restrict__ cap_eff, const int32_t* __restrict__ offsets,
+    const int32_t* __restrict__ cap_eff, int32_t* __restrict__ offsets,
     int32_t* __restrict__ dest_row, int32_t* __restrict__ src,
-    const int32_t* __restrict__ hist, int nblk, const int32_t* __restrict__ capacity,
-    int64_t rows_alloc, int32_t* __restrict__ counts, int32_t* __restrict__ fill,
-    int32_t* status) {
+    const int32_t* __restrict__ hist, int nblk, const CapRule rule,
+    int32_t* __restrict__ capacity, int64_t rows_alloc, int32_t* __restrict__ counts,
+    int32_t* __restrict__ fill, int32_t* status) {
   __shared__ int run[kMaxE];
   __shared__ int wcnt[4][kMaxE];
   __shared__ int capv[kMaxE];
@@ -204,18 +248,36 @@ __global__ __launch_bounds__(256) void route_rank_kernel(
       tot[wave][lane] = all;
     }
     __syncthreads();
-    if (threadIdx.x < E) {
-      const int e = threadIdx.x;
-      run[e] = wcnt[0][e] + wcnt[1][e] + wcnt[2][e] + wcnt[3][e];
+    if (wave == 0) {
+      const int e = min(lane, E - 1);
       const int total = tot[0][e] + tot[1][e] + tot[2][e] + tot[3][e];
-      const int64_t room = region_room(capacity, offsets, rows_alloc, e);
-      if (blockIdx.x == 0) {
-        counts[e] = total;
-        fill[e] = static_cast<int32_t>(min(static_cast<int64_t>(total), room));
-        if (room < capacity[e]) atomicOr(status, MOE_STATUS_REGION);
+      int cap, off;
+      int64_t room;
+      if constexpr (OWN) {
+        cap = capacity_of(rule, T, k, E, total);
+        int end;
+        off = region_start(rule, cap, E, end);
+        room = own_room(cap, off, rows_alloc);
+        if (blockIdx.x == 0 && lane < E) {
+          capacity[e] = cap;
+          offsets[e] = off;
+          if (e == E - 1) offsets[E] = end;
+        }
+      } else {
+        cap = capacity[e];
+        off = offsets[e];
+        room = region_room(capacity, offsets, rows_alloc, e);
       }
-      capv[e] = static_cast<int32_t>(room);
-      offv[e] = offsets[e];
+      if (lane < E) {
+        run[e] = wcnt[0][e] + wcnt[1][e] + wcnt[2][e] + wcnt[3][e];
+        if (blockIdx.x == 0) {
+          counts[e] = total;
+          fill[e] = static_cast<int32_t>(min(static_cast<int64_t>(total), room));
+          if (room < cap) atomicOr(status, MOE_STATUS_REGION);
+        }
+        capv[e] = static_cast<int32_t>(room);
+        offv[e] = off;
+      }
     }
   } else {
     if (threadIdx.x < E) {
@@ -355,6 +417,215 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(
   for_row_batches<kRowBatch>(nvec, lane, [&](auto nb, int v) {
     gather_vecs<decltype(nb)::value>(xr, dst, nvec, v, x_disp);
   });
+}
+
+// ---- count + capacity + dispatch of small batches --------------------------
+// At a few thousand tokens each of the routing kernels costs its launch (about
+// 4.7 us between dependent kernels) and little else, so moe_route does the
+// whole of it in two launches, or one for the smallest batches.  Tokens come
+// in chunks of CT, one workgroup each; per chunk and choice j the histogram
+// kernel counts the live assignments to every expert (hist[chunk][j * E +
+// e]); then every workgroup of the second kernel sums the histograms of all
+// chunks and of those before its own, derives capacities, offsets and the
+// first position of each of its (j, e) groups, ranks its tokens with one
+// wavefront per choice, and copies their rows.  Up to kTinyAssign
+// assignments every workgroup counts the ids itself instead of reading
+// histograms, and a workgroup takes four tokens.  The first rows are loaded
+// before the routing they do not depend on.
+constexpr int kTinyAssign = 2048;     // 8 ids per thread
+constexpr int kMaxHist = 16384;       // histogram entries every workgroup reads (64 KB)
+constexpr int kMaxPairs = kMaxK * kMaxE;
+
+// Lane's assignment among the same choice of the wavefront's tokens: eq =
+// lanes with the same expert (0 for a lane without a live assignment).
+__device__ __forceinline__ uint64_t same_expert(int e, bool live) {
+  uint64_t eq = __ballot(live);
+#pragma unroll
+  for (int b = 0; b < 6; ++b) {
+    const bool bit = live && ((e >> b) & 1);
+    const uint64_t m = __ballot(bit);
+    eq &= bit ? m : ~m;
+  }
+  return live ? eq : 0;
+}
+
+// One wavefront per chunk of CT tokens.
+template <int CT>
+__global__ __launch_bounds__(256) void route_chunk_hist_kernel(
+    const int32_t* __restrict__ ids, int T, int E, int k, int nchunk, int32_t* __restrict__ hist,
+    int32_t* status) {
+  __shared__ int h[4][kMaxPairs];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int chunk = blockIdx.x * 4 + wave;
+  const int P = k * E;
+  for (int i = lane; i < P; i += 64) h[wave][i] = 0;
+  __builtin_amdgcn_wave_barrier();
+  const int t = chunk * CT + lane;
+  for (int j = 0; j < k; ++j) {
+    const bool live = lane < CT && t < T && live_assignment(ids, t, j, k, E, status);
+    const int e = live ? ids[static_cast<size_t>(t) * k + j] : 0;
+    const uint64_t eq = same_expert(e, live);
+    if (live && (eq & ((uint64_t(1) << lane) - 1)) == 0) h[wave][j * E + e] = __popcll(eq);
+  }
+  __builtin_amdgcn_wave_barrier();
+  if (chunk >= nchunk) return;
+  for (int i = lane; i < P; i += 64) hist[static_cast<size_t>(chunk) * P + i] = h[wave][i];
+}
+
+struct RouteArgs {
+  const uint4* x;
+  const int32_t* ids;
+  const int32_t* hist;   // null: counted from the ids
+  int T, E, k, nvec, nchunk;
+  CapRule rule;
+  int64_t rows_alloc;
+  int32_t *capacity, *offsets, *counts, *fill, *dest_row, *src;
+  uint4* x_disp;
+  int32_t* status;
+};
+
+template <int CT>
+__global__ __launch_bounds__(256) void route_fused_kernel(const RouteArgs a) {
+  __shared__ int tot[kMaxPairs], bef[kMaxPairs];   // then bef: first position of (j, e) here
+  __shared__ int capv[kMaxE], offv[kMaxE], fillv[kMaxE];
+  __shared__ int dst[CT][kMaxK];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int E = a.E, k = a.k, P = k * E;
+  const int chunk = blockIdx.x, t0 = chunk * CT;
+  // wavefront w copies the rows of tokens t0 + w, t0 + w + 4, ...: UB of them
+  // and VB vectors of each per lane at a time
+  constexpr int NT = CT / 4, UB = NT < 8 ? NT : 8, VB = UB == 1 ? 4 : 1;
+  uint4 val[UB][VB];
+  auto load = [&](int first, int v) {
+#pragma unroll
+    for (int u = 0; u < UB; ++u)
+#pragma unroll
+      for (int w = 0; w < VB; ++w)
+        if (v + 64 * w < a.nvec)
+          val[u][w] = a.x[static_cast<size_t>(min(first + 4 * u, a.T - 1)) * a.nvec + v + 64 * w];
+  };
+  load(t0 + wave, lane);
+  for (int i = tid; i < P; i += 256) tot[i] = bef[i] = 0;
+  for (int i = tid; i < CT * kMaxK; i += 256) (&dst[0][0])[i] = -1;
+  __syncthreads();
+  if (a.hist) {
+    // threads in groups of P (or more pairs than threads: one group), each
+    // group every G-th chunk, eight loads in flight per thread
+    const int Pt = min(P, 256), G = 256 / Pt, grp = tid / Pt;
+    if (grp < G) {
+      for (int p = tid - grp * Pt; p < P; p += Pt) {
+        int all = 0, lo = 0;
+        for (int c0 = grp; c0 < a.nchunk; c0 += 8 * G) {
+          int v[8];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) {
+            const int c = c0 + u * G;
+            v[u] = c < a.nchunk ? a.hist[static_cast<size_t>(c) * P + p] : 0;
+          }
+#pragma unroll
+          for (int u = 0; u < 8; ++u) {
+            all += v[u];
+            lo += c0 + u * G < chunk ? v[u] : 0;
+          }
+        }
+        atomicAdd(&tot[p], all);
+        atomicAdd(&bef[p], lo);
+      }
+    }
+  } else {
+    const int n = a.T * k;
+    for (int q = tid; q < n; q += 256) {
+      const int t = q / k, j = q - t * k;
+      if (live_assignment(a.ids, t, j, k, E, chunk == 0 ? a.status : nullptr)) {
+        const int p = j * E + a.ids[q];
+        atomicAdd(&tot[p], 1);
+        if (t < t0) atomicAdd(&bef[p], 1);
+      }
+    }
+  }
+  __syncthreads();
+  if (wave == 0) {
+    const int e = min(lane, E - 1);
+    int count = 0;
+    for (int j = 0; j < k; ++j) count += tot[j * E + e];
+    const int cap = capacity_of(a.rule, a.T, k, E, count);
+    int end;
+    const int off = region_start(a.rule, cap, E, end);
+    const int room = own_room(cap, off, a.rows_alloc);
+    if (lane < E) {
+      int run = 0;
+      for (int j = 0; j < k; ++j) {
+        bef[j * E + e] += run;
+        run += tot[j * E + e];
+      }
+      capv[e] = room;
+      offv[e] = off;
+      fillv[e] = min(count, room);
+      if (chunk == 0) {
+        a.counts[e] = count;
+        a.capacity[e] = cap;
+        a.offsets[e] = off;
+        if (e == E - 1) a.offsets[E] = end;
+        a.fill[e] = min(count, room);
+        if (room < cap) atomicOr(a.status, MOE_STATUS_REGION);
+      }
+    }
+  }
+  __syncthreads();
+  // ranks: one wavefront per choice, lane = token
+  for (int j = wave; j < k; j += 4) {
+    const int t = t0 + lane;
+    const bool in = lane < CT && t < a.T;
+    const bool live = in && live_assignment(a.ids, t, j, k, E, nullptr);
+    const size_t as = static_cast<size_t>(t) * k + j;
+    const int e = live ? a.ids[as] : 0;
+    const uint64_t eq = same_expert(e, live);
+    int r = -1;
+    if (live) {
+      const int pos = bef[j * E + e] + __popcll(eq & ((uint64_t(1) << lane) - 1));
+      if (pos < capv[e]) {
+        r = offv[e] + pos;
+        a.src[r] = static_cast<int32_t>(as);
+        dst[lane][j] = r;
+      }
+    }
+    if (in) a.dest_row[as] = r;
+  }
+  // rows that hold no assignment: past the kept ones of their region, or past
+  // the last region
+  for (int64_t r = static_cast<int64_t>(chunk) * 256 + tid; r < a.rows_alloc;
+       r += static_cast<int64_t>(gridDim.x) * 256) {
+    int lo = 0, hi = E - 1;   // last expert whose region starts at or before r
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (offv[mid] <= r) lo = mid;
+      else hi = mid - 1;
+    }
+    if (r - offv[lo] >= fillv[lo]) a.src[r] = -1;
+  }
+  __syncthreads();
+#pragma unroll 1
+  for (int i0 = 0; i0 < NT; i0 += UB) {
+    const int first = t0 + wave + 4 * i0;
+    if (first >= a.T) break;
+    for (int v = lane; v < a.nvec; v += 64 * VB) {
+      if (i0 > 0 || v >= 64 * VB) load(first, v);   // the first batch is there already
+#pragma unroll
+      for (int u = 0; u < UB; ++u)
+#pragma unroll
+        for (int w = 0; w < VB; ++w) hold(val[u][w]);
+      for (int j = 0; j < k; ++j)
+#pragma unroll
+        for (int u = 0; u < UB; ++u) {
+          const int r = __builtin_amdgcn_readfirstlane(dst[wave + 4 * (i0 + u)][j]);
+          if (r < 0) continue;
+#pragma unroll
+          for (int w = 0; w < VB; ++w)
+            if (v + 64 * w < a.nvec) a.x_disp[static_cast<size_t>(r) * a.nvec + v + 64 * w] = val[u][w];
+        }
+    }
+  }
 }
 
 // dx is the layer's last output of a step and is not read again by the
@@ -677,18 +948,22 @@ extern "C" moe_status moe_count(void* stream, int T, int E, int k, const int32_t
   return MOE_OK;
 }
 
+static bool cap_rule_ok(int T, int E, int k, int num, int den, int cap_min, int row_align) {
+  if (!shape_ok(T, E, k) || num < 1 || den < 1 || cap_min < 0) return false;
+  if (row_align < 1 || row_align > kMaxRowAlign) return false;
+  return static_cast<int64_t>(T) * E + static_cast<int64_t>(row_align - 1) * E < (int64_t(1) << 31);
+}
+
 extern "C" moe_status moe_update_capacity(void* stream, int T, int k, int E,
                                           const int32_t* counts, int num, int den,
                                           int cap_min, int row_align, int32_t* capacity,
                                           int32_t* offsets) {
-  if (!shape_ok(T, E, k) || num < 1 || den < 1 || cap_min < 0) return MOE_EINVAL;
-  if (row_align < 1 || row_align > kMaxRowAlign) return MOE_EINVAL;
-  if (!capacity || !offsets) return MOE_EINVAL;
-  if (static_cast<int64_t>(T) * E + static_cast<int64_t>(row_align - 1) * E >= (int64_t(1) << 31))
+  if (!cap_rule_ok(T, E, k, num, den, cap_min, row_align) || !capacity || !offsets)
     return MOE_EINVAL;
   MOE_TIMED("capacity", static_cast<hipStream_t>(stream));
-  capacity_kernel<<<1, 64, 0, static_cast<hipStream_t>(stream)>>>(
-      T, k, E, counts, num, den, cap_min, row_align, capacity, offsets);
+  const CapRule rule = {counts != nullptr, num, den, cap_min, row_align};
+  capacity_kernel<<<1, 64, 0, static_cast<hipStream_t>(stream)>>>(T, k, E, counts, rule, capacity,
+                                                                  offsets);
   MOE_LAUNCH_CHECK();
   return MOE_OK;
 }
@@ -719,12 +994,13 @@ static moe_status dispatch_args_ok(moe_dtype dt, int T, int d, int E, int k, con
   return MOE_OK;
 }
 
-// The launches of moe_dispatch; `workspace` holds moe_dispatch_workspace_bytes.
+// The launches of moe_dispatch (rule null) or, with a capacity rule, of
+// moe_route; `workspace` holds moe_dispatch_workspace_bytes.
 static moe_status dispatch_launch(hipStream_t s, moe_dtype dt, int T, int d, int E, int k,
-                                  const void* x, const int32_t* ids, const int32_t* capacity,
-                                  const int32_t* offsets, int64_t rows_alloc, int32_t* counts,
-                                  int32_t* fill, int32_t* dest_row, int32_t* src, void* x_disp,
-                                  int32_t* status, void* workspace);
+                                  const void* x, const int32_t* ids, const CapRule* rule,
+                                  int32_t* capacity, int32_t* offsets, int64_t rows_alloc,
+                                  int32_t* counts, int32_t* fill, int32_t* dest_row, int32_t* src,
+                                  void* x_disp, int32_t* status, void* workspace);
 
 extern "C" moe_status moe_dispatch(void* stream, moe_dtype dt, int T, int d, int E, int k,
                                    const void* x, const int32_t* ids,
@@ -737,20 +1013,21 @@ extern "C" moe_status moe_dispatch(void* stream, moe_dtype dt, int T, int d, int
   if (st != MOE_OK) return st;
   const size_t need = moe_dispatch_workspace_bytes(T, E, k);
   if (!workspace || workspace_bytes < need) return MOE_EWORKSPACE;
-  return dispatch_launch(static_cast<hipStream_t>(stream), dt, T, d, E, k, x, ids, capacity,
-                         offsets, rows_alloc, counts, fill, dest_row, src, x_disp, status,
-                         workspace);
+  return dispatch_launch(static_cast<hipStream_t>(stream), dt, T, d, E, k, x, ids, nullptr,
+                         const_cast<int32_t*>(capacity), const_cast<int32_t*>(offsets), rows_alloc,
+                         counts, fill, dest_row, src, x_disp, status, workspace);
 }
 
 static moe_status dispatch_launch(hipStream_t s, moe_dtype dt, int T, int d, int E, int k,
-                                  const void* x, const int32_t* ids, const int32_t* capacity,
-                                  const int32_t* offsets, int64_t rows_alloc, int32_t* counts,
-                                  int32_t* fill, int32_t* dest_row, int32_t* src, void* x_disp,
-                                  int32_t* status, void* workspace) {
+                                  const void* x, const int32_t* ids, const CapRule* rule,
+                                  int32_t* capacity, int32_t* offsets, int64_t rows_alloc,
+                                  int32_t* counts, int32_t* fill, int32_t* dest_row, int32_t* src,
+                                  void* x_disp, int32_t* status, void* workspace) {
   const int nblk = route_nblk(T, k);
   int32_t* hist = static_cast<int32_t*>(workspace);
   int32_t* base = hist + static_cast<size_t>(nblk) * E;
   int32_t* cap_eff = base + static_cast<size_t>(nblk) * E;
+  const CapRule cr = rule ? *rule : CapRule{};
   {
     MOE_TIMED("route_hist", s);
     route_hist_kernel<<<nblk, 256, 0, s>>>(ids, T, E, k, nblk, rows_alloc, hist, src, status);
@@ -759,21 +1036,22 @@ static moe_status dispatch_launch(hipStream_t s, moe_dtype dt, int T, int d, int
   if (nblk <= kScanChunks) {
     // the rank kernel does the scan too (and writes counts and fill)
     MOE_TIMED("route_rank", s);
-    route_rank_kernel<true><<<nblk, 256, 0, s>>>(ids, T, E, k, nullptr, nullptr, offsets,
-                                                 dest_row, src, hist, nblk, capacity,
-                                                 rows_alloc, counts, fill, status);
+    (rule ? route_rank_kernel<true, true> : route_rank_kernel<true, false>)<<<nblk, 256, 0, s>>>(
+        ids, T, E, k, nullptr, nullptr, offsets, dest_row, src, hist, nblk, cr, capacity,
+        rows_alloc, counts, fill, status);
     MOE_LAUNCH_CHECK();
   } else {
     {
       MOE_TIMED("route_scan", s);
-      route_scan_kernel<<<1, 64, 0, s>>>(hist, nblk, E, capacity, offsets, rows_alloc, base,
-                                         cap_eff, counts, fill, status);
+      (rule ? route_scan_kernel<true> : route_scan_kernel<false>)<<<1, 64, 0, s>>>(
+          hist, nblk, T, k, E, cr, capacity, offsets, rows_alloc, base, cap_eff, counts, fill,
+          status);
       MOE_LAUNCH_CHECK();
     }
     MOE_TIMED("route_rank", s);
-    route_rank_kernel<false><<<nblk, 256, 0, s>>>(ids, T, E, k, base, cap_eff, offsets,
-                                                  dest_row, src, nullptr, nblk, nullptr,
-                                                  rows_alloc, nullptr, nullptr, nullptr);
+    route_rank_kernel<false, false><<<nblk, 256, 0, s>>>(
+        ids, T, E, k, base, cap_eff, offsets, dest_row, src, nullptr, nblk, cr, nullptr,
+        rows_alloc, nullptr, nullptr, nullptr);
     MOE_LAUNCH_CHECK();
   }
   if (T == 0) return MOE_OK;
@@ -781,6 +1059,67 @@ static moe_status dispatch_launch(hipStream_t s, moe_dtype dt, int T, int d, int
   const int nvec = static_cast<int>(static_cast<int64_t>(d) * esize(dt) / 16);
   gather_rows_kernel<<<nblocks(T, kRowWaves), 256, 0, s>>>(
       static_cast<const uint4*>(x), dest_row, T, k, nvec, static_cast<uint4*>(x_disp));
+  MOE_LAUNCH_CHECK();
+  return MOE_OK;
+}
+
+// ---- count + capacity + dispatch in one call ---------------------------------
+// Tokens per chunk of the fused kernels (32 or 64), or 0 for the general path
+// (chunks of kChunk assignments, a scan and a gather of their own): the
+// histogram entries every workgroup sums bound the batch.  The smaller chunk
+// gives the row copies more workgroups.  Past the bound every workgroup would
+// read over 64 KB of histograms for about 50 KB of rows.  The two kernels
+// against the six (fill, count, capacity, histogram, rank, gather): T = 8192,
+// k = 2, E = 16, d = 512: 14 us against 32 us; T = 16384, k = 1, E = 64, d =
+// 1024: 23 us against 42 us; T = 32, k = 2, E = 8, d = 4096 (one kernel): 5.6
+// us against 29 us.
+static int route_chunk_tokens(int T, int E, int k) {
+  for (int ct = 32; ct <= 64; ct *= 2)
+    if (T > 0 && static_cast<int64_t>(nblocks(T, ct)) * k * E <= kMaxHist) return ct;
+  return 0;
+}
+
+extern "C" size_t moe_route_workspace_bytes(int T, int E, int k) {
+  const size_t general = moe_dispatch_workspace_bytes(T, E, k);
+  return general && route_chunk_tokens(T, E, k)
+             ? std::max(general, static_cast<size_t>(kMaxHist) * sizeof(int32_t))
+             : general;
+}
+
+extern "C" moe_status moe_route(void* stream, moe_dtype dt, int T, int d, int E, int k,
+                                const void* x, const int32_t* ids, int dynamic, int num, int den,
+                                int cap_min, int row_align, int64_t rows_alloc, int32_t* capacity,
+                                int32_t* offsets, int32_t* counts, int32_t* fill,
+                                int32_t* dest_row, int32_t* src, void* x_disp, int32_t* status,
+                                void* workspace, size_t workspace_bytes) {
+  const moe_status st = dispatch_args_ok(dt, T, d, E, k, x, ids, capacity, offsets, rows_alloc,
+                                         counts, fill, dest_row, src, x_disp, status);
+  if (st != MOE_OK) return st;
+  if (!cap_rule_ok(T, E, k, num, den, cap_min, row_align)) return MOE_EINVAL;
+  if (!workspace || workspace_bytes < moe_route_workspace_bytes(T, E, k)) return MOE_EWORKSPACE;
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  const CapRule rule = {dynamic != 0, num, den, cap_min, row_align};
+  const int ct = route_chunk_tokens(T, E, k);
+  if (ct == 0)
+    return dispatch_launch(s, dt, T, d, E, k, x, ids, &rule, capacity, offsets, rows_alloc, counts,
+                           fill, dest_row, src, x_disp, status, workspace);
+  const bool tiny = T * k <= kTinyAssign;
+  const int nchunk = nblocks(T, tiny ? 4 : ct);
+  int32_t* hist = nullptr;
+  if (!tiny) {
+    hist = static_cast<int32_t*>(workspace);
+    MOE_TIMED("route_hist", s);
+    (ct == 32 ? route_chunk_hist_kernel<32> : route_chunk_hist_kernel<64>)<<<
+        nblocks(nchunk, 4), 256, 0, s>>>(ids, T, E, k, nchunk, hist, status);
+    MOE_LAUNCH_CHECK();
+  }
+  const RouteArgs a = {static_cast<const uint4*>(x), ids, hist, T, E, k,
+                       static_cast<int>(static_cast<int64_t>(d) * esize(dt) / 16), nchunk, rule,
+                       rows_alloc, capacity, offsets, counts, fill, dest_row, src,
+                       static_cast<uint4*>(x_disp), status};
+  MOE_TIMED("dispatch_gather", s);
+  (tiny ? route_fused_kernel<4> : ct == 32 ? route_fused_kernel<32> : route_fused_kernel<64>)<<<
+      nchunk, 256, 0, s>>>(a);
   MOE_LAUNCH_CHECK();
   return MOE_OK;
 }
@@ -845,8 +1184,9 @@ extern "C" moe_status moe_dispatch_noalloc(void* stream, moe_dtype dt, int T, in
   void* ws = nullptr;
   const moe_status sa = scratch_address(s, &ws);
   if (sa != MOE_OK) return sa;
-  return dispatch_launch(s, dt, T, d, E, k, x, ids, capacity, offsets, rows_alloc, counts, fill,
-                         dest_row, src, x_disp, status, ws);
+  return dispatch_launch(s, dt, T, d, E, k, x, ids, nullptr, const_cast<int32_t*>(capacity),
+                         const_cast<int32_t*>(offsets), rows_alloc, counts, fill, dest_row, src,
+                         x_disp, status, ws);
 }
 
 // Calls f with std::integral_constant<int, KT> for the smallest pick bound

@@ -71,7 +71,8 @@ class MoELayer:
         self.x_disp = e(max(R, 1), d)
         self.y_disp = e(max(R, 1), d)
         self.y = e(T, d)
-        self.ws_dispatch = B.workspace(B.moe_dispatch_workspace_bytes(T, E, k), self.dev)
+        self.ws_dispatch = B.workspace(max(B.moe_dispatch_workspace_bytes(T, E, k),
+                                           B.moe_route_workspace_bytes(T, E, k)), self.dev)
         self.ws_fwd = B.workspace(B.moe_ffn_fwd_workspace_bytes(dt, self.act, E, d, f, R), self.dev)
         self.backward_enabled = backward
         self.h_save = None
@@ -118,6 +119,12 @@ class MoELayer:
         B.moe_dispatch(x, self.ids if ids is None else ids, self.E, self.capacity, self.offsets,
                        self.rows_alloc, self.counts, self.fill, self.dest_row, self.src,
                        self.x_disp, self.status, self.ws_dispatch)
+
+    def route(self, x, ids, dynamic: bool, num: int, den: int):
+        """count (dynamic), capacity and dispatch of this batch in one call."""
+        B.moe_route(x, ids, self.E, dynamic, num, den, 0, self.rows_alloc, self.capacity,
+                    self.offsets, self.counts, self.fill, self.dest_row, self.src, self.x_disp,
+                    self.status, self.ws_dispatch, row_align=self.row_align)
 
     def ffn_fwd(self, w1, w3, w2, rows: str = "fill"):
         """rows="fill": the method, each expert over its kept rows.
@@ -196,21 +203,21 @@ class MoELayer:
             B.moe_dispatch_bwd(self.dx_disp, self.dest_row, self.E, None, None, self.dx)
 
     # ---- whole layer ---------------------------------------------------------
-    def _capacity(self, capacity, ids, counts_from_batch):
+    def _capacity_dispatch(self, x, capacity, ids, counts_from_batch):
         kind, num, den = capacity
-        if kind == "static":
-            self.capacity_static(num, den)
-        elif kind == "policy":
-            pass            # capacity and offsets uploaded by a CapacityPolicy
+        if kind == "policy":
+            self.dispatch(x, ids)   # capacity and offsets uploaded by a CapacityPolicy
+        elif kind == "static" or counts_from_batch:
+            self.route(x, ids, kind != "static", num, den)
         else:
-            if counts_from_batch:
-                self.count(ids)
             self.capacity_dynamic(num, den)
+            self.dispatch(x, ids)
 
     def forward(self, x, w1, w3, w2, *, w_g=None, bias=None, renorm=0, ids=None, weights=None,
                 capacity=("dynamic", 1, 1), counts_from_batch=True, rows="fill",
                 balance: Optional[float] = None):
-        """gate (or cached ids) -> [count ->] capacity -> dispatch -> FFN -> combine.
+        """gate (or cached ids) -> [count ->] capacity -> dispatch -> FFN -> combine
+        (count, capacity and dispatch in one library call where they follow each other).
 
         capacity = ("static", num, den) | ("dynamic", num, den) | ("policy",
         1, 1); a dynamic rule uses this batch's counts when counts_from_batch,
@@ -222,8 +229,7 @@ class MoELayer:
         if ids is None:
             self.gate(x, w_g, bias, renorm)
             ids, weights = self.ids, self.weights
-        self._capacity(capacity, ids, counts_from_batch)
-        self.dispatch(x, ids)
+        self._capacity_dispatch(x, capacity, ids, counts_from_batch)
         if balance is not None:
             self.balance(balance)
         self.ffn_fwd(w1, w3, w2, rows=rows)
@@ -260,8 +266,7 @@ class MoELayer:
             B.moe_cache_update(self.ids, cached, cache_out, unchanged)
             gate_done = torch.cuda.Event()
             gate_done.record(gs)
-        self._capacity(capacity, cached, True)
-        self.dispatch(x, cached)
+        self._capacity_dispatch(x, capacity, cached, True)
         self.ffn_fwd(w1, w3, w2, rows=rows)
         main.wait_event(gate_done)
         self.combine(self.cached_weights)

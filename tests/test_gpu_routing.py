@@ -315,3 +315,61 @@ def test_policy_uploads_aligned_offsets():
     np.testing.assert_array_equal(to_np(cap), [440, 660, 550, 550])
     np.testing.assert_array_equal(to_np(off), O.exclusive_offsets([440, 660, 550, 550], 256))
     assert rows == int(O.exclusive_offsets([440, 660, 550, 550], 256)[-1])
+
+
+# moe_route against the separate calls: one launch (ids counted by every
+# workgroup), 32- and 64-token chunks with histograms, the general path with
+# and without its scan kernel, and the sizes where the choice changes
+@pytest.mark.parametrize("T,d,E,k,dt", [
+    (1, 8, 1, 1, "bf16"),
+    (31, 24, 5, 3, "f32"),
+    (256, 64, 4, 1, "f32"),
+    (256, 72, 64, 8, "bf16"),
+    (257, 72, 64, 8, "bf16"),          # one assignment row more: histograms
+    (2048, 40, 7, 1, "bf16"),
+    (2049, 40, 7, 1, "bf16"),
+    (1000, 2056, 33, 2, "bf16"),
+    (4096, 16, 64, 2, "bf16"),         # 128 chunks of 32: the most of that size
+    (4097, 16, 64, 2, "bf16"),         # chunks of 64
+    (8192, 16, 64, 2, "bf16"),
+    (8193, 16, 64, 2, "f32"),          # general path
+    (40000, 8, 64, 2, "bf16"),         # with the scan kernel
+])
+@pytest.mark.parametrize("rule", ["static", "dynamic", "tight"])
+def test_route_matches_separate_calls(T, d, E, k, dt, rule):
+    rng = np.random.default_rng(T + E * 7 + k)
+    ids_np = np.argsort(rng.random((T, E)), axis=1)[:, :k].astype(np.int32)
+    ids_np[rng.random((T, k)) < 0.02] = E + 3          # bad ids
+    if k > 1:
+        dup = rng.random(T) < 0.02
+        ids_np[dup, 1] = ids_np[dup, 0]
+    ids = torch.from_numpy(ids_np).to(dev())
+    x = torch.randn(T, d, device=dev()).to(torch_dtype(dt))
+    num, den, cap_min, align = (3, 2, 0, 1) if rule == "static" else (11, 10, 3, 8)
+    R = E * (-(-num * T * k // (den * E)) + align) if rule == "static" else 2 * T * k + 11 * E
+    if rule == "tight":
+        R = max(1, T * k // 2)                          # regions cut by the buffer's end
+    i32 = lambda *s: torch.full(s, 77, dtype=torch.int32, device=dev())
+
+    def buffers():
+        return dict(capacity=i32(E), offsets=i32(E + 1), counts=i32(E), fill=i32(E),
+                    dest_row=i32(T, k), src=i32(R),
+                    x_disp=torch.full((R, d), 5.0, device=dev(), dtype=torch_dtype(dt)),
+                    status=torch.zeros(1, dtype=torch.int32, device=dev()))
+
+    a, b = buffers(), buffers()
+    ws = B.workspace(B.moe_route_workspace_bytes(T, E, k), dev())
+    ws.fill_(255)
+    B.moe_route(x, ids, E, rule != "static", num, den, cap_min, R, a["capacity"], a["offsets"],
+                a["counts"], a["fill"], a["dest_row"], a["src"], a["x_disp"], a["status"], ws,
+                row_align=align)
+    if rule != "static":
+        B.moe_count(ids, E, b["counts"], b["status"])
+    B.moe_update_capacity(T, k, E, b["counts"] if rule != "static" else None, num, den, cap_min,
+                          b["capacity"], b["offsets"], row_align=align)
+    B.moe_dispatch(x, ids, E, b["capacity"], b["offsets"], R, b["counts"], b["fill"],
+                   b["dest_row"], b["src"], b["x_disp"], b["status"],
+                   B.workspace(B.moe_dispatch_workspace_bytes(T, E, k), dev()))
+    torch.cuda.synchronize()
+    for n in a:
+        assert torch.equal(a[n], b[n]), n

@@ -65,6 +65,7 @@ constexpr int kGroupM = 4;      // M tiles per scheduling group
 constexpr int kXcds = 8;
 constexpr int kSplitFloor = 512;  // smallest K chunk of a split dW product
 constexpr int kKc = 64;           // split chunks are multiples of this many rows
+constexpr int kSplitItems = 256;  // work items the split aims at: one 256x256 tile per CU
 constexpr int64_t kMaxOperandRowBytes = (int64_t(1) << 23) - 64;  // 256 rows < 2^31 bytes
 // dx_disp up to this size is produced last in the backward (MI355X has a
 // 256 MB last-level cache; measured on a 268 MB dx_disp, T = 32768 tokens of
@@ -79,7 +80,6 @@ struct Sched {
   int n_mtiles;    // (expert, m0) tiles of BM rows
   int n_mid[2];    // tiles of the two-workgroups-per-CU kernel, per list
   int n_segs;      // (expert, k range) segments of the dW products
-  int kc;          // split chunk (rows)
   int n_slots;     // partial-sum slots used
   int rows[kMaxE];    // clamped rows per expert
   int slot0[kMaxE];   // first partial slot of expert e (split experts)
@@ -225,8 +225,14 @@ __device__ __forceinline__ int find_expert(const int* incl, int E, int t) {
 //    tiles make tiles a little higher rather than one more round of tiles.
 //    An expert's units are spread evenly over its tiles.
 //  * the weight-gradient products (last wavefront) split an expert's rows
-//    into K segments only when few experts carry most rows (about 512 work
-//    items over all of them).
+//    into K segments only when few experts carry most rows: an expert's rows
+//    over the share of all 256x256 tile work that one of kSplitItems CUs
+//    would get, rounded, is its number of segments.  A segment costs the
+//    write and the read of its partial sums: 8 experts of 2048 rows, 1024 x
+//    2816 and 5632 x 1024 gradients, took 154 + 77 and 264 + 77 us (products
+//    + reductions) in two segments each, 123 and 212 us in one; 15,650 of
+//    16,384 rows in one of 64 experts, 4096 x 1024, 343 + 54 us in eight
+//    segments, 325 + 29 us in four.
 // Should a bound be exceeded (inconsistent offsets), one thread instead walks
 // the experts in order and cuts the lists where the bounds stop them.
 struct SchedArgs {
@@ -244,7 +250,7 @@ __global__ __launch_bounds__(64 * kSchedWaves) void schedule_kernel(
     int4* __restrict__ seg) {
   __shared__ int ti[kMaxE], si[kMaxE], mid_incl[kMidMaxH][kMaxE], rw[kMaxE], q0s[kMaxE];
   __shared__ int64_t cost[2][kMidMaxH];
-  __shared__ int kc_s, fit_rows, fit_segs;
+  __shared__ int fit_rows, fit_segs;
   const int E = A.E;
   const int g = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
@@ -284,11 +290,11 @@ __global__ __launch_bounds__(64 * kSchedWaves) void schedule_kernel(
     int64_t kwork = kw;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) kwork += __shfl_xor(kwork, o, 64);
-    int64_t kc = (kwork * A.tmn_min + 511) / 512;
-    kc = (kc + kKc - 1) / kKc * kKc;
+    const int64_t kc = (kwork * A.tmn_min + kSplitItems - 1) / kSplitItems;
     const int kci = static_cast<int>(min(max(kc, static_cast<int64_t>(kSplitFloor)),
-                                         static_cast<int64_t>(0x7FFFFFC0)));
-    const int nsp = g < E ? (m > kci ? (m - 1) / kci + 1 : 1) : 0;
+                                         static_cast<int64_t>(1 << 29)));
+    const int q = m / kci;
+    const int nsp = g < E ? max(1, q + (2 * (m - q * kci) >= kci ? 1 : 0)) : 0;
     const int segs_incl = wave_incl_scan(nsp);
     const int slots_incl = wave_incl_scan(nsp > 1 ? nsp : 0);
     const int slots_total = __shfl(slots_incl, 63, 64);
@@ -296,7 +302,6 @@ __global__ __launch_bounds__(64 * kSchedWaves) void schedule_kernel(
     q0s[g] = nsp > 1 ? slots_incl - nsp : -1;
     if (g == 63) {
       fit_segs = segs_incl <= A.max_segs && slots_total <= A.max_slots;
-      kc_s = kci;
       s->n_slots = slots_total;
     }
   }
@@ -328,7 +333,6 @@ __global__ __launch_bounds__(64 * kSchedWaves) void schedule_kernel(
       s->n_mid[0] = mi2[0][E - 1];
       s->n_mid[1] = mi2[1][E - 1];
       s->n_segs = si[E - 1];
-      s->kc = kc_s;
     }
     for (int t = tid; t < ti[E - 1]; t += nthreads) {
       const int e = find_expert(ti, E, t);
@@ -344,9 +348,11 @@ __global__ __launch_bounds__(64 * kSchedWaves) void schedule_kernel(
     for (int t = tid; t < si[E - 1]; t += nthreads) {
       const int e = find_expert(si, E, t);
       const int first = e ? si[e - 1] : 0, n = si[e] - first, i = t - first;
-      const int64_t k0 = static_cast<int64_t>(i) * kc_s, k1 = k0 + kc_s;
-      seg[t] = make_int4(e, n > 1 ? static_cast<int>(k0) : 0,
-                         n > 1 ? static_cast<int>(min(k1, static_cast<int64_t>(rw[e]))) : rw[e],
+      // equal segments, in whole K steps; the last ones may be short or empty
+      const int64_t len = ((rw[e] + n - 1) / n + kKc - 1) / kKc * kKc;
+      const int64_t me = rw[e];
+      seg[t] = make_int4(e, static_cast<int>(min(i * len, me)),
+                         n > 1 ? static_cast<int>(min((i + 1) * len, me)) : rw[e],
                          n > 1 ? q0s[e] + i : -1);
     }
     return;
@@ -373,7 +379,7 @@ __global__ __launch_bounds__(64 * kSchedWaves) void schedule_kernel(
   }
   s->n_mtiles = nm;
   s->n_mid[0] = s->n_mid[1] = nmid;
-  int64_t kcc = (kwork_c * tmn_min + 511) / 512;
+  int64_t kcc = (kwork_c * tmn_min + kSplitItems - 1) / kSplitItems;
   kcc = (kcc + kKc - 1) / kKc * kKc;
   kcc = max(kcc, static_cast<int64_t>(kSplitFloor));
   int ns = 0, slots = 0;
@@ -393,7 +399,6 @@ __global__ __launch_bounds__(64 * kSchedWaves) void schedule_kernel(
   }
   s->n_segs = ns;
   s->n_slots = slots;
-  s->kc = static_cast<int>(kcc);
 }
 
 // ---------------------------------------------------------------------------

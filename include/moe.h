@@ -520,12 +520,10 @@ int moe_timing_report(char* buf, size_t len);
  * and tiles of 32 to 192 rows and 128 columns (two workgroups per CU; the
  * heights chosen on the device from the rows per expert) -- the latter for
  * products with few tiles per CU; both kernels add every output's products in the same
- * order, so results are identical bit for bit in every mode.  float32: the
- * forward products of small layers (at most 4096 blocks of 32x32 outputs
- * for the row budget) run one wavefront per 32x32 block, the others on
- * 256x256 tiles (the two add in different orders).  1: 256x256 only (both
- * dtypes); 2: 128-column tiles only (bf16; float32 as in mode 0).  Process-wide; read
- * when a product is launched.  Returns MOE_EINVAL for other modes. [host]
+ * order, so results are identical bit for bit in every mode.  1:
+ * 256x256 only; 2: 128-column tiles only.  float32 layers run every product
+ * on 128-column tiles in every mode.  Process-wide; read when a product is
+ * launched.  Returns MOE_EINVAL for other modes. [host]
  */
 moe_status moe_set_gemm_tiles(int mode);
 

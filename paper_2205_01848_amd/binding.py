@@ -517,8 +517,8 @@ def moe_timing_enable(on: bool):
 
 
 def moe_set_gemm_tiles(mode: int):
-    """0: automatic tile choice; 1: 256x256 tiles only (bf16 and fp32); 2: 128-column tiles
-    only (bf16)."""
+    """0: automatic tile choice; 1: 256x256 tiles only; 2: 128-column tiles only (bf16;
+    fp32 always runs on 128-column tiles)."""
     _check(lib().moe_set_gemm_tiles(int(mode)), "moe_set_gemm_tiles")
 
 

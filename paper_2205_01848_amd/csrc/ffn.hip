@@ -13,10 +13,8 @@
 //    32 to 192 rows and 128 columns (two workgroups per CU;
 //    ffn_gemm16_mid_kernel), whose heights the schedule chooses; both add
 //    every output's products in the same order.
-//  * fp32 layers: 8 wavefronts of 128x64 on v_mfma_f32_32x32x2f32 in two
-//    ping-pong teams, one team's MFMAs overlapping the other's LDS reads
-//    (ffn_gemm_f32_kernel); the forward of small fp32 layers instead runs
-//    one wavefront per 32x32 output block (ffn_gemm_f32_tiny_kernel).
+//  * fp32 layers: v_mfma_f32_32x32x2f32 on tiles of 32 to 192 rows and 128
+//    columns, two workgroups per CU (ffn_gemm_f32_kernel).
 //  * var-M products (forward H, Y; backward dA, dX): the M dimension of
 //    expert e is its row count, read on the device; tiles are listed by a
 //    one-workgroup schedule kernel, so no host synchronisation is needed.
@@ -45,22 +43,15 @@ namespace {
 
 constexpr int BM = 256;
 constexpr int BN = 256;
-constexpr int kThreads = 512;                     // 8 wavefronts, two per SIMD
 constexpr int kRowBytes = 128;                    // one K tile of one operand row
 constexpr int kTileBytes = BM * kRowBytes;        // 32 KB
-constexpr int kStripRows = 16;                    // accumulator rows staged per pass
-constexpr int kStripPitch = 72;                   // floats per staged row (64 + 8):
-                                                  // rows 4 apart fall 32 banks apart
-constexpr int kStripBytes = kStripRows * kStripPitch * 4;
-constexpr int kStripsPerArray = kTileBytes / kStripBytes;
-static_assert(3 * kStripsPerArray >= 16, "two staging strips per wave in three operand buffers");
 
-// Tiles of the two-workgroups-per-CU bf16 kernel: kMidN columns, and 1 to
+// Tiles of the two-workgroups-per-CU kernels: kMidN columns, and 1 to
 // kMidMaxH units of kMidUnit rows, chosen per tile.
 constexpr int kMidUnit = 32;
 constexpr int kMidMaxH = 6;
 constexpr int kMidN = 128;
-constexpr int kMidDwM = 128;    // its rows in the weight-gradient products
+constexpr int kMidDwH = 4;      // its units in the bf16 weight-gradient products
 constexpr int kGroupM = 4;      // M tiles per scheduling group
 constexpr int kXcds = 8;
 constexpr int kSplitFloor = 512;  // smallest K chunk of a split dW product
@@ -84,48 +75,6 @@ struct Sched {
   int rows[kMaxE];    // clamped rows per expert
   int slot0[kMaxE];   // first partial slot of expert e (split experts)
   int nsplit[kMaxE];  // K segments of expert e
-};
-
-// 8 consecutive layer-dtype elements <-> 8 floats (16 bytes bf16, 32 bytes fp32)
-template <typename T> __device__ __forceinline__ void store_vec(char* p, const float* v);
-template <> __device__ __forceinline__ void store_vec<uint16_t>(char* p, const float* v) {
-  *reinterpret_cast<uint4*>(p) = pack8(v);
-}
-template <> __device__ __forceinline__ void store_vec<float>(char* p, const float* v) {
-  *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
-  *reinterpret_cast<float4*>(p + 16) = make_float4(v[4], v[5], v[6], v[7]);
-}
-template <typename T> __device__ __forceinline__ void load_vec(const char* p, float* v);
-template <> __device__ __forceinline__ void load_vec<uint16_t>(const char* p, float* v) {
-  unpack8(*reinterpret_cast<const uint4*>(p), v);
-}
-template <> __device__ __forceinline__ void load_vec<float>(const char* p, float* v) {
-  const float4 a = *reinterpret_cast<const float4*>(p);
-  const float4 b = *reinterpret_cast<const float4*>(p + 16);
-  v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
-  v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
-}
-
-// 8 elements as raw bits (one 16-byte vector of bf16, two of fp32), so a
-// load can be issued early and decoded later.
-template <typename T> struct Raw8 {
-  uint4 v[sizeof(T) / 2];
-  __device__ __forceinline__ void load(const char* p) {
-#pragma unroll
-    for (int i = 0; i < static_cast<int>(sizeof(T) / 2); ++i)
-      v[i] = reinterpret_cast<const uint4*>(p)[i];
-  }
-  __device__ __forceinline__ void to_f(float* f) const {
-    if constexpr (sizeof(T) == 2) {
-      unpack8(v[0], f);
-    } else {
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        f[4 * i + 0] = __uint_as_float(v[i].x); f[4 * i + 1] = __uint_as_float(v[i].y);
-        f[4 * i + 2] = __uint_as_float(v[i].z); f[4 * i + 3] = __uint_as_float(v[i].w);
-      }
-    }
-  }
 };
 
 // ---------------------------------------------------------------------------
@@ -192,11 +141,17 @@ __device__ __forceinline__ int2 mid_tile(int rows, int n, int i, int e) {
 // us at h = 4 and 1.21 us at h = 6 with operands in the caches, about a tenth
 // more in a layer; a round of K = 512 at h = 4 takes 3.2 us more than its 8
 // steps.  A last round that leaves at least one of the two places of every
-// CU empty takes about 0.65 of a full one.
-__host__ __device__ inline int64_t mid_time(int64_t tiles, int h, int slots, int steps) {
+// CU empty takes about 0.65 of a full one.  fp32 (K steps of 32): the
+// 16 h MFMAs of a step and wave, 64 cycles each, for both workgroups.
+struct StepCost {
+  int fixed, per_unit;   // ns per K step, ns per K step and unit of rows
+};
+constexpr StepCost kStep16 = {210, 185}, kStepF32 = {60, 890};
+__host__ __device__ inline int64_t mid_time(int64_t tiles, int h, int slots, int steps,
+                                            const StepCost& c) {
   const int64_t full = tiles / slots, rem = tiles - full * slots;
   return (20 * full + (rem == 0 ? 0 : 2 * rem <= slots ? 13 : 20)) *
-         (static_cast<int64_t>(steps) * (210 + 185 * h) + 3200) / 20;
+         (static_cast<int64_t>(steps) * (c.fixed + c.per_unit * h) + 3200) / 20;
 }
 
 // First index g < E whose inclusive prefix exceeds t.
@@ -241,6 +196,7 @@ struct SchedArgs {
   int max_mtiles, max_mid, max_segs, tmn_min, max_slots;
   int nt[2], steps[2];   // column tiles and K steps of the products of the two mid lists
   int slots_mid;         // workgroups of the mid kernel's persistent grid
+  StepCost cost;
 };
 constexpr int kSchedWaves = kMidMaxH + 2;
 
@@ -275,7 +231,7 @@ __global__ __launch_bounds__(64 * kSchedWaves) void schedule_kernel(
     const int tot = __shfl(incl, 63, 64);
     mid_incl[wave][g] = incl;
     if (g < 2)
-      cost[g][wave] = mid_time(static_cast<int64_t>(tot) * A.nt[g], hm, A.slots_mid, A.steps[g]);
+      cost[g][wave] = mid_time(static_cast<int64_t>(tot) * A.nt[g], hm, A.slots_mid, A.steps[g], A.cost);
   } else if (wave == kMidMaxH) {
     ti[g] = wave_incl_scan((m + BM - 1) / BM);
     rw[g] = m;
@@ -470,236 +426,6 @@ __device__ __forceinline__ uint2 read_tr(const char* p) {
   return __builtin_bit_cast(uint2, v);
 }
 
-// fp32 layers: acc += A_tile * B_tile^T over the whole K extent with 8
-// wavefronts in two teams of four, one wave of each team per SIMD.  Team t
-// computes tile rows 128t..128t+127, its wave q columns 64q..64q+63 (gated
-// forward: hidden units 32q..32q+31, W1 then W3).  Each half K step (16
-// values) is a memory phase (12 fragments, LDS -> registers) followed by an
-// MFMA phase (16 block products of four v_mfma_f32_32x32x2f32 each).  Team 1
-// runs one barrier behind team 0, so while one wave of a SIMD issues MFMAs
-// the other reads LDS.  Operand tiles go HBM -> LDS with buffer_load ... lds
-// (no register staging), issued by team 0 one step ahead into the other of
-// two stages.  FULL: every tile row and column is valid; K tails are checked
-// per step either way.
-template <int ALAY, int BLAY, bool GATED, bool FULL>
-__device__ __forceinline__ void mainloop_f32(const TileOps& op, char* la0, char* lb0, char* la1,
-                                             char* lb1, floatx16 (&acc)[4][2]) {
-  constexpr int ES = 4;                   // bytes per element
-  constexpr int KSTEP = kRowBytes / ES;   // k values per step (KC: 128 bytes per row)
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
-  const int team = wave >> 2, wq = wave & 3;
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.f;
-  const int K = op.K;
-  const int nk = (K + KSTEP - 1) / KSTEP;
-  if (nk <= 0) return;
-  const int nk2 = (nk + 1) & ~1;   // odd counts load one all-zero step
-
-  // ---- loads.  A 1 KB load covers one 8-row block of a KC tile (lane l ->
-  // row 8 blk + (l >> 3), physical chunk l & 7, logical chunk (l & 7) ^
-  // swz(row), depending on the parity of blk only), or one k-row of a KM
-  // tile (lane l -> physical elements 4l .. 4l + 3 of k-row blk, column =
-  // segment swizzled by k & 3).
-  const int l3 = lane >> 3;
-  const int co0 = ((lane & 7) ^ swz(l3)) * 16, co1 = ((lane & 7) ^ swz(l3 + 8)) * 16;
-  const int pe = lane * 4;                // KM physical element
-  // KM column of the lane for k-row residue q = k & 3
-  auto km_col = [&](int q) { return (((pe >> 5) ^ q) << 5) + (pe & 31); };
-  auto ld_of = [&](const Operand& o) { return static_cast<int>(o.ld); };
-
-  // one operand, one block, one K step.  rs/rs2: resources (KM: of this step)
-  auto load_op = [&](auto lay, const Operand& o, const __amdgpu_buffer_rsrc_t& rs,
-                     const __amdgpu_buffer_rsrc_t& rs2, char* dst, int blk, int kt, bool kfull,
-                     bool kany, bool gated) {
-    constexpr int LAY = decltype(lay)::value;
-    uint32_t off;
-    int soff;
-    bool second = false;
-    if constexpr (LAY == L_KC) {
-      const int co = (blk & 1) ? co1 : co0;
-      // gated forward: W1/W3 groups of 32 rows
-      const int row0 = gated ? (blk >> 3) * 32 + (blk & 3) * 8 : blk * 8;
-      second = gated && ((blk >> 2) & 1);
-      off = static_cast<uint32_t>(l3 * ld_of(o)) + co;
-      soff = row0 * ld_of(o) + kt * kRowBytes;
-      if (!FULL || !kfull) {
-        const bool ok = (FULL || row0 + l3 < o.rows) && (kfull || kt * kRowBytes + co < K * ES);
-        if (!ok) off = kOob;
-      }
-    } else {
-      const int krel = blk;                        // the block's k-row in the step
-      const int kabs = kt * KSTEP + krel;
-      const int q = krel & 3;                      // k & 3 (steps are multiples of 4 rows)
-      const int col = km_col(q);
-      second = kabs >= o.split;
-      off = static_cast<uint32_t>(col * ES);
-      soff = krel * ld_of(o);
-      if (!FULL || !kfull) {
-        const bool ok = (FULL || col < o.rows) && (kfull || kabs < K);
-        if (!ok) off = kOob;
-      }
-    }
-    if (!kany) off = kOob;
-    if (second)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs2, MOE_LDS(dst + blk * 1024), 16, off, soff, 0, 0);
-    else
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, MOE_LDS(dst + blk * 1024), 16, off, soff, 0, 0);
-  };
-  using KC_ = std::integral_constant<int, L_KC>;
-  using KM_ = std::integral_constant<int, L_KM>;
-  // resources: KC operands over the whole tile, KM operands re-based per step
-  const __amdgpu_buffer_rsrc_t ra_t = tile_rsrc(op.a.base);
-  const __amdgpu_buffer_rsrc_t rb_t = tile_rsrc(op.b.base);
-  const __amdgpu_buffer_rsrc_t rb3_t = tile_rsrc(GATED ? op.b.base2 : op.b.base);
-  auto km_rsrc = [&](const Operand& o, int kt, bool second) {
-    const int64_t k = static_cast<int64_t>(kt) * KSTEP - (second ? o.split : 0);
-    return tile_rsrc((second ? o.base2 : o.base) + k * o.ld);
-  };
-  auto load = [&](int kt, char* sa, char* sb, int b0, int nb) {
-    const bool kfull = (kt + 1) * KSTEP <= K;   // wave-uniform
-    const bool kany = kt * KSTEP < K;
-    __amdgpu_buffer_rsrc_t ra = ra_t, ra2 = ra_t, rb = rb_t, rb2 = rb3_t;
-    if constexpr (ALAY == L_KM) {
-      ra = km_rsrc(op.a, kt, false);
-      ra2 = op.a.base2 ? km_rsrc(op.a, kt, true) : ra;
-    }
-    if constexpr (BLAY == L_KM) {
-      rb = km_rsrc(op.b, kt, false);
-      rb2 = op.b.base2 ? km_rsrc(op.b, kt, true) : rb;
-    }
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      if (i < nb) {
-        if constexpr (ALAY == L_KC) load_op(KC_{}, op.a, ra, ra2, sa, b0 + i, kt, kfull, kany, false);
-        else load_op(KM_{}, op.a, ra, ra2, sa, b0 + i, kt, kfull, kany, false);
-        if constexpr (BLAY == L_KC) load_op(KC_{}, op.b, rb, rb2, sb, b0 + i, kt, kfull, kany, GATED);
-        else load_op(KM_{}, op.b, rb, rb2, sb, b0 + i, kt, kfull, kany, false);
-      }
-    }
-  };
-
-  // ---- fragments.  MFMA operand of lane l: row/column l % 32 of the
-  // sub-tile, k values 4 (2s + l / 32) .. +3 of sub-step s.
-  const int fr_row = lane & 31;
-  // KC: 16-byte reads of row fr_row
-  const int fr_a = (team * 128 + fr_row) * kRowBytes;
-  const int fr_b = (wq * 64 + fr_row) * kRowBytes;
-  // KM: four 4-byte reads, one per k-row (k-row c at physical segment
-  // (column >> 5) ^ c, the swizzle of the loads)
-  auto km_frag = [&](const char* st, int cb, int s) -> uint4 {
-    const int k0 = 4 * (2 * s + (lane >> 5));
-    uint32_t v[4];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int phys = (((cb >> 5) ^ c) << 5) + fr_row;
-      v[c] = *reinterpret_cast<const uint32_t*>(st + (k0 + c) * 1024 + phys * 4);
-    }
-    return make_uint4(v[0], v[1], v[2], v[3]);
-  };
-  uint4 fa[4][2], fb[2][2];   // [sub-tile][k sub-step within the half step]
-  // fragments of k sub-steps 2h and 2h+1 (one half of a K step)
-  auto fread = [&](const char* sa, const char* sb, int h) {
-#pragma unroll
-    for (int s2 = 0; s2 < 2; ++s2) {
-      const int s = 2 * h + s2;
-      const int sw = ((2 * s + (lane >> 5)) ^ swz(fr_row)) << 4;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        if constexpr (ALAY == L_KC)
-          fa[i][s2] = *reinterpret_cast<const uint4*>(sa + fr_a + i * 32 * kRowBytes + sw);
-        else
-          fa[i][s2] = km_frag(sa, team * 128 + i * 32, s);
-      }
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        if constexpr (BLAY == L_KC)
-          fb[j][s2] = *reinterpret_cast<const uint4*>(sb + fr_b + j * 32 * kRowBytes + sw);
-        else
-          fb[j][s2] = km_frag(sb, wq * 64 + j * 32, s);
-      }
-    }
-  };
-  auto mma = [&]() {
-#pragma unroll
-    for (int s2 = 0; s2 < 2; ++s2)
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) mma_f32(acc[i][j], fa[i][s2], fb[j][s2]);
-  };
-  // s_waitcnt immediates (gfx9 encoding)
-  constexpr int kWaitVm0 = 0x0F70;    // vmcnt(0)
-  constexpr int kWaitLgkm0 = 0xC07F;  // lgkmcnt(0)
-  // one ping-pong phase pair: read half h of a stage, then its 16 block products
-  // A wave whose rows or columns of the tile are all beyond the valid ones
-  // (the ragged last tile of an expert, the last column tile) skips its
-  // reads and MFMAs; it still takes part in every barrier.  Its accumulators
-  // stay zero and the epilogue stores none of them.
-  bool active = true;
-  if constexpr (!FULL) {
-    const int wcols = GATED ? 32 : 64;   // the wave's columns (gated: hidden units)
-    active = team * 128 < op.a.rows && wq * wcols < op.b.rows;
-  }
-  auto half = [&](const char* sa, const char* sb, int h, bool wait_loads) {
-    if (active) fread(sa, sb, h);
-    __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_sched_barrier(0);
-    if (active) mma();
-    __builtin_amdgcn_sched_barrier(0);
-    if (wait_loads) __builtin_amdgcn_s_waitcnt(kWaitVm0);
-    __builtin_amdgcn_s_barrier();
-  };
-
-  load(0, la0, lb0, wave * 4, 4);    // stage 0: all eight waves
-  __builtin_amdgcn_s_waitcnt(kWaitVm0);
-  __syncthreads();
-  if (team == 0) {
-    // team 0 also loads stage kt+1 at the start of step kt and waits for it
-    // at the end of the step, four phases later
-    for (int kt = 0; kt < nk2; kt += 2) {
-      load(kt + 1, la1, lb1, wq * 8, 8);
-      half(la0, lb0, 0, false);
-      half(la0, lb0, 1, true);
-      if (kt + 2 < nk2) load(kt + 2, la0, lb0, wq * 8, 8);
-      half(la1, lb1, 0, false);
-      half(la1, lb1, 1, true);
-    }
-    __builtin_amdgcn_s_barrier();
-  } else {
-    __builtin_amdgcn_s_barrier();
-    for (int kt = 0; kt < nk2; kt += 2) {
-      half(la0, lb0, 0, false);
-      half(la0, lb0, 1, false);
-      half(la1, lb1, 0, false);
-      half(la1, lb1, 1, false);
-    }
-  }
-  // every wave has passed the last barrier after its last LDS read: the
-  // operand buffers are free
-}
-
-// Stage rows [16h, 16h+16) of the wave's accumulator row-block i (32 rows x
-// 64 columns) as fp32, row pitch kStripPitch: the lane's registers q in
-// [8h, 8h+8) hold those rows.
-__device__ __forceinline__ void stage_strip(float* strip, const floatx16 (&acc)[4][2], int i,
-                                            int h) {
-  const int lane = threadIdx.x & 63;
-  const int half = lane >> 5, col = lane & 31;
-#pragma unroll
-  for (int j = 0; j < 2; ++j)
-#pragma unroll
-    for (int q = 8 * h; q < 8 * h + 8; ++q) {
-      const int row = ((q >> 2) - 2 * h) * 8 + half * 4 + (q & 3);
-      strip[row * kStripPitch + j * 32 + col] = acc[i][j][q];
-    }
-}
-
 // ---------------------------------------------------------------------------
 // kernel parameters
 // ---------------------------------------------------------------------------
@@ -735,26 +461,11 @@ struct GemmParams {
   const Sched* sched;
   const int2* mtile;
   const int4* seg;
-  int mid_list;       // two-workgroups-per-CU kernel: its tile list
+  int mid_list;       // two-workgroups-per-CU kernels: the tile list
+  int dw_h;           // and the units of a weight-gradient tile
 };
 
-// tile order: groups of kGroupM M-tiles, N-major inside a group
-__device__ __forceinline__ void decode_grouped(int L, int n_mt, int n_nt, int& mt, int& nt) {
-  const int full = (n_mt / kGroupM) * kGroupM * n_nt;
-  if (L < full) {
-    const int grp = L / (kGroupM * n_nt);
-    const int rem = L - grp * kGroupM * n_nt;
-    nt = rem / kGroupM;
-    mt = grp * kGroupM + (rem - nt * kGroupM);
-  } else {
-    const int rem = L - full;
-    const int gm = n_mt - (n_mt / kGroupM) * kGroupM;
-    nt = rem / gm;
-    mt = (n_mt / kGroupM) * kGroupM + (rem - nt * gm);
-  }
-}
-
-// bf16 tile order, two levels above each XCD's kGroupM x 8 block of tiles.
+// Tile order, two levels above each XCD's kGroupM x 8 block of tiles.
 // Tiles come in bands of kBandM M-tiles; inside a band, in N-blocks of 8
 // columns, and inside an N-block, in M-blocks of kGroupM rows whose tiles
 // run M fastest.  The blocks of one N-block follow each other, so the 8
@@ -819,347 +530,6 @@ __host__ __device__ constexpr int a_layout(int pass) {
 __host__ __device__ constexpr int b_layout(int pass) {
   return pass == P_BWD_DA || pass == P_BWD_DX || pass == P_BWD_DW2 || pass == P_BWD_DW13 ? L_KM
                                                                                           : L_KC;
-}
-
-template <int MODE, int PASS>
-__global__ __launch_bounds__(kThreads, 1) void ffn_gemm_f32_kernel(const GemmParams p) {
-  // two stages of the A and B tiles, four distinct objects (see mainloop);
-  // after the K loop the same memory holds each wave's epilogue strip
-  __shared__ __attribute__((aligned(16))) char la0[kTileBytes];
-  __shared__ __attribute__((aligned(16))) char lb0[kTileBytes];
-  __shared__ __attribute__((aligned(16))) char la1[kTileBytes];
-  __shared__ __attribute__((aligned(16))) char lb1[kTileBytes];
-  using T = float;
-  constexpr int ES = 4;
-  constexpr bool VARK = MODE == M_DW;
-  constexpr bool GATED = MODE == M_FWD1_SWIGLU;
-  constexpr int ALAY = a_layout(PASS), BLAY = b_layout(PASS);
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
-  const int team = wave >> 2, wq = wave & 3;
-  const Sched& sc = *p.sched;
-  const int n_items = VARK ? sc.n_segs * p.mtiles_out * p.ntiles : sc.n_mtiles * p.ntiles;
-  const int G = gridDim.x;
-  const int lbase = (blockIdx.x % kXcds) * (G / kXcds) + blockIdx.x / kXcds;
-  // the wave's staging strip (kStripsPerArray per 32 KB array)
-  auto strip_at = [&](int sidx) {
-    const int arr = sidx / kStripsPerArray, off = (sidx % kStripsPerArray) * kStripBytes;
-    char* base = arr == 0 ? la0 : (arr == 1 ? lb0 : la1);
-    return reinterpret_cast<float*>(base + off);
-  };
-
-  for (int round = 0;; ++round) {
-    const int L = round * G + lbase;
-    if (L >= n_items) break;
-    // An opaque zero, produced inside the tile loop: the per-lane epilogue
-    // addresses derived from it are computed per tile instead of being
-    // hoisted out of the loop and held (or spilled) across the K loop.
-    int z;
-    asm volatile("s_mov_b32 %0, 0" : "=s"(z));
-    float* strip = strip_at(2 * wave) + z;
-    TileOps op;
-    int g, row0, m_valid;       // var-M: expert, first global row, valid rows in tile
-    int n0;                      // first output column of the tile
-    int slot = -1, mt, nt;
-    if constexpr (!VARK) {
-      int mti;
-      decode_grouped(L, sc.n_mtiles, p.ntiles, mti, nt);
-      const int2 tm = p.mtile[mti];
-      g = tm.x;
-      row0 = p.offsets[g] + tm.y;
-      m_valid = min(BM, sc.rows[g] - tm.y);
-      op.a = {p.A + static_cast<int64_t>(row0) * p.lda, nullptr, p.lda, m_valid, 0};
-      op.K = p.K;
-      const char* bg = p.B + static_cast<int64_t>(g) * p.b_gstride;
-      if constexpr (GATED) {
-        n0 = nt * (BN / 2);  // hidden units covered by this tile (W1 and W3 rows)
-        op.b = {bg + static_cast<int64_t>(n0) * p.ldb,
-                p.B2 + static_cast<int64_t>(g) * p.b_gstride + static_cast<int64_t>(n0) * p.ldb,
-                p.ldb, min(BN / 2, p.N - n0), 0};
-      } else if constexpr (BLAY == L_KC) {
-        n0 = nt * BN;
-        op.b = {bg + static_cast<int64_t>(n0) * p.ldb, nullptr, p.ldb, min(BN, p.N - n0), 0};
-      } else {  // K-major weights: k-row 0, column n0
-        n0 = nt * BN;
-        op.b = {bg + static_cast<int64_t>(n0) * ES,
-                p.B2 ? p.B2 + static_cast<int64_t>(g) * p.b_gstride + static_cast<int64_t>(n0) * ES
-                     : nullptr,
-                p.ldb, min(BN, p.N - n0), p.B2 ? p.kmsplit : 0x7FFFFFFF};
-      }
-    } else {
-      const int tmn = p.mtiles_out * p.ntiles;
-      const int si = L / tmn;
-      decode_grouped(L - si * tmn, p.mtiles_out, p.ntiles, mt, nt);
-      const int4 sg = p.seg[si];
-      g = sg.x;
-      slot = sg.w;
-      // this segment's dispatched rows: offsets[g] + [k0, k1) of the expert
-      const int k1 = min(sg.z, sc.rows[g]);
-      const int64_t krow = static_cast<int64_t>(p.offsets[g]) + sg.y;
-      row0 = mt * BM;
-      n0 = nt * BN;
-      m_valid = min(BM, p.M_out - row0);
-      op.a = {p.A + krow * p.lda + static_cast<int64_t>(row0) * ES, nullptr, p.lda, m_valid,
-              0x7FFFFFFF};
-      op.b = {p.B + krow * p.ldb + static_cast<int64_t>(n0) * ES, nullptr, p.ldb,
-              min(BN, p.N - n0), 0x7FFFFFFF};
-      op.K = max(0, k1 - sg.y);
-    }
-
-    floatx16 acc[4][2];
-    if (op.a.rows >= BM && op.b.rows >= (GATED ? BN / 2 : BN))
-      mainloop_f32<ALAY, BLAY, GATED, true>(op, la0, lb0, la1, lb1, acc);
-    else
-      mainloop_f32<ALAY, BLAY, GATED, false>(op, la0, lb0, la1, lb1, acc);
-
-    // Epilogue, wave by wave: 16 accumulator rows at a time go through the
-    // wave's own LDS strip, then each lane finishes 8 consecutive columns of
-    // a row and writes them as one vector.
-    const int wcol = wq * 64;   // the wave's first tile column
-    if constexpr (MODE == M_BWD_DA || MODE == M_BWD_DA_SWIGLU) {
-      // dH = dA act'(H): 16 (row block, strip half, row group) iterations,
-      // each reading 8 saved pre-activations (two planes for SwiGLU) per
-      // lane.  Those loads run kPf iterations ahead of their use, so the
-      // wave waits for HBM once per tile rather than once per iteration.
-      constexpr bool SW = MODE == M_BWD_DA_SWIGLU;
-      constexpr int kIt = 16, kPf = 4;
-      Raw8<T> q1[kIt], q3[kIt];
-      auto pos = [&](int n, int& lm, int& gc) {
-        const int i = n >> 2, h = (n >> 1) & 1, it = n & 1;
-        lm = team * 128 + i * 32 + h * 16 + it * 8 + (lane >> 3);
-        gc = n0 + wcol + (lane & 7) * 8;
-      };
-      auto issue = [&](int n) {
-        int lm, gc;
-        pos(n, lm, gc);
-        const bool ok = lm < m_valid && gc < p.N;
-        // out-of-tile lanes read the tile's first valid element instead
-        const int64_t o = static_cast<int64_t>(row0 + (ok ? lm : 0)) * p.ldh +
-                          static_cast<int64_t>(ok ? gc : n0) * ES;
-        q1[n].load(p.H1 + o);
-        if constexpr (SW) q3[n].load(p.H3 + o);
-      };
-#pragma unroll
-      for (int n = 0; n < kPf; ++n) issue(n);
-#pragma unroll
-      for (int n = 0; n < kIt; ++n) {
-        if (n + kPf < kIt) issue(n + kPf);
-        if ((n & 1) == 0) stage_strip(strip, acc, n >> 2, (n >> 1) & 1);
-        int lm, gc;
-        pos(n, lm, gc);
-        if (lm < m_valid && gc < p.N) {
-          const int r = (n & 1) * 8 + (lane >> 3), c8 = (lane & 7) * 8;
-          const int64_t grow = row0 + lm;
-          float h1[8], g1[8];
-          q1[n].to_f(h1);
-          if constexpr (SW) {
-            float h3[8], g3[8];
-            q3[n].to_f(h3);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-              // d silu(h1) h3 / dh1 = h3 sg (1 + h1 (1 - sg)), d / dh3 = h1 sg
-              const float da = strip[r * kStripPitch + c8 + e];
-              const float sg = sigm(h1[e]);
-              const float t = da * sg, u = t * h3[e];
-              g1[e] = __builtin_fmaf(u, __builtin_fmaf(-h1[e], sg, h1[e]), u);
-              g3[e] = t * h1[e];
-            }
-            store_vec<T>(p.C + grow * p.ldc + static_cast<int64_t>(gc) * ES, g1);
-            store_vec<T>(p.C + grow * p.ldc + static_cast<int64_t>(p.f + gc) * ES, g3);
-          } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-              g1[e] = strip[r * kStripPitch + c8 + e] * act_grad_f(h1[e], p.act);
-            store_vec<T>(p.C + grow * p.ldc + static_cast<int64_t>(gc) * ES, g1);
-          }
-        }
-      }
-    } else {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        stage_strip(strip, acc, i, h);
-        const int srow0 = team * 128 + i * 32 + h * 16;  // strip's first row within the tile
-        if constexpr (MODE == M_FWD1_SWIGLU) {
-          // strip columns [0,32): H1, [32,64): H3 of hidden units n0 + 32wq + c
-          const int r = lane >> 2, c8 = (lane & 3) * 8;
-          const int lm = srow0 + r;
-          const int gc = n0 + wq * 32 + c8;
-          if (lm < m_valid && gc < p.N) {
-            float h1[8], h3[8], a[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-              h1[e] = Elem<T>::to_f(Elem<T>::from_f(strip[r * kStripPitch + c8 + e]));
-              h3[e] = Elem<T>::to_f(Elem<T>::from_f(strip[r * kStripPitch + 32 + c8 + e]));
-              a[e] = h1[e] * sigm(h1[e]) * h3[e];
-            }
-            const int64_t grow = row0 + lm;
-            if (p.H1) {
-              store_vec<T>(p.H1 + grow * p.ldh + static_cast<int64_t>(gc) * ES, h1);
-              store_vec<T>(p.H3 + grow * p.ldh + static_cast<int64_t>(gc) * ES, h3);
-            }
-            store_vec<T>(p.C + grow * p.ldc + static_cast<int64_t>(gc) * ES, a);
-          }
-        } else if constexpr (MODE == M_FWD1 || MODE == M_STORE) {
-#pragma unroll
-          for (int it = 0; it < 2; ++it) {
-            const int r = it * 8 + (lane >> 3), c8 = (lane & 7) * 8;
-            const int lm = srow0 + r;
-            const int gc = n0 + wcol + c8;
-            if (lm < m_valid && gc < p.N) {
-              float v[8];
-#pragma unroll
-              for (int e = 0; e < 8; ++e) v[e] = strip[r * kStripPitch + c8 + e];
-              const int64_t grow = row0 + lm;
-              if constexpr (MODE == M_FWD1) {
-                float hh[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                  hh[e] = Elem<T>::to_f(Elem<T>::from_f(v[e]));
-                  v[e] = act_f(hh[e], p.act);
-                }
-                if (p.H1) store_vec<T>(p.H1 + grow * p.ldh + static_cast<int64_t>(gc) * ES, hh);
-              }
-              store_vec<T>(p.C + grow * p.ldc + static_cast<int64_t>(gc) * ES, v);
-            }
-          }
-        } else {  // M_DW: fp32 rows of dW (or of a partial-sum slot)
-#pragma unroll
-          for (int it = 0; it < 2; ++it) {
-            const int r = it * 8 + (lane >> 3), c8 = (lane & 7) * 8;
-            const int lm = srow0 + r;
-            const int gc = n0 + wcol + c8;
-            if (lm < m_valid && gc < p.N) {
-              const int orow = row0 + lm;
-              float* dst;
-              if (slot >= 0) {
-                dst = p.partial + static_cast<int64_t>(slot) * p.slot_elems +
-                      static_cast<int64_t>(orow) * p.N + gc;
-              } else if (orow < p.split_row) {
-                dst = p.dwA + static_cast<int64_t>(g) * p.dw_gstride +
-                      static_cast<int64_t>(orow) * p.N + gc;
-              } else {
-                dst = p.dwB + static_cast<int64_t>(g) * p.dw_gstride +
-                      static_cast<int64_t>(orow - p.split_row) * p.N + gc;
-              }
-              const float* sp = strip + r * kStripPitch + c8;
-              *reinterpret_cast<float4*>(dst) = make_float4(sp[0], sp[1], sp[2], sp[3]);
-              *reinterpret_cast<float4*>(dst + 4) = make_float4(sp[4], sp[5], sp[6], sp[7]);
-            }
-          }
-        }
-      }
-    }
-    }
-    __syncthreads();   // strips are free before the next tile's loads
-  }
-}
-
-// ---------------------------------------------------------------------------
-// fp32 forward products with few rows
-// ---------------------------------------------------------------------------
-// A 256x256 fp32 tile is one wavefront's 128x64 block on each of eight
-// wavefronts, whatever the rows: with a few dozen rows per expert (fp32
-// matrix cores run at a sixteenth of the bf16 rate) the handful of busy
-// wavefronts sets the time.  Here one wavefront computes one 32x32 output
-// block (gated: 32 hidden units of H1 and of H3) with v_mfma_f32_32x32x2f32,
-// reading both K-contiguous operands straight from memory (64 k at a time,
-// the next 64 in flight), so the work spreads over as many SIMDs as there
-// are blocks.  Lane l supplies row (column) l % 32 and, for the four MFMAs
-// of an 8-wide k step, k values k0 + 4 (l / 32) + j (j = 0..3): every k of
-// the step enters exactly one MFMA, for the A and the B operand alike.  Item = (expert, 32-row block,
-// 32-column block); blocks past the expert's rows or past N exit at once.
-constexpr int kTinyB = 32;
-constexpr int kTinyMaxItems = 4096;
-
-template <int MODE>
-__global__ __launch_bounds__(256) void ffn_gemm_f32_tiny_kernel(const GemmParams p, int E,
-                                                                int mblocks, int nblocks) {
-  constexpr bool GATED = MODE == M_FWD1_SWIGLU;
-  const int lane = threadIdx.x & 63;
-  const int item = static_cast<int>(blockIdx.x) * 4 + (static_cast<int>(threadIdx.x) >> 6);
-  const int per_e = mblocks * nblocks;
-  const int g = item / per_e;
-  if (g >= E) return;
-  const int rem = item - g * per_e;
-  const int m0 = (rem / nblocks) * kTinyB, n0 = (rem % nblocks) * kTinyB;
-  const int rows_g = p.sched->rows[g];
-  if (m0 >= rows_g || n0 >= p.N) return;
-  const int r = lane & 31, kh = 4 * (lane >> 5);
-  const bool arow = m0 + r < rows_g, brow = n0 + r < p.N;
-  const int64_t grow0 = static_cast<int64_t>(p.offsets[g]) + m0;
-  const float* a = reinterpret_cast<const float*>(p.A + (grow0 + (arow ? r : 0)) * p.lda);
-  const int64_t boff = static_cast<int64_t>(g) * p.b_gstride + static_cast<int64_t>(n0 + (brow ? r : 0)) * p.ldb;
-  const float* b1 = reinterpret_cast<const float*>(p.B + boff);
-  const float* b3 = GATED ? reinterpret_cast<const float*>(p.B2 + boff) : b1;
-  const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
-  floatx16 c1, c3;
-#pragma unroll
-  for (int q = 0; q < 16; ++q) c1[q] = c3[q] = 0.f;
-  // k in chunks of 64 (8 steps of 8): a chunk's operands are loaded
-  // together, the next chunk's before the current chunk's MFMAs (K is a
-  // multiple of 8; steps past K load zeros)
-  constexpr int kSteps = 8;
-  struct Chunk { float4 a[kSteps], b[kSteps], w[kSteps]; };
-  auto load = [&](int k0, Chunk& c) {
-#pragma unroll
-    for (int s = 0; s < kSteps; ++s) {
-      const int kk = k0 + 8 * s + kh;
-      const bool ok = kk < p.K;
-      c.a[s] = arow && ok ? *reinterpret_cast<const float4*>(a + kk) : zero;
-      c.b[s] = brow && ok ? *reinterpret_cast<const float4*>(b1 + kk) : zero;
-      if constexpr (GATED) c.w[s] = brow && ok ? *reinterpret_cast<const float4*>(b3 + kk) : zero;
-    }
-  };
-  auto mma = [&](const Chunk& c) {
-#pragma unroll
-    for (int s = 0; s < kSteps; ++s) {
-      c1 = __builtin_amdgcn_mfma_f32_32x32x2f32(c.a[s].x, c.b[s].x, c1, 0, 0, 0);
-      c1 = __builtin_amdgcn_mfma_f32_32x32x2f32(c.a[s].y, c.b[s].y, c1, 0, 0, 0);
-      c1 = __builtin_amdgcn_mfma_f32_32x32x2f32(c.a[s].z, c.b[s].z, c1, 0, 0, 0);
-      c1 = __builtin_amdgcn_mfma_f32_32x32x2f32(c.a[s].w, c.b[s].w, c1, 0, 0, 0);
-      if constexpr (GATED) {
-        c3 = __builtin_amdgcn_mfma_f32_32x32x2f32(c.a[s].x, c.w[s].x, c3, 0, 0, 0);
-        c3 = __builtin_amdgcn_mfma_f32_32x32x2f32(c.a[s].y, c.w[s].y, c3, 0, 0, 0);
-        c3 = __builtin_amdgcn_mfma_f32_32x32x2f32(c.a[s].z, c.w[s].z, c3, 0, 0, 0);
-        c3 = __builtin_amdgcn_mfma_f32_32x32x2f32(c.a[s].w, c.w[s].w, c3, 0, 0, 0);
-      }
-    }
-  };
-  constexpr int KC = 8 * kSteps;
-  Chunk c0, cn;
-  load(0, c0);
-  for (int k0 = 0; k0 < p.K; k0 += 2 * KC) {
-    if (k0 + KC < p.K) load(k0 + KC, cn);
-    mma(c0);
-    if (k0 + KC >= p.K) break;
-    if (k0 + 2 * KC < p.K) load(k0 + 2 * KC, c0);
-    mma(cn);
-  }
-  // accumulator q of lane l: column l % 32, row 8 (q / 4) + 4 (l / 32) + q % 4
-  const int col = n0 + r;
-  if (col >= p.N) return;
-#pragma unroll
-  for (int q = 0; q < 16; ++q) {
-    const int row = m0 + 8 * (q >> 2) + kh + (q & 3);
-    if (row >= rows_g) continue;
-    const int64_t grow = static_cast<int64_t>(p.offsets[g]) + row;
-    float* cp = reinterpret_cast<float*>(p.C + grow * p.ldc) + col;
-    if constexpr (MODE == M_FWD1_SWIGLU) {
-      const float h1 = c1[q], h3 = c3[q];
-      if (p.H1) {
-        reinterpret_cast<float*>(p.H1 + grow * p.ldh)[col] = h1;
-        reinterpret_cast<float*>(p.H3 + grow * p.ldh)[col] = h3;
-      }
-      *cp = h1 * sigm(h1) * h3;
-    } else if constexpr (MODE == M_FWD1) {
-      if (p.H1) reinterpret_cast<float*>(p.H1 + grow * p.ldh)[col] = c1[q];
-      *cp = act_f(c1[q], p.act);
-    } else {
-      *cp = c1[q];
-    }
-  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1745,7 +1115,7 @@ __device__ __forceinline__ void epilogue16(const GemmParams& p,
             *reinterpret_cast<uint4*>(p.H1 + grow * p.ldh + static_cast<int64_t>(gc) * ES) = b1;
             *reinterpret_cast<uint4*>(p.H3 + grow * p.ldh + static_cast<int64_t>(gc) * ES) = b3;
           }
-          store_vec<T>(p.C + grow * p.ldc + static_cast<int64_t>(gc) * ES, a);
+          *reinterpret_cast<uint4*>(p.C + grow * p.ldc + static_cast<int64_t>(gc) * ES) = pack8(a);
         }
       }
     }
@@ -1758,7 +1128,7 @@ __device__ __forceinline__ void epilogue16(const GemmParams& p,
     constexpr bool SW = MODE == M_BWD_DA_SWIGLU;
     constexpr int LR = WC / 8, RG = 64 / LR, GB = 16 / RG;
     constexpr int kIt = C::RB * GB, kPf = 4, kRing = kPf + 1;
-    Raw8<T> q1[kRing], q3[kRing];
+    uint4 q1[kRing], q3[kRing];
     auto pos = [&](int n, int& lm, int& gc) {
       lm = wr0 + 16 * (n / GB) + RG * (n % GB) + el / LR;
       gc = n0 + wn * WC + (el % LR) * 8;
@@ -1770,8 +1140,8 @@ __device__ __forceinline__ void epilogue16(const GemmParams& p,
       // out-of-tile lanes read the tile's first valid element instead
       const int64_t o = static_cast<int64_t>(row0 + (ok ? lm : 0)) * p.ldh +
                         static_cast<int64_t>(ok ? gc : n0) * ES;
-      q1[n % kRing].load(p.H1 + o);
-      if constexpr (SW) q3[n % kRing].load(p.H3 + o);
+      q1[n % kRing] = *reinterpret_cast<const uint4*>(p.H1 + o);
+      if constexpr (SW) q3[n % kRing] = *reinterpret_cast<const uint4*>(p.H3 + o);
     };
 #pragma unroll
     for (int n = 0; n < kPf; ++n) issue(n);
@@ -1785,10 +1155,10 @@ __device__ __forceinline__ void epilogue16(const GemmParams& p,
         const int r = RG * (n % GB) + el / LR, c8 = (el % LR) * 8;
         const int64_t grow = row0 + lm;
         float h1[8], g1[8];
-        q1[n % kRing].to_f(h1);
+        unpack8(q1[n % kRing], h1);
         if constexpr (SW) {
           float h3[8], g3[8];
-          q3[n % kRing].to_f(h3);
+          unpack8(q3[n % kRing], h3);
 #pragma unroll
           for (int e = 0; e < 8; ++e) {
             // d silu(h1) h3 / dh1 = h3 sg (1 + h1 (1 - sg)), d / dh3 = h1 sg
@@ -1798,13 +1168,13 @@ __device__ __forceinline__ void epilogue16(const GemmParams& p,
             g1[e] = __builtin_fmaf(u, __builtin_fmaf(-h1[e], sg, h1[e]), u);
             g3[e] = t * h1[e];
           }
-          store_vec<T>(p.C + grow * p.ldc + static_cast<int64_t>(gc) * ES, g1);
-          store_vec<T>(p.C + grow * p.ldc + static_cast<int64_t>(p.f + gc) * ES, g3);
+          *reinterpret_cast<uint4*>(p.C + grow * p.ldc + static_cast<int64_t>(gc) * ES) = pack8(g1);
+          *reinterpret_cast<uint4*>(p.C + grow * p.ldc + static_cast<int64_t>(p.f + gc) * ES) = pack8(g3);
         } else {
 #pragma unroll
           for (int e = 0; e < 8; ++e)
             g1[e] = strip[r * kP + c8 + e] * act_grad_f(h1[e], ACT);
-          store_vec<T>(p.C + grow * p.ldc + static_cast<int64_t>(gc) * ES, g1);
+          *reinterpret_cast<uint4*>(p.C + grow * p.ldc + static_cast<int64_t>(gc) * ES) = pack8(g1);
         }
       }
     }
@@ -1847,7 +1217,7 @@ __device__ __forceinline__ void epilogue16(const GemmParams& p,
                   *reinterpret_cast<uint4*>(p.H1 + grow * p.ldh + static_cast<int64_t>(gc) * ES) = hb;
               }
             }
-            store_vec<T>(p.C + grow * p.ldc + static_cast<int64_t>(gc) * ES, v);
+            *reinterpret_cast<uint4*>(p.C + grow * p.ldc + static_cast<int64_t>(gc) * ES) = pack8(v);
           }
         }
       }
@@ -1952,96 +1322,110 @@ __global__ __launch_bounds__(kThreads16, 1) void ffn_gemm16_kernel(const GemmPar
   }
 }
 
-// The two-workgroups-per-CU kernel: var-M tiles of the heights the schedule
-// chose, weight-gradient tiles of kMidDwM rows.
+// One tile of the two-workgroups-per-CU kernels: var-M tiles of the heights
+// the schedule chose, weight-gradient tiles of p.dw_h units of rows.
+struct MidTile {
+  TileOps op;
+  int g, h;                // expert (or its segment's), units of rows
+  int row0, m_valid, n0;   // first output row, valid rows, first column
+  int slot;                // partial-sum slot, or -1
+};
+
+template <int MODE>
+__device__ __forceinline__ int mid_items(const GemmParams& p) {
+  const Sched& sc = *p.sched;
+  return (MODE == M_DW ? sc.n_segs * p.mtiles_out : sc.n_mid[p.mid_list]) * p.ntiles;
+}
+
+// Tile L of the launch; ES: bytes per element.
+template <int MODE, int PASS, int ES>
+__device__ __forceinline__ void mid_operands(const GemmParams& p, int L, MidTile& t) {
+  constexpr bool GATED = MODE == M_FWD1_SWIGLU;
+  constexpr int BLAY = b_layout(PASS), TN = kMidN;
+  const Sched& sc = *p.sched;
+  int mt, nt;
+  t.slot = -1;
+  if constexpr (MODE != M_DW) {
+    decode_banded(L, sc.n_mid[p.mid_list], p.ntiles, mt, nt);
+    const int2 tm = p.mtile[mt];
+    const int g = t.g = tm.x & 255;
+    t.h = tm.x >> 8;
+    t.row0 = p.offsets[g] + tm.y;
+    t.m_valid = min(t.h * kMidUnit, sc.rows[g] - tm.y);
+    t.op.a = {p.A + static_cast<int64_t>(t.row0) * p.lda, nullptr, p.lda, t.m_valid, 0};
+    t.op.K = p.K;
+    const char* bg = p.B + static_cast<int64_t>(g) * p.b_gstride;
+    const char* bg2 = p.B2 + static_cast<int64_t>(g) * p.b_gstride;
+    t.n0 = nt * (GATED ? TN / 2 : TN);
+    if constexpr (GATED) {
+      t.op.b = {bg + static_cast<int64_t>(t.n0) * p.ldb, bg2 + static_cast<int64_t>(t.n0) * p.ldb,
+                p.ldb, min(TN / 2, p.N - t.n0), 0};
+    } else if constexpr (BLAY == L_KC) {
+      t.op.b = {bg + static_cast<int64_t>(t.n0) * p.ldb, nullptr, p.ldb, min(TN, p.N - t.n0), 0};
+    } else {
+      const int64_t o = static_cast<int64_t>(t.n0) * ES;
+      t.op.b = {bg + o, p.B2 ? bg2 + o : nullptr, p.ldb, min(TN, p.N - t.n0),
+                p.B2 ? p.kmsplit : 0x7FFFFFFF};
+    }
+  } else {
+    const int tmn = p.mtiles_out * p.ntiles;
+    const int si = L / tmn;
+    decode_banded(L - si * tmn, p.mtiles_out, p.ntiles, mt, nt);
+    const int4 sg = p.seg[si];
+    t.g = sg.x;
+    t.h = p.dw_h;
+    t.slot = sg.w;
+    const int k1 = min(sg.z, sc.rows[t.g]);
+    const int64_t krow = static_cast<int64_t>(p.offsets[t.g]) + sg.y;
+    t.row0 = mt * t.h * kMidUnit;
+    t.n0 = nt * TN;
+    t.m_valid = min(t.h * kMidUnit, p.M_out - t.row0);
+    t.op.a = {p.A + krow * p.lda + static_cast<int64_t>(t.row0) * ES, nullptr, p.lda, t.m_valid,
+              0x7FFFFFFF};
+    t.op.b = {p.B + krow * p.ldb + static_cast<int64_t>(t.n0) * ES, nullptr, p.ldb,
+              min(TN, p.N - t.n0), 0x7FFFFFFF};
+    t.op.K = max(0, k1 - sg.y);
+  }
+}
+
 template <int MODE, int PASS>
 __global__ __launch_bounds__(kThreads16, 2) void ffn_gemm16_mid_kernel(const GemmParams p) {
   constexpr bool VARK = MODE == M_DW;
-  constexpr int kRowsA = VARK ? kMidDwM : kMidMaxH * kMidUnit;
+  constexpr int kRowsA = (VARK ? kMidDwH : kMidMaxH) * kMidUnit;
   __shared__ __attribute__((aligned(16))) char la0[kRowsA * kRowBytes];
   __shared__ __attribute__((aligned(16))) char lb0[kMidN * kRowBytes];
   __shared__ __attribute__((aligned(16))) char la1[kRowsA * kRowBytes];
   __shared__ __attribute__((aligned(16))) char lb1[kMidN * kRowBytes];
-  constexpr int ES = 2;
   constexpr bool GATED = MODE == M_FWD1_SWIGLU;
   constexpr int ALAY = a_layout(PASS), BLAY = b_layout(PASS);
-  constexpr int TN = kMidN;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
   const int wm = wave >> 1, wn = wave & 1;
-  const Sched& sc = *p.sched;
-  const int n_mt = VARK ? 0 : sc.n_mid[p.mid_list];
-  const int n_items = VARK ? sc.n_segs * p.mtiles_out * p.ntiles : n_mt * p.ntiles;
+  const int n_items = mid_items<MODE>(p);
   const int G = gridDim.x;
   const int lbase = (blockIdx.x % kXcds) * (G / kXcds) + blockIdx.x / kXcds;
 
   for (int round = 0;; ++round) {
     const int L = round * G + lbase;
     if (L >= n_items) break;
-    TileOps op;
-    int g, row0, m_valid, n0, h;
-    int slot = -1, mt, nt;
-    if constexpr (!VARK) {
-      int mti;
-      decode_banded(L, n_mt, p.ntiles, mti, nt);
-      const int2 tm = p.mtile[mti];
-      g = tm.x & 255;
-      h = tm.x >> 8;
-      row0 = p.offsets[g] + tm.y;
-      m_valid = min(h * kMidUnit, sc.rows[g] - tm.y);
-      op.a = {p.A + static_cast<int64_t>(row0) * p.lda, nullptr, p.lda, m_valid, 0};
-      op.K = p.K;
-      const char* bg = p.B + static_cast<int64_t>(g) * p.b_gstride;
-      if constexpr (GATED) {
-        n0 = nt * (TN / 2);
-        op.b = {bg + static_cast<int64_t>(n0) * p.ldb,
-                p.B2 + static_cast<int64_t>(g) * p.b_gstride + static_cast<int64_t>(n0) * p.ldb,
-                p.ldb, min(TN / 2, p.N - n0), 0};
-      } else if constexpr (BLAY == L_KC) {
-        n0 = nt * TN;
-        op.b = {bg + static_cast<int64_t>(n0) * p.ldb, nullptr, p.ldb, min(TN, p.N - n0), 0};
-      } else {
-        n0 = nt * TN;
-        op.b = {bg + static_cast<int64_t>(n0) * ES,
-                p.B2 ? p.B2 + static_cast<int64_t>(g) * p.b_gstride + static_cast<int64_t>(n0) * ES
-                     : nullptr,
-                p.ldb, min(TN, p.N - n0), p.B2 ? p.kmsplit : 0x7FFFFFFF};
-      }
-    } else {
-      const int tmn = p.mtiles_out * p.ntiles;
-      const int si = L / tmn;
-      decode_banded(L - si * tmn, p.mtiles_out, p.ntiles, mt, nt);
-      const int4 sg = p.seg[si];
-      g = sg.x;
-      h = kMidDwM / kMidUnit;
-      slot = sg.w;
-      const int k1 = min(sg.z, sc.rows[g]);
-      const int64_t krow = static_cast<int64_t>(p.offsets[g]) + sg.y;
-      row0 = mt * kMidDwM;
-      n0 = nt * TN;
-      m_valid = min(kMidDwM, p.M_out - row0);
-      op.a = {p.A + krow * p.lda + static_cast<int64_t>(row0) * ES, nullptr, p.lda, m_valid,
-              0x7FFFFFFF};
-      op.b = {p.B + krow * p.ldb + static_cast<int64_t>(n0) * ES, nullptr, p.ldb,
-              min(TN, p.N - n0), 0x7FFFFFFF};
-      op.K = max(0, k1 - sg.y);
-    }
+    MidTile t;
+    mid_operands<MODE, PASS, 2>(p, L, t);
     auto run = [&](auto hc) {
       constexpr int RB = decltype(hc)::value;
       using C = Tile16<RB, 4>;
       int zt, z;   // opaque zeros: see ffn_gemm16_kernel
       asm volatile("s_mov_b32 %0, 0" : "=s"(zt));
       floatx4 acc[RB][4];
-      mainloop_mid<RB, ALAY, BLAY, GATED>(op, la0, lb0, la1, lb1, acc, zt);
+      mainloop_mid<RB, ALAY, BLAY, GATED>(t.op, la0, lb0, la1, lb1, acc, zt);
       asm volatile("s_mov_b32 %0, 0" : "=s"(z));
       float* strip = reinterpret_cast<float*>((wave < 2 ? lb0 : lb1) + (wave & 1) * C::kStripBytes + z);
-      epilogue16<MODE, C>(p, acc, strip, lane + z, wm, wn, g, slot, row0, m_valid, n0,
-                          VARK && op.K == 0);
+      epilogue16<MODE, C>(p, acc, strip, lane + z, wm, wn, t.g, t.slot, t.row0, t.m_valid, t.n0,
+                          VARK && t.op.K == 0);
     };
     if constexpr (VARK) {
-      run(std::integral_constant<int, kMidDwM / kMidUnit>{});
+      run(std::integral_constant<int, kMidDwH>{});
     } else {
-      switch (h) {
+      switch (t.h) {
         case 1: run(std::integral_constant<int, 1>{}); break;
         case 2: run(std::integral_constant<int, 2>{}); break;
         case 3: run(std::integral_constant<int, 3>{}); break;
@@ -2051,6 +1435,249 @@ __global__ __launch_bounds__(kThreads16, 2) void ffn_gemm16_mid_kernel(const Gem
       }
     }
     __syncthreads();   // strips are free before the next tile's loads
+  }
+}
+
+// ---------------------------------------------------------------------------
+// fp32 products
+// ---------------------------------------------------------------------------
+// fp32 matrix cores run at a sixteenth of the bf16 rate, so any tile keeps
+// them fed from LDS and the caches; what costs time is tiles that leave
+// wavefronts idle.  Every fp32 product therefore runs on tiles of 128 columns
+// and RB units of 32 rows, RB chosen per tile by the schedule (weight
+// gradients: per product by the host), two workgroups per CU, with
+// v_mfma_f32_32x32x2f32.  (8 experts of about 512 rows, d = 256, f = 1024: the
+// six products of a step took 991 us on 256x256 tiles and take 249 us; 8 of 4096 rows, 1024 x 4096 SwiGLU: step 25.9 -> 20.8 ms;
+// 4 of 64 rows, 64 -> 128 -> 64: 31 -> 13 us against one wavefront per 32x32
+// block reading memory directly.)  Wave w of four owns columns 32w .. +31 of the tile
+// and all its rows (RB blocks of 32x32); of a gated forward tile (64 hidden
+// units of W1 and of W3) units 32 (w & 1) .. +31 of both and row blocks
+// w >> 1, (w >> 1) + 2, ..  K steps of 32 go HBM -> LDS by buffer loads, two
+// stages, the next step's loads issued before the step's MFMAs.
+constexpr int kF32Step = 32;
+
+// LDS tiles.  K-contiguous: rows of 128 bytes with the swizzle of the bf16
+// tiles.  K-major: 32 k-rows of SEG segments of 32 elements (SEG = RB for A,
+// 4 for B), segment s of k-row k stored at s ^ (k & (SEG - 1)).
+template <int NB> struct AccF32 { floatx16 v[NB]; };   // row blocks of a wave
+
+template <int RB, int PASS, bool GATED, int NB>
+__device__ __forceinline__ void mainloop_f32(const TileOps& op, char* la0, char* lb0, char* la1,
+                                             char* lb1, AccF32<NB>& acc_, AccF32<NB>& acc3_) {
+  static_assert(NB == (GATED ? (RB + 1) / 2 : RB), "row blocks per wave");
+  constexpr int ALAY = a_layout(PASS), BLAY = b_layout(PASS);
+  floatx16(&acc)[NB] = acc_.v;
+  floatx16(&acc3)[NB] = acc3_.v;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+#pragma unroll
+  for (int i = 0; i < NB; ++i)
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      acc[i][q] = 0.f;
+      if constexpr (GATED) acc3[i][q] = 0.f;
+    }
+  const int K = op.K;
+  const int nk = (K + kF32Step - 1) / kF32Step;
+  if (nk <= 0) return;
+  // ---- loads: 1 KB blocks 4i + w of A (i < RB) and of B (i < 4)
+  const int l3 = lane >> 3;
+  const int co = ((lane & 7) ^ swz(l3 + (wave & 1) * 8)) * 16;   // KC: block rows 8(4i + w) + l3
+  const int lda = static_cast<int>(op.a.ld), ldb = static_cast<int>(op.b.ld);
+  auto bad = [](bool b) { return static_cast<uint32_t>(b) << 31; };
+  // KM: a block is 8 / SEG k-rows of SEG segments; the lane's k-row within
+  // it and physical element
+  auto km_row = [&](int seg) { return lane / (8 * seg); };
+  auto km_elem = [&](int seg) { return (lane % (8 * seg)) * 4; };
+  auto brow = [&](int i) { return GATED ? (i >> 1) * 32 + wave * 8 : (4 * i + wave) * 8; };
+  const __amdgpu_buffer_rsrc_t ra_t = tile_rsrc(op.a.base);
+  const __amdgpu_buffer_rsrc_t rb_t = tile_rsrc(op.b.base);
+  const __amdgpu_buffer_rsrc_t rb3_t = tile_rsrc(GATED ? op.b.base2 : op.b.base);
+  auto load_km = [&](auto seg_c, const Operand& o, char* dst, int i, int kt, int ld) {
+    constexpr int SEG = decltype(seg_c)::value;
+    const int blk = 4 * i + wave;
+    const int k0 = blk * (8 / SEG), kr = km_row(SEG);      // first k-row of the block, the lane's
+    const int pe = km_elem(SEG);
+    const int col = (((pe >> 5) ^ ((k0 + kr) & (SEG - 1))) << 5) + (pe & 31);
+    const int kabs = kt * kF32Step + k0;
+    const bool second = kabs >= o.split;                   // a multiple of 8
+    const int64_t kb = static_cast<int64_t>(kt) * kF32Step - (second ? o.split : 0);
+    const __amdgpu_buffer_rsrc_t rs = tile_rsrc((second ? o.base2 : o.base) + kb * o.ld);
+    const uint32_t off = static_cast<uint32_t>(kr * ld + col * 4) | bad(col >= o.rows || kabs + kr >= K);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, MOE_LDS(dst + blk * 1024), 16, off, k0 * ld, 0, 0);
+  };
+  auto load = [&](int kt, char* sa, char* sb) {
+    const uint32_t kbad = bad(kt * kRowBytes + co >= K * 4);
+#pragma unroll
+    for (int i = 0; i < RB; ++i) {
+      if constexpr (ALAY == L_KC) {
+        const int blk = 4 * i + wave;
+        const uint32_t off = static_cast<uint32_t>(l3 * lda + co) | bad(blk * 8 + l3 >= op.a.rows) | kbad;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(ra_t, MOE_LDS(sa + blk * 1024), 16, off,
+                                                 blk * 8 * lda + kt * kRowBytes, 0, 0);
+      } else {
+        load_km(std::integral_constant<int, RB>{}, op.a, sa, i, kt, lda);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if constexpr (BLAY == L_KC) {
+        const int blk = 4 * i + wave;
+        const uint32_t off = static_cast<uint32_t>(l3 * ldb + co) | bad(brow(i) + l3 >= op.b.rows) | kbad;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(GATED && (i & 1) ? rb3_t : rb_t,
+                                                 MOE_LDS(sb + blk * 1024), 16, off,
+                                                 brow(i) * ldb + kt * kRowBytes, 0, 0);
+      } else {
+        load_km(std::integral_constant<int, 4>{}, op.b, sb, i, kt, ldb);
+      }
+    }
+  };
+  // ---- fragments.  MFMA operand of lane l: row/column l % 32 of the block,
+  // k values 8 s + 4 (l / 32) .. +3 of sub-step s
+  const int r32 = lane & 31, kh = lane >> 5;
+  auto frag_kc = [&](const char* st, int blk, int s) {
+    const int row = blk * 32 + r32;
+    return *reinterpret_cast<const uint4*>(st + row * kRowBytes + (((2 * s + kh) ^ swz(row)) << 4));
+  };
+  auto frag_km = [&](auto seg_c, const char* st, int blk, int s) {
+    constexpr int SEG = decltype(seg_c)::value;
+    uint32_t v[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int k = 8 * s + 4 * kh + c;
+      v[c] = *reinterpret_cast<const uint32_t*>(
+          st + (k * SEG + (blk ^ (c & (SEG - 1)))) * 128 + r32 * 4);   // k & (SEG - 1) = c & (SEG - 1)
+    }
+    return make_uint4(v[0], v[1], v[2], v[3]);
+  };
+  auto compute = [&](const char* sa, const char* sb) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      uint4 b, b3;
+      if constexpr (GATED) {
+        b = frag_kc(sb, 2 * (wave & 1), s);
+        b3 = frag_kc(sb, 2 * (wave & 1) + 1, s);
+      } else if constexpr (BLAY == L_KC) {
+        b = frag_kc(sb, wave, s);
+      } else {
+        b = frag_km(std::integral_constant<int, 4>{}, sb, wave, s);
+      }
+#pragma unroll
+      for (int i = 0; i < NB; ++i) {
+        const int blk = GATED ? min(2 * i + (wave >> 1), RB - 1) : i;
+        uint4 a;
+        if constexpr (ALAY == L_KC) a = frag_kc(sa, blk, s);
+        else a = frag_km(std::integral_constant<int, RB>{}, sa, blk, s);
+        mma_f32(acc[i], a, b);
+        if constexpr (GATED) mma_f32(acc3[i], a, b3);
+      }
+    }
+  };
+  load(0, la0, lb0);
+  __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+  __builtin_amdgcn_s_barrier();
+  auto step = [&](int kt, char* ca, char* cb, char* na, char* nb) {
+    if (kt + 1 < nk) load(kt + 1, na, nb);
+    __builtin_amdgcn_sched_barrier(0);
+    compute(ca, cb);
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0) lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+  };
+  for (int kt = 0; kt < nk; kt += 2) {
+    step(kt, la0, lb0, la1, lb1);
+    if (kt + 1 < nk) step(kt + 1, la1, lb1, la0, lb0);
+  }
+}
+
+template <int MODE, int PASS>
+__global__ __launch_bounds__(kThreads16, 2) void ffn_gemm_f32_kernel(const GemmParams p) {
+  constexpr bool VARK = MODE == M_DW;
+  constexpr int kRowsA = (VARK ? 4 : kMidMaxH) * kMidUnit;
+  __shared__ __attribute__((aligned(16))) char la0[kRowsA * kRowBytes];
+  __shared__ __attribute__((aligned(16))) char lb0[kMidN * kRowBytes];
+  __shared__ __attribute__((aligned(16))) char la1[kRowsA * kRowBytes];
+  __shared__ __attribute__((aligned(16))) char lb1[kMidN * kRowBytes];
+  constexpr bool GATED = MODE == M_FWD1_SWIGLU;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+  const int n_items = mid_items<MODE>(p);
+  const int G = gridDim.x;
+  const int lbase = (blockIdx.x % kXcds) * (G / kXcds) + blockIdx.x / kXcds;
+  for (int round = 0;; ++round) {
+    const int L = round * G + lbase;
+    if (L >= n_items) break;
+    MidTile t;
+    mid_operands<MODE, PASS, 4>(p, L, t);
+    auto run = [&](auto hc) {
+      constexpr int RB = decltype(hc)::value;
+      constexpr int NB = GATED ? (RB + 1) / 2 : RB;
+      AccF32<NB> c1, c3;   // c3: the W3 half of a gated tile
+      mainloop_f32<RB, PASS, GATED, NB>(t.op, la0, lb0, la1, lb1, c1, c3);
+      floatx16(&acc)[NB] = c1.v;
+      floatx16(&acc3)[NB] = c3.v;
+      // accumulator q of lane l: column l % 32, row 8 (q / 4) + 4 (l / 32) + q % 4
+      const int col = t.n0 + (GATED ? wave & 1 : wave) * 32 + (lane & 31);
+      if (col >= p.N) return;
+#pragma unroll
+      for (int i = 0; i < NB; ++i) {
+        const int blk = GATED ? 2 * i + (wave >> 1) : i;
+        if (GATED && blk >= RB) continue;
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+          const int lm = blk * 32 + 8 * (q >> 2) + 4 * (lane >> 5) + (q & 3);
+          if (lm >= t.m_valid) continue;
+          const int64_t row = t.row0 + lm;
+          if constexpr (MODE == M_DW) {
+            float* dst;
+            if (t.slot >= 0) dst = p.partial + static_cast<int64_t>(t.slot) * p.slot_elems + row * p.N;
+            else if (row < p.split_row) dst = p.dwA + static_cast<int64_t>(t.g) * p.dw_gstride + row * p.N;
+            else dst = p.dwB + static_cast<int64_t>(t.g) * p.dw_gstride + (row - p.split_row) * p.N;
+            dst[col] = acc[i][q];
+          } else {
+            float* c = reinterpret_cast<float*>(p.C + row * p.ldc) + col;
+            if constexpr (MODE == M_FWD1_SWIGLU) {
+              const float h1 = acc[i][q], h3 = acc3[i][q];
+              if (p.H1) {
+                reinterpret_cast<float*>(p.H1 + row * p.ldh)[col] = h1;
+                reinterpret_cast<float*>(p.H3 + row * p.ldh)[col] = h3;
+              }
+              *c = h1 * sigm(h1) * h3;
+            } else if constexpr (MODE == M_FWD1) {
+              if (p.H1) reinterpret_cast<float*>(p.H1 + row * p.ldh)[col] = acc[i][q];
+              *c = act_f(acc[i][q], p.act);
+            } else if constexpr (MODE == M_BWD_DA_SWIGLU) {
+              const float h1 = reinterpret_cast<const float*>(p.H1 + row * p.ldh)[col];
+              const float h3 = reinterpret_cast<const float*>(p.H3 + row * p.ldh)[col];
+              // d silu(h1) h3 / dh1 = h3 sg (1 + h1 (1 - sg)), d / dh3 = h1 sg
+              const float sg = sigm(h1), x = acc[i][q] * sg, u = x * h3;
+              *c = __builtin_fmaf(u, __builtin_fmaf(-h1, sg, h1), u);
+              c[p.f] = x * h1;
+            } else if constexpr (MODE == M_BWD_DA) {
+              *c = acc[i][q] * act_grad_f(reinterpret_cast<const float*>(p.H1 + row * p.ldh)[col], p.act);
+            } else {
+              *c = acc[i][q];
+            }
+          }
+        }
+      }
+    };
+    if constexpr (VARK) {
+      switch (t.h) {
+        case 1: run(std::integral_constant<int, 1>{}); break;
+        case 2: run(std::integral_constant<int, 2>{}); break;
+        default: run(std::integral_constant<int, 4>{}); break;
+      }
+    } else {
+      switch (t.h) {
+        case 1: run(std::integral_constant<int, 1>{}); break;
+        case 2: run(std::integral_constant<int, 2>{}); break;
+        case 3: run(std::integral_constant<int, 3>{}); break;
+        case 4: run(std::integral_constant<int, 4>{}); break;
+        case 5: run(std::integral_constant<int, 5>{}); break;
+        default: run(std::integral_constant<int, 6>{}); break;
+      }
+    }
   }
 }
 
@@ -2233,10 +1860,12 @@ bool make_plan(moe_dtype dt, moe_act act, int E, int d, int f, int64_t rows_allo
 // (K = d) and with N = d (K = k1), for the heights of the two mid tile lists.
 moe_status launch_schedule(hipStream_t s, const FfnPlan& pl, const int32_t* offsets,
                            const int32_t* rows, int nt0, int nt1, int k1, char* ws) {
+  const bool f32 = pl.es == 4;
+  const int ks = f32 ? kF32Step : 64;
   MOE_TIMED("ffn_schedule", s);
   const SchedArgs a = {pl.E, pl.rows_alloc, pl.max_mtiles, pl.max_mid, pl.max_segs, pl.tmn_min,
-                       pl.max_slots, {nt0, nt1}, {cdiv(pl.d, 64), cdiv(k1, 64)},
-                       2 * persistent_grid()};
+                       pl.max_slots, {nt0, nt1}, {cdiv(pl.d, ks), cdiv(k1, ks)},
+                       2 * persistent_grid(), f32 ? kStepF32 : kStep16};
   schedule_kernel<<<1, 64 * kSchedWaves, 0, s>>>(
       offsets, rows, a, reinterpret_cast<Sched*>(ws + pl.o_sched),
       reinterpret_cast<int2*>(ws + pl.o_mtile), reinterpret_cast<int2*>(ws + pl.o_mid),
@@ -2275,13 +1904,13 @@ int g_tile_mode = 0;
 // 256x256 tiles.
 bool use_mid_tiles(const FfnPlan& pl, moe_dtype dt, bool vark, bool gated, bool act, int N,
                    int M_out, int K) {
-  if (dt != MOE_BF16) return false;
+  if (dt == MOE_F32) return true;
   if (g_tile_mode == 1) return false;
   if (g_tile_mode == 2) return true;
   const int G = persistent_grid();
   if (vark) {
     const int64_t big = static_cast<int64_t>(pl.E) * cdiv(M_out, BM) * cdiv(N, BN);
-    const int64_t mid = static_cast<int64_t>(pl.E) * cdiv(M_out, kMidDwM) * cdiv(N, kMidN);
+    const int64_t mid = static_cast<int64_t>(pl.E) * cdiv(M_out, kMidDwH * kMidUnit) * cdiv(N, kMidN);
     return 13 * ((mid + 2 * G - 1) / (2 * G)) < 20 * ((big + G - 1) / G);
   }
   const int steps = cdiv(K, 64);
@@ -2292,7 +1921,7 @@ bool use_mid_tiles(const FfnPlan& pl, moe_dtype dt, bool vark, bool gated, bool 
   int64_t t_mid = 0;
   for (int h = 1; h <= kMidMaxH; ++h) {
     const int64_t n = (2 * per + kMidUnit + 2 * kMidUnit * h - 1) / (2 * kMidUnit * h);
-    const int64_t t = mid_time(n * pl.E * cdiv(N, gated ? kMidN / 2 : kMidN), h, 2 * G, steps);
+    const int64_t t = mid_time(n * pl.E * cdiv(N, gated ? kMidN / 2 : kMidN), h, 2 * G, steps, kStep16);
     if (h == 1 || t < t_mid) t_mid = t;
   }
   return t_mid < t_big;
@@ -2326,9 +1955,18 @@ moe_status launch_gemm(hipStream_t s, moe_dtype dt, const FfnPlan& pl, char* ws,
   constexpr bool VARK = MODE == M_DW, GATED = MODE == M_FWD1_SWIGLU;
   constexpr bool ACTIVE = MODE != M_STORE && MODE != M_DW;
   const bool mid = use_mid_tiles(pl, dt, VARK, GATED, ACTIVE, p.N, p.M_out, VARK ? 0 : p.K);
-  const int tm = mid ? kMidDwM : BM, tn = mid ? kMidN : BN;
+  const int tn = mid ? kMidN : BN;
   p.ntiles = cdiv(p.N, GATED ? tn / 2 : tn);
-  if (VARK) p.mtiles_out = cdiv(p.M_out, tm);
+  p.dw_h = kMidDwH;
+  if constexpr (VARK) {
+    // fp32 weight gradients: the highest tile that still gives every place of
+    // the persistent grid one
+    if (dt == MOE_F32)
+      while (p.dw_h > 1 && static_cast<int64_t>(pl.E) * cdiv(p.M_out, p.dw_h * kMidUnit) * p.ntiles <
+                               2 * persistent_grid())
+        p.dw_h /= 2;
+    p.mtiles_out = cdiv(p.M_out, mid ? p.dw_h * kMidUnit : BM);
+  }
   // tile list 0: the products with N = f (H, dA); list 1: N = d (Y, dX)
   p.mid_list = PASS == P_FWD_H || PASS == P_BWD_DA ? 0 : 1;
   if (mid) p.mtile = reinterpret_cast<const int2*>(ws + pl.o_mid) + p.mid_list * static_cast<int64_t>(pl.max_mid);
@@ -2339,26 +1977,14 @@ moe_status launch_gemm(hipStream_t s, moe_dtype dt, const FfnPlan& pl, char* ws,
                                        p.ntiles;
   const int64_t full = (mid ? 2 : 1) * static_cast<int64_t>(persistent_grid());
   const int grid = static_cast<int>(std::min(full, std::max<int64_t>(kXcds, (max_items + kXcds - 1) / kXcds * kXcds)));
-  if constexpr ((MODE == M_FWD1 || MODE == M_FWD1_SWIGLU || MODE == M_STORE) &&
-                (PASS == P_FWD_H || PASS == P_FWD_Y)) {
-    // fp32 forward with few rows: one wavefront per 32x32 output block
-    const int64_t mb = cdiv(pl.rows_alloc, kTinyB), nb = cdiv(p.N, kTinyB);
-    const int64_t items = static_cast<int64_t>(pl.E) * mb * nb;
-    if (dt == MOE_F32 && g_tile_mode != 1 && items <= kTinyMaxItems) {
-      MOE_TIMED(pass_name(PASS), s);
-      ffn_gemm_f32_tiny_kernel<MODE><<<static_cast<unsigned>(cdiv(items, 4)), 256, 0, s>>>(
-          p, pl.E, static_cast<int>(mb), static_cast<int>(nb));
-      MOE_LAUNCH_CHECK();
-      return MOE_OK;
-    }
-  }
   MOE_TIMED(pass_name(PASS), s);
-  if (dt == MOE_BF16 && mid)
+  if (dt == MOE_F32) {
+    if constexpr (PASS != P_BWD_DX_T) ffn_gemm_f32_kernel<MODE, PASS><<<grid, kThreads16, 0, s>>>(p);
+  } else if (mid) {
     ffn_gemm16_mid_kernel<MODE, PASS><<<grid, kThreads16, 0, s>>>(p);
-  else if (dt == MOE_BF16)
+  } else {
     ffn_gemm16_kernel<MODE, PASS><<<grid, kThreads16, 0, s>>>(p);
-  else
-    ffn_gemm_f32_kernel<MODE, PASS><<<grid, kThreads, 0, s>>>(p);
+  }
   MOE_LAUNCH_CHECK();
   return MOE_OK;
 }

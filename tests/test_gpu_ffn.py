@@ -259,6 +259,23 @@ def test_tile_kernels_bit_identical(act):
     assert np.isfinite(gs[0]["dw1"]).all()
 
 
+# heights of the 128-column tiles: 8 column tiles (16 for the gated forward),
+# so 2048 h rows fill one round of tiles of h units of 32 rows; the uneven
+# split leaves tiles of h and of fewer units, the second expert a partial one
+@pytest.mark.parametrize("h,act", [(1, "relu"), (2, "swiglu"), (3, "gelu_tanh"), (4, "relu"),
+                                   (5, "swiglu"), (6, "gelu_tanh")])
+def test_tile_heights_bit_identical(h, act):
+    E, d, f = 3, 72, 1000
+    n = 1900 * h if act != "swiglu" else 950 * h
+    rows, cap, off, R, P = _problem(E, d, f, [n + 17, 0, 33], [0, 1, 2], act, "bf16", False, 80 + h)
+    gs = [_gpu(rows, cap, off, R, P, act, "bf16", E, d, f, tiles=t) for t in (1, 2)]
+    valid = np.concatenate([np.arange(off[e], off[e] + rows[e]) for e in range(E)])
+    np.testing.assert_array_equal(gs[0]["h"][:, valid], gs[1]["h"][:, valid])
+    for name in ("y", "dx"):
+        np.testing.assert_array_equal(gs[0][name][valid], gs[1][name][valid], err_msg=name)
+    assert np.isfinite(gs[0]["dx"][valid]).all()
+
+
 # ---- combine, combine backward, dispatch backward -----------------------------
 @pytest.mark.parametrize("dt,k,d", [("bf16", 2, 512), ("f32", 1, 64), ("bf16", 3, 136),
                                     ("bf16", 5, 1096), ("f32", 2, 584),

@@ -70,13 +70,11 @@ __global__ __launch_bounds__(256) void cached_weights_kernel(const float* __rest
                                                              const int32_t* __restrict__ ids,
                                                              int T, int E, int k, int renorm,
                                                              float* __restrict__ weights) {
-  const int t = blockIdx.x * 256 + threadIdx.x;
-  if (t >= T) return;
-  const float* l = logits + static_cast<size_t>(t) * E;
-  float m = -INFINITY;
-  for (int e = 0; e < E; ++e) m = fmaxf(m, l[e]);
-  float s = 0.f;
-  for (int e = 0; e < E; ++e) s += expf(l[e] - m);
+  const int t = blockIdx.x * 32 + (threadIdx.x >> 3), sub = threadIdx.x & 7;
+  const float* l = logits + static_cast<size_t>(min(t, T - 1)) * E;
+  float z[kGroupE], m, s;
+  group8_softmax(l, E, sub, z, m, s);
+  if (t >= T || sub != 0) return;
   float pe[kMaxK];
   float sel = 0.f;
 #pragma unroll
@@ -123,7 +121,7 @@ extern "C" moe_status moe_cached_weights(void* stream, int T, int E, int k, int 
   if (!logits || !ids || !weights) return MOE_EINVAL;
   hipStream_t s = static_cast<hipStream_t>(stream);
   MOE_TIMED("cached_weights", s);
-  cached_weights_kernel<<<(T + 255) / 256, 256, 0, s>>>(logits, ids, T, E, k, renorm, weights);
+  cached_weights_kernel<<<(T + 31) / 32, 256, 0, s>>>(logits, ids, T, E, k, renorm, weights);
   MOE_LAUNCH_CHECK();
   return MOE_OK;
 }

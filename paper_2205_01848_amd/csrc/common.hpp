@@ -92,6 +92,102 @@ __device__ __forceinline__ float wave_sum(float v) {
   return v;
 }
 
+// ---- fp32 x bf16 products on bf16 matrix cores --------------------------------
+// A float is the sum of three bf16 values (its top 8 significant bits, the
+// next 8, the last 8: each the truncation of what the ones before leave), so
+// a product with a bf16 value is the sum of three exact bf16 products, and
+// three bf16 MFMAs with fp32 sums give what fp32 FMAs give, at 16 / 3 times
+// the rate of fp32 MFMAs.  An infinity keeps to the first part.
+struct Split8 {
+  uint4 part[3];   // 8 values each, packed bf16
+};
+__device__ __forceinline__ uint32_t high_halves(uint32_t lo, uint32_t hi) {
+  return __builtin_amdgcn_perm(hi, lo, 0x07060302u);
+}
+__device__ __forceinline__ uint32_t low_halves(uint32_t lo, uint32_t hi) {
+  return __builtin_amdgcn_perm(hi, lo, 0x05040100u);
+}
+__device__ __forceinline__ Split8 split8(const float (&g)[8]) {
+  Split8 o;
+  uint32_t* const p[3] = {&o.part[0].x, &o.part[1].x, &o.part[2].x};
+  uint32_t h[8], m[8], l[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    h[i] = __float_as_uint(g[i]);
+    const float r1 = __builtin_isinf(g[i]) ? 0.f : g[i] - __uint_as_float(h[i] & 0xFFFF0000u);
+    m[i] = __float_as_uint(r1);
+    l[i] = __float_as_uint(r1 - __uint_as_float(m[i] & 0xFFFF0000u));
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    p[0][i] = high_halves(h[2 * i], h[2 * i + 1]);
+    p[1][i] = high_halves(m[2 * i], m[2 * i + 1]);
+    p[2][i] = high_halves(l[2 * i], l[2 * i + 1]);
+  }
+  return o;
+}
+// 8 x 8 transpose: out[j] = element j of each of the 8 rows (bf16).
+__device__ __forceinline__ void transpose8(const uint4 (&in)[8], uint4 (&out)[8]) {
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    uint32_t d[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) d[i] = c == 0 ? in[i].x : c == 1 ? in[i].y : c == 2 ? in[i].z : in[i].w;
+    out[2 * c] = make_uint4(low_halves(d[0], d[1]), low_halves(d[2], d[3]),
+                            low_halves(d[4], d[5]), low_halves(d[6], d[7]));
+    out[2 * c + 1] = make_uint4(high_halves(d[0], d[1]), high_halves(d[2], d[3]),
+                                high_halves(d[4], d[5]), high_halves(d[6], d[7]));
+  }
+}
+// c += a * b over 32 k: lane l = 16 G + n holds row (column) n at k = 8 G .. +7
+__device__ __forceinline__ void mma_split(floatx4& c, const Split8& a, const uint4& b) {
+  const bf16x8 bv = __builtin_bit_cast(bf16x8, b);
+#pragma unroll
+  for (int i = 2; i >= 0; --i)
+    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a.part[i]), bv, c, 0, 0, 0);
+}
+
+// Eight lanes (8i .. 8i+7 of a wavefront) share one token's experts: lane
+// `sub` of them holds experts sub, sub + 8, .., at most kGroupE of them.  A
+// thread per token walks up to 64 experts several times over in series; the
+// group takes an eighth of each walk and three lane exchanges.  Every kernel
+// that evaluates the gate's softmax uses this one order of its sum.
+constexpr int kGroupE = 8;
+__device__ __forceinline__ float group8_sum(float v) {
+#pragma unroll
+  for (int o = 1; o < 8; o <<= 1) v += __shfl_xor(v, o, 64);
+  return v;
+}
+__device__ __forceinline__ float group8_max(float v) {
+#pragma unroll
+  for (int o = 1; o < 8; o <<= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
+  return v;
+}
+// z[i] = exp(l[sub + 8 i] - m) (0 past E), m the largest logit, s the sum of
+// all z.
+__device__ __forceinline__ void group8_softmax(const float* l, int E, int sub, float (&z)[kGroupE],
+                                               float& m, float& s) {
+  m = -INFINITY;
+#pragma unroll
+  for (int i = 0; i < kGroupE; ++i) {
+    const int e = sub + 8 * i;
+    z[i] = e < E ? l[e] : -INFINITY;
+    m = fmaxf(m, z[i]);
+  }
+  m = group8_max(m);
+  s = 0.f;
+#pragma unroll
+  for (int i = 0; i < kGroupE; ++i) {
+    if (8 * i >= E) {
+      z[i] = 0.f;
+      continue;
+    }
+    z[i] = sub + 8 * i < E ? expf(z[i] - m) : 0.f;
+    s += z[i];
+  }
+  s = group8_sum(s);
+}
+
 __device__ __forceinline__ int ceil_div_i(int a, int b) { return (a + b - 1) / b; }
 
 // ---- opt-in kernel timing (moe_timing_enable / moe_timing_report) ---------

@@ -7,7 +7,7 @@
 // longer than 2048 and at most 8 experts a second kernel streams whole rows
 // and forms the dot products with v_dot2.  Either way x is streamed from HBM
 // exactly once, so the gate is HBM-bound.
-// fp32 forward: one thread per token with float32 FMAs (small layers only).
+// fp32 forward: v_mfma_f32_16x16x4_f32, four waves splitting K.
 
 #include <algorithm>
 #include <type_traits>
@@ -18,40 +18,51 @@
 namespace moe {
 namespace {
 
-// Per-token finish: softmax, top-k with ties to the lower index, weights.
-// `l` points at the token's E logits (LDS).
-__device__ __forceinline__ void finish_token(const float* l, int E, int k,
-                                             int renorm, int32_t* ids_out,
-                                             float* w_out) {
-  float m = -INFINITY;
-  for (int e = 0; e < E; ++e) m = fmaxf(m, l[e]);
-  float s = 0.f;
-  for (int e = 0; e < E; ++e) s += expf(l[e] - m);
+// Finish of one token by a group of eight lanes (all lanes of the wavefront
+// call it; `live` guards the stores): softmax, top-k with ties to the lower
+// index, weights.  `l` points at the token's E logits (LDS).  The pick is the
+// one a scan in index order finds that starts from the first untaken expert
+// and moves on strictly larger logits: that first one if its logit is a NaN,
+// else the largest (a NaN further on is never larger).
+__device__ __forceinline__ void finish_group8(const float* l, int E, int k, int renorm, int sub,
+                                              bool live, int32_t* ids_out, float* w_out) {
+  float z[kGroupE], m, s;
+  group8_softmax(l, E, sub, z, m, s);
   uint64_t taken = 0;
-  float pe[kMaxK];
-  int id[kMaxK];
-  float sel = 0.f;
+  float sel = 0.f, mine = 0.f;
+  int my_id = 0;
 #pragma unroll
   for (int j = 0; j < kMaxK; ++j) {
     if (j < k) {
-      int bi = -1;
-      float best = -INFINITY;
-      for (int e = 0; e < E; ++e) {
-        if ((taken >> e) & 1ull) continue;
-        if (bi < 0 || l[e] > best) { best = l[e]; bi = e; }
+      const int first = __builtin_ctzll(~taken);
+      const float lf = l[first];
+      int bi = first;
+      float best = lf;
+#pragma unroll
+      for (int i = 0; i < kGroupE; ++i) {
+        const int e = sub + 8 * i;
+        if (e >= E || ((taken >> e) & 1ull)) continue;
+        const float v = l[e];
+        if (v > best || (v == best && e < bi)) { best = v; bi = e; }
+      }
+#pragma unroll
+      for (int o = 1; o < 8; o <<= 1) {
+        const float v = __shfl_xor(best, o, 64);
+        const int e = __shfl_xor(bi, o, 64);
+        if (v > best || (v == best && e < bi)) { best = v; bi = e; }
       }
       taken |= 1ull << bi;
-      id[j] = bi;
-      pe[j] = expf(l[bi] - m);
-      sel += pe[j];
+      const float pe = expf(l[bi] - m);
+      sel += pe;
+      if (sub == j) {
+        mine = pe;
+        my_id = bi;
+      }
     }
   }
-#pragma unroll
-  for (int j = 0; j < kMaxK; ++j) {
-    if (j < k) {
-      ids_out[j] = id[j];
-      w_out[j] = renorm ? pe[j] / sel : pe[j] / s;
-    }
+  if (live && sub < k) {
+    ids_out[sub] = my_id;
+    w_out[sub] = renorm ? mine / sel : mine / s;
   }
 }
 
@@ -213,11 +224,11 @@ __global__ __launch_bounds__(256) void gate_fwd_bf16_kernel(
     if (tb + row < T) logits[static_cast<size_t>(tb + row) * E + e] = v;
   }
   __syncthreads();
-  const int row = threadIdx.x;
-  if (row < tiles * kGateTile && tb + row < T) {
+  for (int row = threadIdx.x >> 3; row < tiles * kGateTile; row += 32) {
     const int tt = row / kGateTile, rr = row - tt * kGateTile;
     const size_t t = tb + row;
-    finish_token(&wpart(tt * S)[rr][0], E, k, renorm, ids + t * k, weights + t * k);
+    finish_group8(&wpart(tt * S)[rr][0], E, k, renorm, threadIdx.x & 7, tb + row < T, ids + t * k,
+                  weights + t * k);
   }
 }
 
@@ -244,7 +255,7 @@ inline int gate_split(int T) {
 // wave's next group, so one group (4 * NCH KB) stays in flight per wave;
 // every load is issued (out-of-range lanes read zeros) and the loops have
 // no branch but their own.  The logits of a batch of 32 tokens collect in
-// the wave's LDS, then 32 lanes finish one token each.
+// the wave's LDS, then eight lanes finish each of them.
 // Sum of value (lane >> 1) of v[0..31] over all 64 lanes, in lanes lane and
 // lane ^ 1.  Each step pairs a lane with a partner that holds the same
 // subset of values, keeps one half of that subset (the upper half in the
@@ -381,187 +392,287 @@ __global__ __launch_bounds__(256, 2) void gate_rows_bf16_kernel(
       if ((lane & 1) == 0) my[s * 32 + idx] = l;
       if ((lane & 1) == 0 && ve < E && tok < T) logits[static_cast<size_t>(tok) * E + ve] = l;
     }
-    // token slot lane = (group s, token t) of the batch, its logits at lane * EC
+    // token slot (group s, token t) of the batch: its logits at slot * EC;
+    // eight lanes finish one
     __builtin_amdgcn_wave_barrier();
-    const int tok = (gb + (lane / TPW) * nw) * TPW + lane % TPW;
-    if (lane < kRowsBatch && tok < T)
-      finish_token(my + lane * EC, E, k, renorm, ids + static_cast<size_t>(tok) * k,
-                   weights + static_cast<size_t>(tok) * k);
+    for (int slot = lane >> 3; slot < kRowsBatch; slot += 8) {
+      const int tok = (gb + (slot / TPW) * nw) * TPW + slot % TPW;
+      finish_group8(my + slot * EC, E, k, renorm, lane & 7, tok < T,
+                    ids + static_cast<size_t>(tok) * k, weights + static_cast<size_t>(tok) * k);
+    }
     __builtin_amdgcn_wave_barrier();
   }
 }
 
-__global__ __launch_bounds__(64) void gate_fwd_f32_kernel(
+// fp32 gate: a workgroup scores 16 tokens against EB blocks of 16 experts with
+// v_mfma_f32_16x16x4_f32 (token rows as A, expert rows of w_g as B).  Lane l =
+// 16 G + n reads 16 bytes of row n, k = 16 s + 4 G .. +3, and MFMA j of step s
+// takes its j-th value, so every k of the step enters one MFMA, of A and B
+// alike.  Wavefront w takes steps w, w + 4, .. (four steps are 256 contiguous
+// bytes of a row), kF32Steps of them loaded ahead; the four partial scores
+// are summed through LDS in order.  One thread per token instead leaves T / 64
+// wavefronts walking whole rows: T = 2048, d = 256, E = 8 took 55 us, now
+// 7.6 us.
+constexpr int kF32Tok = 16;
+constexpr int kF32Steps = 4;
+template <int EB>
+__global__ __launch_bounds__(256) void gate_fwd_f32_kernel(
     const float* __restrict__ x, const float* __restrict__ wg,
     const float* __restrict__ bias, int T, int d, int E, int k, int renorm,
     float* __restrict__ logits, int32_t* __restrict__ ids,
     float* __restrict__ weights) {
-  __shared__ float sl[64][65];
-  const int lane = threadIdx.x;
-  const int t = blockIdx.x * 64 + lane;
-  if (t < T) {
-    // the token's row is read 16 bytes at a time (d is a multiple of 8, rows
-    // start 32-byte aligned), eight such loads issued before they are used,
-    // and scored against 8 experts per pass: 8 independent sums, each over i
-    // in order; w_g is the same for every lane
-    const float* xr = x + static_cast<size_t>(t) * d;
-    constexpr int kXb = 8;   // row vectors in flight
-    for (int e0 = 0; e0 < E; e0 += 8) {
-      float a[8];
+  __shared__ float part[4][kF32Tok][EB * 16 + 1];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = lane & 15, G = lane >> 4;
+  const int t0 = blockIdx.x * kF32Tok;
+  const int nsteps = (d + 15) / 16;
+  const float* xr = x + static_cast<size_t>(min(t0 + n, T - 1)) * d;
+  floatx4 acc[EB];
 #pragma unroll
-      for (int q = 0; q < 8; ++q) a[q] = 0.f;
-      for (int i0 = 0; i0 < d; i0 += 4 * kXb) {
-        float4 xv[kXb];
+  for (int b = 0; b < EB; ++b) acc[b] = floatx4{0.f, 0.f, 0.f, 0.f};
+  for (int s0 = wave; s0 < nsteps; s0 += 4 * kF32Steps) {
+    float4 a[kF32Steps], w[kF32Steps][EB];
 #pragma unroll
-        for (int u = 0; u < kXb; ++u)
-          if (i0 + 4 * u < d) xv[u] = *reinterpret_cast<const float4*>(xr + i0 + 4 * u);
+    for (int u = 0; u < kF32Steps; ++u) {
+      const int kk = 16 * (s0 + 4 * u) + 4 * G;   // d is a multiple of 8: whole or past the end
+      const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+      a[u] = kk < d ? *reinterpret_cast<const float4*>(xr + kk) : zero;
 #pragma unroll
-        for (int u = 0; u < kXb; ++u) {
-          const int i = i0 + 4 * u;
-          if (i >= d) break;
-#pragma unroll
-          for (int q = 0; q < 8; ++q) {
-            if (e0 + q < E) {
-              const float4 w = *reinterpret_cast<const float4*>(wg + static_cast<size_t>(e0 + q) * d + i);
-              a[q] = fmaf(xv[u].x, w.x, a[q]);
-              a[q] = fmaf(xv[u].y, w.y, a[q]);
-              a[q] = fmaf(xv[u].z, w.z, a[q]);
-              a[q] = fmaf(xv[u].w, w.w, a[q]);
-            }
-          }
-        }
-      }
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const int e = e0 + q;
-        if (e < E) {
-          const float v = a[q] + (bias ? bias[e] : 0.f);
-          sl[lane][e] = v;
-          logits[static_cast<size_t>(t) * E + e] = v;
-        }
-      }
+      for (int b = 0; b < EB; ++b)
+        w[u][b] = kk < d && 16 * b + n < E
+                      ? *reinterpret_cast<const float4*>(wg + static_cast<size_t>(16 * b + n) * d + kk)
+                      : zero;
     }
-    finish_token(&sl[lane][0], E, k, renorm, ids + static_cast<size_t>(t) * k,
-                 weights + static_cast<size_t>(t) * k);
+#pragma unroll
+    for (int u = 0; u < kF32Steps; ++u)
+#pragma unroll
+      for (int b = 0; b < EB; ++b) {
+        acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u].x, w[u][b].x, acc[b], 0, 0, 0);
+        acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u].y, w[u][b].y, acc[b], 0, 0, 0);
+        acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u].z, w[u][b].z, acc[b], 0, 0, 0);
+        acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u].w, w[u][b].w, acc[b], 0, 0, 0);
+      }
+  }
+  // acc[b][q]: token 4 G + q, expert 16 b + n
+#pragma unroll
+  for (int b = 0; b < EB; ++b)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) part[wave][4 * G + q][16 * b + n] = acc[b][q];
+  __syncthreads();
+  for (int i = tid; i < kF32Tok * E; i += 256) {
+    const int r = i / E, e = i - r * E;
+    float v = part[0][r][e];
+    for (int w = 1; w < 4; ++w) v += part[w][r][e];
+    v += bias ? bias[e] : 0.f;
+    part[0][r][e] = v;
+    if (t0 + r < T) logits[static_cast<size_t>(t0 + r) * E + e] = v;
+  }
+  __syncthreads();
+  if (tid < 8 * kF32Tok) {
+    const int r = tid >> 3;
+    const size_t t = t0 + r;
+    finish_group8(&part[0][r][0], E, k, renorm, tid & 7, t0 + r < T, ids + t * k, weights + t * k);
   }
 }
 
 // ---- backward ---------------------------------------------------------------
-// dlogits per token (thread per token).
-__global__ __launch_bounds__(64) void gate_bwd_dlogits_kernel(
+// dlogits, eight lanes per token.
+__global__ __launch_bounds__(256) void gate_bwd_dlogits_kernel(
     const float* __restrict__ logits, const int32_t* __restrict__ ids,
     const float* __restrict__ dweights, const float* __restrict__ coef, int T, int E, int k,
     int renorm, float* __restrict__ dlogits) {
-  __shared__ float sp[64][65];
-  __shared__ float sdp[64][65];
-  const int lane = threadIdx.x;
-  const int t = blockIdx.x * 64 + lane;
-  if (t >= T) return;
-  const float* l = logits + static_cast<size_t>(t) * E;
-  float m = -INFINITY;
-  for (int e = 0; e < E; ++e) m = fmaxf(m, l[e]);
-  float s = 0.f;
-  for (int e = 0; e < E; ++e) {
-    const float z = expf(l[e] - m);
-    sp[lane][e] = z;
-    s += z;
-  }
+  const int t = blockIdx.x * 32 + (threadIdx.x >> 3), sub = threadIdx.x & 7;
+  const size_t tt = min(t, T - 1);
+  float p[kGroupE], m, s;
+  group8_softmax(logits + tt * E, E, sub, p, m, s);
   const float inv = 1.f / s;
-  for (int e = 0; e < E; ++e) {
-    sp[lane][e] *= inv;
-    sdp[lane][e] = coef ? coef[e] : 0.f;  // a dprobs term shared by every token
+#pragma unroll
+  for (int i = 0; i < kGroupE; ++i) p[i] *= inv;
+  // picks of each of the lane's experts and the sum of their dweights.  An id
+  // outside [0, E) (a bad cached id) is not a pick: its weight is 0 and it
+  // takes no part in the normalisation, as in moe_cached_weights.
+  float dw[kGroupE], hits[kGroupE];
+#pragma unroll
+  for (int i = 0; i < kGroupE; ++i) dw[i] = hits[i] = 0.f;
+  const int32_t* id = ids + tt * k;
+  for (int j = 0; j < k; ++j) {
+    const int e = id[j];
+    const float g = dweights[tt * k + j];
+#pragma unroll
+    for (int i = 0; i < kGroupE; ++i)
+      if (e == sub + 8 * i && e < E) {
+        dw[i] += g;
+        hits[i] += 1.f;
+      }
   }
-  const int32_t* id = ids + static_cast<size_t>(t) * k;
-  const float* dw = dweights + static_cast<size_t>(t) * k;
-  // An id outside [0, E) (a bad cached id) is not a pick: its weight is 0
-  // and it takes no part in the normalisation, as in moe_cached_weights.
   float S = 0.f, dot = 0.f;
-  for (int j = 0; j < k; ++j) {
-    const int e = id[j];
-    if (e >= 0 && e < E) S += sp[lane][e];
-  }
   if (renorm) {
-    for (int j = 0; j < k; ++j) {
-      const int e = id[j];
-      if (e >= 0 && e < E) dot += dw[j] * (sp[lane][e] / S);
-    }
+#pragma unroll
+    for (int i = 0; i < kGroupE; ++i)
+      if (hits[i] > 0.f) S += hits[i] * p[i];
+    S = group8_sum(S);
+#pragma unroll
+    for (int i = 0; i < kGroupE; ++i)
+      if (hits[i] > 0.f) dot += dw[i] * (p[i] / S);
+    dot = group8_sum(dot);
   }
-  for (int j = 0; j < k; ++j) {
-    const int e = id[j];
-    if (e < 0 || e >= E) continue;
-    const float g = renorm ? (dw[j] - dot) / S : dw[j];
-    sdp[lane][e] += g;
+  float pd = 0.f, dp[kGroupE];
+#pragma unroll
+  for (int i = 0; i < kGroupE; ++i) {
+    const int e = sub + 8 * i;
+    dp[i] = 0.f;
+    if (e >= E) continue;
+    if (coef) dp[i] = coef[e];   // a dprobs term shared by every token
+    if (hits[i] > 0.f) dp[i] += renorm ? (dw[i] - hits[i] * dot) / S : dw[i];
+    pd += dp[i] * p[i];
   }
-  float pd = 0.f;
-  for (int e = 0; e < E; ++e) pd += sdp[lane][e] * sp[lane][e];
-  float* out = dlogits + static_cast<size_t>(t) * E;
-  for (int e = 0; e < E; ++e) out[e] = sp[lane][e] * (sdp[lane][e] - pd);
+  pd = group8_sum(pd);
+  if (t >= T) return;
+#pragma unroll
+  for (int i = 0; i < kGroupE; ++i) {
+    const int e = sub + 8 * i;
+    if (e < E) dlogits[tt * E + e] = p[i] * (dp[i] - pd);
+  }
 }
 
-// dw_g partial sums: block = 64 threads x 8 columns = 512 columns, 8 experts,
-// one chunk of kGbTok tokens.  grid = (E/8 groups, d/512, chunks).  The
-// tokens of a chunk are taken kGbBatch at a time: the batch's x vectors are
-// loaded before any of them is used, so the loads overlap instead of each
-// waiting out its own latency.  Per column the sum runs over the tokens in
-// order (batching changes only when the loads are issued).
-constexpr int kGbTok = 128;
-constexpr int kGbBatch = 8;
+// dw_g partial sums: dw_g[e, c] = sum over tokens of dl[t, e] x[t, c] on
+// matrix cores, dl in fp32.  A wavefront keeps EB blocks of 16 experts by
+// 16 kVec columns and walks TW tokens, 32 at a time with the next 32 loading;
+// the four wavefronts of a workgroup take consecutive token ranges and add
+// their sums through LDS in order, so a partial sum in memory covers 4 TW
+// tokens.  x is read 16 bytes per lane (kVec columns from kVec n), and the
+// MFMA of column block j takes the lane's j-th values, so its column n stands
+// for column kVec n + j.
+//  * bf16 x: lane l = 16 G + n loads tokens 8 G .. +7 of the 32, an 8 x 8
+//    transpose in registers makes the eight B fragments, and dl enters as
+//    three bf16 parts (split8).
+//  * fp32 x: v_mfma_f32_16x16x4_f32, lane l supplies token 4 u + G of step u.
+// One FMA per (token, expert, column) with eight experts per thread read x
+// E / 8 times and left most CUs without work on short batches.  T = 8192, d =
+// 2048, E = 64: 76 -> 26 us; T = 3001, d = 1000, E = 13: 59 -> 7 us;
+// fp32 T = 2048, d = 256, E = 8: 49 -> 4 us; T = 65536, d = 4096, E = 8: 139
+// -> 132 us (537 MB).
+constexpr int kGbStep = 32;            // tokens
+constexpr int kGbTok = 128;            // tokens per partial sum, at least
+constexpr int kGbWaves = 2048;         // wavefronts a launch aims at
 
-template <typename T>
-__global__ __launch_bounds__(64) void gate_bwd_dwg_partial_kernel(
-    const T* __restrict__ x, const float* __restrict__ dl, int Ttok, int d,
-    int E, float* __restrict__ part) {
-  constexpr int kVecs = sizeof(T) / 2;   // 16-byte vectors per 8 elements
-  const int eg = blockIdx.x * 8;
-  const int c0 = (blockIdx.y * 64 + threadIdx.x) * 8;
-  const int chunk = blockIdx.z;
-  const int tb = chunk * kGbTok, te = min(Ttok, tb + kGbTok);
-  float acc[8][8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e)
-#pragma unroll
-    for (int c = 0; c < 8; ++c) acc[e][c] = 0.f;
+template <typename T, int EB>
+__global__ __launch_bounds__(256) void gate_bwd_dwg_partial_kernel(
+    const T* __restrict__ x, const float* __restrict__ dl, int Ttok, int d, int E, int TW,
+    float* __restrict__ part) {
+  constexpr int V = Elem<T>::kVec;
+  __shared__ floatx4 sums[4][V][64];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+  const int n = lane & 15, G = lane >> 4;
+  const int c0 = (blockIdx.x * 16 + n) * V;     // the lane's first column
+  const int chunk = blockIdx.y;
+  const int tb = (chunk * 4 + wave) * TW, te = min(Ttok, tb + TW);
   const bool colok = c0 < d;
-  for (int t0 = tb; t0 < te; t0 += kGbBatch) {
-    uint4 raw[kGbBatch][kVecs];
+  // columns past d read column 0 and experts past E expert 0 (their sums are
+  // not stored); tokens past te count as zero rows of both
+  const T* xp = x + (colok ? c0 : 0);
+  int go[EB];
 #pragma unroll
-    for (int u = 0; u < kGbBatch; ++u) {
-      const int t = t0 + u;
+  for (int b = 0; b < EB; ++b) go[b] = 16 * b + n < E ? 16 * b + n : 0;
+  constexpr bool BF = sizeof(T) == 2;
+  // token of the lane's i-th value among the 32
+  auto tok = [&](int i) { return BF ? 8 * G + i : 4 * i + G; };
+  floatx4 acc[EB][V];
 #pragma unroll
-      for (int v = 0; v < kVecs; ++v) {
-        raw[u][v] = (colok && t < te)
-                        ? reinterpret_cast<const uint4*>(x + static_cast<size_t>(t) * d + c0)[v]
-                        : make_uint4(0u, 0u, 0u, 0u);
+  for (int b = 0; b < EB; ++b)
+#pragma unroll
+    for (int j = 0; j < V; ++j) acc[b][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+  struct Batch {
+    uint4 x[8];
+    float g[EB][8];
+  };
+  auto load = [&](int t0, Batch& h) {
+    if (t0 + kGbStep <= te) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const size_t t = t0 + tok(i);
+        h.x[i] = *reinterpret_cast<const uint4*>(xp + t * d);
+#pragma unroll
+        for (int b = 0; b < EB; ++b) h.g[b][i] = dl[t * E + go[b]];
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const bool in = t0 + tok(i) < te;
+        const size_t t = in ? t0 + tok(i) : 0;
+        const uint4 v = *reinterpret_cast<const uint4*>(xp + t * d);
+        h.x[i] = in ? v : make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+        for (int b = 0; b < EB; ++b) {
+          const float g = dl[t * E + go[b]];
+          h.g[b][i] = in ? g : 0.f;
+        }
       }
     }
+  };
+  Batch cur, nxt;
+  load(tb, cur);
+#pragma unroll 1
+  for (int t0 = tb; t0 < te; t0 += kGbStep) {
+    load(t0 + kGbStep, nxt);   // past te: zeros, not used
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (BF) {
+      uint4 f[8];
+      transpose8(cur.x, f);
 #pragma unroll
-    for (int u = 0; u < kGbBatch; ++u) {
-      const int t = t0 + u;
-      if (t >= te) break;
-      float xv[8];
-      if constexpr (sizeof(T) == 2) {
-        unpack8(raw[u][0], xv);
-      } else {
-        Elem<float>::load(raw[u][0], xv);
-        Elem<float>::load(raw[u][kVecs - 1], xv + 4);
+      for (int b = 0; b < EB; ++b) {
+        const Split8 g = split8(cur.g[b]);
+#pragma unroll
+        for (int j = 0; j < V; ++j) mma_split(acc[b][j], g, f[j]);
       }
-      const float* dlr = dl + static_cast<size_t>(t) * E + eg;
+    } else {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const float g = (eg + e < E) ? dlr[e] : 0.f;
+      for (int i = 0; i < 8; ++i) {
+        float f[V];
+        Elem<T>::load(cur.x[i], f);
 #pragma unroll
-        for (int c = 0; c < 8; ++c) acc[e][c] = fmaf(g, xv[c], acc[e][c]);
+        for (int j = 0; j < V; ++j)
+#pragma unroll
+          for (int b = 0; b < EB; ++b)
+            acc[b][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(cur.g[b][i], f[j], acc[b][j], 0, 0, 0);
       }
     }
+    cur = nxt;
   }
-  if (!colok) return;
+  // acc[b][j][q]: expert 16 b + 4 G + q, column c0 + j.  Wavefront w finishes
+  // q = w.
+  float* out = part + static_cast<size_t>(chunk) * E * d;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    if (eg + e >= E) break;
-    float* p = part + (static_cast<size_t>(chunk) * E + eg + e) * d + c0;
-    *reinterpret_cast<float4*>(p) = make_float4(acc[e][0], acc[e][1], acc[e][2], acc[e][3]);
-    *reinterpret_cast<float4*>(p + 4) = make_float4(acc[e][4], acc[e][5], acc[e][6], acc[e][7]);
+  for (int b = 0; b < EB; ++b) {
+    if (b) __syncthreads();
+#pragma unroll
+    for (int j = 0; j < V; ++j) sums[wave][j][lane] = acc[b][j];
+    __syncthreads();
+    float v[V];
+#pragma unroll
+    for (int j = 0; j < V; ++j) {
+      auto at = [&](int w) { return reinterpret_cast<const float*>(&sums[w][j][lane])[wave]; };
+      v[j] = at(0);
+#pragma unroll
+      for (int w = 1; w < 4; ++w) v[j] += at(w);
+    }
+    const int e = 16 * b + 4 * G + wave;
+    if (colok && e < E) {
+      float* o = out + static_cast<size_t>(e) * d + c0;
+#pragma unroll
+      for (int j = 0; j < V; j += 4)
+        *reinterpret_cast<float4*>(o + j) = make_float4(v[j], v[j + 1], v[j + 2], v[j + 3]);
+    }
   }
+}
+
+// Tokens per wavefront of the partial sums: a multiple of 32 that leaves
+// about kGbWaves wavefronts.
+inline int gate_bwd_tokens(int T, int groups) {
+  const int64_t tw = static_cast<int64_t>(T) * groups / kGbWaves;
+  return static_cast<int>((std::max<int64_t>(tw, 1) + kGbTok / 4 - 1) / (kGbTok / 4) * (kGbTok / 4));
 }
 
 // dw_g[e,i] = sum over chunks in order (loads issued 8 chunks ahead of the adds)
@@ -640,9 +751,17 @@ extern "C" moe_status moe_gate_topk(void* stream, moe_dtype dt, int T, int d,
     else if (E <= 32) go(I1{}, std::integral_constant<int, 4>{}, I3{});
     else go(I2{}, std::integral_constant<int, 8>{}, I2{});
   } else {
-    gate_fwd_f32_kernel<<<dim3((T + 63) / 64), 64, 0, s>>>(
-        static_cast<const float*>(x), static_cast<const float*>(w_g), bias, T, d,
-        E, k, renorm, logits, ids, weights);
+    auto go = [&](auto eb) {
+      gate_fwd_f32_kernel<decltype(eb)::value><<<dim3((T + kF32Tok - 1) / kF32Tok), 256, 0, s>>>(
+          static_cast<const float*>(x), static_cast<const float*>(w_g), bias, T, d, E, k, renorm,
+          logits, ids, weights);
+    };
+    switch ((E + 15) / 16) {
+      case 1: go(std::integral_constant<int, 1>{}); break;
+      case 2: go(std::integral_constant<int, 2>{}); break;
+      case 3: go(std::integral_constant<int, 3>{}); break;
+      default: go(std::integral_constant<int, 4>{}); break;
+    }
   }
   MOE_LAUNCH_CHECK();
   return MOE_OK;
@@ -674,26 +793,39 @@ extern "C" moe_status moe_gate_bwd(void* stream, moe_dtype dt, int T, int d,
   if (!aligned16(x) || !aligned16(dw_g)) return MOE_EINVAL;
   const size_t need = moe_gate_bwd_workspace_bytes(T, d, E);
   if (!workspace || workspace_bytes < need) return MOE_EWORKSPACE;
-  float* part = static_cast<float*>(workspace);
-  const int nchunks = (T + kGbTok - 1) / kGbTok;
   {
     MOE_TIMED("gate_bwd_dlogits", s);
-    gate_bwd_dlogits_kernel<<<dim3((T + 63) / 64), 64, 0, s>>>(logits, ids, dweights,
+    gate_bwd_dlogits_kernel<<<dim3((T + 31) / 32), 256, 0, s>>>(logits, ids, dweights,
                                                              dprob_coef, T, E, k, renorm,
                                                              dlogits);
     MOE_LAUNCH_CHECK();
   }
-  dim3 grid((E + 7) / 8, (d + 511) / 512, nchunks);
+  const int vec = dt == MOE_BF16 ? Elem<uint16_t>::kVec : Elem<float>::kVec;
+  const int groups = (d + 16 * vec - 1) / (16 * vec);
+  const int TW = gate_bwd_tokens(T, groups);
+  const int nchunks = (T + 4 * TW - 1) / (4 * TW);   // at most the workspace's T / kGbTok
+  float* part = nchunks == 1 ? dw_g : static_cast<float*>(workspace);
+  const dim3 grid(groups, nchunks);
   {
-  MOE_TIMED("gate_bwd_dwg_partial", s);
-  if (dt == MOE_BF16)
-    gate_bwd_dwg_partial_kernel<uint16_t><<<grid, 64, 0, s>>>(
-        static_cast<const uint16_t*>(x), dlogits, T, d, E, part);
-  else
-    gate_bwd_dwg_partial_kernel<float><<<grid, 64, 0, s>>>(static_cast<const float*>(x),
-                                                           dlogits, T, d, E, part);
-  MOE_LAUNCH_CHECK();
+    MOE_TIMED("gate_bwd_dwg_partial", s);
+    auto go = [&](auto eb) {
+      constexpr int EB = decltype(eb)::value;
+      if (dt == MOE_BF16)
+        gate_bwd_dwg_partial_kernel<uint16_t, EB><<<grid, 256, 0, s>>>(
+            static_cast<const uint16_t*>(x), dlogits, T, d, E, TW, part);
+      else
+        gate_bwd_dwg_partial_kernel<float, EB><<<grid, 256, 0, s>>>(
+            static_cast<const float*>(x), dlogits, T, d, E, TW, part);
+    };
+    switch ((E + 15) / 16) {
+      case 1: go(std::integral_constant<int, 1>{}); break;
+      case 2: go(std::integral_constant<int, 2>{}); break;
+      case 3: go(std::integral_constant<int, 3>{}); break;
+      default: go(std::integral_constant<int, 4>{}); break;
+    }
+    MOE_LAUNCH_CHECK();
   }
+  if (nchunks == 1) return MOE_OK;
   MOE_TIMED("gate_bwd_dwg_reduce", s);
   gate_bwd_dwg_reduce_kernel<<<dim3((n + 255) / 256), 256, 0, s>>>(part, nchunks,
                                                                    static_cast<int>(n), dw_g);

@@ -379,3 +379,64 @@ def test_gate_backward_skips_invalid_cached_ids(renorm):
     dl_ref, dwg_ref = O.gate_bwd(logits, ids, dwts, renorm, _dec(x, "bf16"))
     assert_close(to_np(dl), dl_ref, 1e-5, "dlogits")
     assert_close(to_np(dwg), dwg_ref, 1e-5, "dw_g")
+
+
+# edges of the matrix-core gate backward: partial and several token ranges of
+# 32 per wavefront, one and many partial sums, partial blocks of 16 experts and
+# of 128 (bf16) or 64 (fp32) columns
+@pytest.mark.parametrize("T,d,E,k", [(1, 8, 2, 1), (31, 136, 17, 2), (33, 64, 33, 3), (129, 72, 48, 2),
+                                     (515, 1000, 64, 8), (9000, 264, 20, 1)])
+@pytest.mark.parametrize("dt", ["bf16", "f32"])
+def test_gate_backward_edges(dt, T, d, E, k):
+    rng = np.random.default_rng(T + E)
+    x = _enc(rng.standard_normal((T, d)), dt)
+    logits = (rng.standard_normal((T, E)) * 2).astype(np.float32)
+    ids = O.topk(logits, k)
+    dwts = (rng.standard_normal((T, k)) * 10.0 ** rng.uniform(-9, 0, (T, k))).astype(np.float32)
+    dl = torch.empty(T, E, dtype=torch.float32, device=dev())
+    dwg = torch.full((E, d), float("nan"), dtype=torch.float32, device=dev())
+    ws = B.workspace(B.moe_gate_bwd_workspace_bytes(T, d, E), dev())
+    B.moe_gate_bwd(to_dev(x, dt), torch.from_numpy(logits).to(dev()),
+                   torch.from_numpy(ids).to(dev()), torch.from_numpy(dwts).to(dev()),
+                   int(k > 1), dl, dwg, ws)
+    torch.cuda.synchronize()
+    # dlogits = p (dp - <dp, p>) with dp = (dw - <dw, w>) / S: differences of
+    # terms of up to max|dw| / S, each within a few ulps (24-bit floats, sums of
+    # at most 64 terms in at most 8 + 3 steps)
+    dl_ref, _ = O.gate_bwd(logits, ids, dwts, int(k > 1), _dec(x, dt))
+    p = np.exp(logits - logits.max(1, keepdims=True).astype(np.float64))
+    p /= p.sum(1, keepdims=True)
+    S = np.take_along_axis(p, ids.astype(np.int64), 1).sum(1, keepdims=True) if k > 1 else 1.0
+    bound = 64 * 2.0 ** -24 * p * np.abs(dwts).max(1, keepdims=True) / S
+    got = to_np(dl)
+    assert (np.abs(got - dl_ref) <= bound + 1e-5 * np.abs(dl_ref)).all()
+    # dw_g from the kernel's own dlogits
+    assert_close(to_np(dwg), got.T @ _dec(x, dt), 1e-5, "dw_g")
+
+
+# dispatch backward of wide gates (more than 16 experts: dlogits as three bf16
+# parts on matrix cores): one and two steps of 32 experts, partial tiles of 16
+# tokens and 128 columns, every pick bound, dlogits off 16-byte alignment
+@pytest.mark.parametrize("T,d,E,k,shift", [(1, 8, 17, 1, 0), (16, 128, 32, 2, 1), (70, 136, 33, 3, 0),
+                                           (700, 264, 64, 8, 3), (1030, 1032, 60, 2, 0),
+                                           (40, 120, 64, 1, 2)])
+def test_dispatch_backward_wide_gate(T, d, E, k, shift):
+    rng = np.random.default_rng(T + d)
+    R = T * k + 3
+    dest = rng.permutation(R)[:T * k].reshape(T, k).astype(np.int32)
+    dest[rng.random((T, k)) < 0.2] = -1
+    dxd = _enc(rng.standard_normal((R, d)), "bf16")
+    wg = _enc(rng.standard_normal((E, d)) * 0.02, "bf16")
+    dl = (rng.standard_normal((T, E)) * 10.0 ** rng.uniform(-6, 0, (T, E))).astype(np.float32)
+    buf = torch.zeros(T * E + shift, dtype=torch.float32, device=dev())
+    t_dl = buf[shift:].view(T, E)
+    t_dl.copy_(torch.from_numpy(dl))
+    dx = torch.full((T, d), float("nan"), dtype=torch.bfloat16, device=dev())
+    B.moe_dispatch_bwd(to_dev(dxd, "bf16"), torch.from_numpy(dest).to(dev()), E, t_dl,
+                       to_dev(wg, "bf16"), dx)
+    torch.cuda.synchronize()
+    ref = O.dispatch_bwd(_dec(dxd, "bf16"), dest.astype(np.int64), dl.astype(np.float64),
+                         _dec(wg, "bf16"), "bf16")
+    # both round once: where the fp32 sums fall on either side of a midpoint
+    # the results are neighbouring bf16 values, at most 2^-7 apart (relative)
+    assert_close(to_np(dx), ref, 2.0 ** -7, "dx")

@@ -373,3 +373,37 @@ def test_route_matches_separate_calls(T, d, E, k, dt, rule):
     torch.cuda.synchronize()
     for n in a:
         assert torch.equal(a[n], b[n]), n
+
+
+def _scan_picks(l, k):
+    """Top-k by a scan in index order that starts from the first untaken expert
+    and moves on strictly larger logits (a NaN is neither larger nor passed)."""
+    taken, out = set(), []
+    for _ in range(k):
+        best = None
+        for e in range(len(l)):
+            if e not in taken and (best is None or l[e] > l[best]):
+                best = e
+        taken.add(best)
+        out.append(best)
+    return out
+
+
+# eight lanes finish a token: experts in one and in several turns per lane,
+# non-finite logits (rows of w_g), ties across lanes
+@pytest.mark.parametrize("dt,d,E,k", [("f32", 64, 3, 2), ("f32", 40, 64, 8), ("bf16", 64, 20, 4),
+                                      ("bf16", 2056, 8, 3), ("bf16", 128, 33, 8)])
+def test_gate_picks_with_nonfinite_logits(dt, d, E, k):
+    rng = np.random.default_rng(E + k)
+    T = 75
+    x = rng.integers(-2, 3, (T, d)) / 4.0
+    wg = rng.integers(-2, 3, (E, d)) / 4.0
+    wg[E - 1] = wg[0]                                   # ties of the first and last expert
+    bias = np.zeros(E)
+    bias[1], bias[2] = np.nan, -np.inf
+    if E > 10:
+        bias[9], bias[10] = np.inf, np.nan
+    with np.errstate(invalid="ignore"):
+        logits, ids, w = _run_gate(x, wg, bias, k, 1, dt)
+    for t in range(T):
+        assert list(ids[t]) == _scan_picks(logits[t], k), t

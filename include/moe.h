@@ -185,6 +185,36 @@ moe_status moe_route(void* stream, moe_dtype dt, int T, int d, int E, int k,
                      size_t workspace_bytes);
 
 /*
+ * moe_layer_fwd - a whole layer forward in one call: moe_gate_topk (unless
+ * cached_ids gives the picks), moe_route, moe_expert_ffn_fwd over the kept
+ * rows, moe_combine (unless y is NULL).  The same results and errors as those
+ * calls; an argument error enqueues nothing.
+ *   w_g, bias, logits, ids   the gate's; unused with cached_ids
+ *   weights   [T,k] out of the gate; with cached_ids the combine weights, in
+ *             (may be NULL when y is NULL)
+ *   the other members as the arguments of those calls; rows = fill
+ */
+typedef struct moe_layer_fwd_args {
+  moe_dtype dtype;
+  moe_act act;
+  int T, d, E, k, f, renorm;
+  int dynamic, num, den, cap_min, row_align;
+  int64_t rows_alloc;
+  const void *x, *w_g;
+  const float* bias;
+  const void *w1, *w3, *w2;
+  const int32_t* cached_ids;
+  float *logits, *weights;
+  int32_t *ids, *capacity, *offsets, *counts, *fill, *dest_row, *src, *status;
+  void *x_disp, *h_save, *y_disp, *y;
+  void* route_ws;
+  size_t route_ws_bytes;
+  void* ffn_ws;
+  size_t ffn_ws_bytes;
+} moe_layer_fwd_args;
+moe_status moe_layer_fwd(void* stream, const moe_layer_fwd_args* args);
+
+/*
  * moe_dispatch_noalloc - moe_dispatch for callers that cannot allocate
  * device memory (code under HIP graph capture, tight serving loops,
  * harnesses that forbid hipMalloc): the same arguments, results and errors,

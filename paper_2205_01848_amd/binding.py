@@ -21,6 +21,20 @@ STATUS_BAD_ID, STATUS_DUP_ID, STATUS_REGION = 1, 2, 4
 
 _c_int, _c_i64, _c_size, _p = ctypes.c_int, ctypes.c_int64, ctypes.c_size_t, ctypes.c_void_p
 
+
+class LayerFwdArgs(ctypes.Structure):
+    """moe_layer_fwd_args."""
+    _fields_ = ([(n, _c_int) for n in ("dtype", "act", "T", "d", "E", "k", "f", "renorm",
+                                       "dynamic", "num", "den", "cap_min", "row_align")] +
+                [("rows_alloc", _c_i64)] +
+                [(n, _p) for n in ("x", "w_g", "bias", "w1", "w3", "w2", "cached_ids", "logits",
+                                   "weights", "ids", "capacity", "offsets", "counts", "fill",
+                                   "dest_row", "src", "status", "x_disp", "h_save", "y_disp",
+                                   "y")] +
+                [("route_ws", _p), ("route_ws_bytes", _c_size), ("ffn_ws", _p),
+                 ("ffn_ws_bytes", _c_size)])
+
+
 # name -> (restype, argtypes)
 SIGNATURES = {
     "moe_status_string": (ctypes.c_char_p, [_c_int]),
@@ -37,6 +51,7 @@ SIGNATURES = {
     "moe_route": (_c_int, [_p, _c_int, _c_int, _c_int, _c_int, _c_int, _p, _p, _c_int, _c_int,
                            _c_int, _c_int, _c_int, _c_i64, _p, _p, _p, _p, _p, _p, _p, _p, _p,
                            _c_size]),
+    "moe_layer_fwd": (_c_int, [_p, ctypes.POINTER(LayerFwdArgs)]),
     "moe_dispatch_noalloc": (_c_int, [_p, _c_int, _c_int, _c_int, _c_int, _c_int, _p, _p, _p,
                                       _p, _c_i64, _p, _p, _p, _p, _p, _p]),
     "moe_dispatch_noalloc_max_assignments": (_c_size, []),
@@ -241,6 +256,49 @@ def moe_route(x, ids, E, dynamic, num, den, cap_min, rows_alloc, capacity, offse
                            den, cap_min, row_align, rows_alloc, _ptr(capacity), _ptr(offsets),
                            _ptr(counts), _ptr(fill), _ptr(dest_row), _ptr(src), _ptr(x_disp),
                            _ptr(status), _ptr(ws), _nbytes(ws)), "moe_route")
+
+
+def moe_layer_fwd(x, w_g, bias, w1, w3, w2, cached_ids, weights, *, act, k, renorm, dynamic, num,
+                  den, rows_alloc, logits, ids, capacity, offsets, counts, fill, dest_row, src,
+                  status, x_disp, h_save, y_disp, y, route_ws, ffn_ws, cap_min=0, row_align=1):
+    """A whole layer forward in one call.  cached_ids None: the gate writes
+    logits, ids and weights; else weights are the combine weights (None with
+    y None: no combine)."""
+    T, d = x.shape
+    E, f, _ = w1.shape
+    dt, R = x.dtype, rows_alloc
+    a = LayerFwdArgs(_dt(x), act, T, d, E, k, f, int(renorm), int(dynamic), num, den, cap_min,
+                     row_align, R)
+    # every tensor the call reads or writes: (member, tensor, elements, type)
+    need = [("x", x, T * d, dt), ("w1", w1, E * f * d, dt), ("w2", w2, E * d * f, dt),
+            ("capacity", capacity, E, _I32), ("offsets", offsets, E + 1, _I32),
+            ("counts", counts, E, _I32), ("fill", fill, E, _I32),
+            ("dest_row", dest_row, T * k, _I32), ("src", src, R, _I32), ("status", status, 1, _I32),
+            ("x_disp", x_disp, R * d, dt), ("y_disp", y_disp, R * d, dt)]
+    if cached_ids is None:
+        need += [("w_g", w_g, E * d, dt), ("logits", logits, T * E, _F32), ("ids", ids, T * k, _I32),
+                 ("weights", weights, T * k, _F32)]
+        if bias is not None:
+            need.append(("bias", bias, E, _F32))
+    else:
+        need.append(("cached_ids", cached_ids, T * k, _I32))
+        if y is not None:
+            need.append(("weights", weights, T * k, _F32))
+    if w3 is not None or act == MOE_SWIGLU:
+        need.append(("w3", w3, E * f * d, dt))
+    if h_save is not None:
+        need.append(("h_save", h_save, h_save_planes(act) * R * f, dt))
+    if y is not None:
+        need.append(("y", y, T * d, dt))
+    for name, t, n, dtype in need:
+        if t is None or t.dtype != dtype or t.numel() < n or not t.is_cuda or not t.is_contiguous():
+            _need(t, n, name, dtype)
+            _ptr(t)
+        setattr(a, name, t.data_ptr())
+    for name, ws in (("route_ws", route_ws), ("ffn_ws", ffn_ws)):
+        setattr(a, name, _ptr(ws))
+        setattr(a, name + "_bytes", _nbytes(ws))
+    _check(lib().moe_layer_fwd(_stream(), ctypes.byref(a)), "moe_layer_fwd")
 
 
 def moe_dispatch_noalloc_max_assignments() -> int:

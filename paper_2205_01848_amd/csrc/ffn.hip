@@ -36,27 +36,17 @@
 #include <type_traits>
 
 #include "common.hpp"
+#include "ffn.hpp"
+#include "sched.hpp"
 #include "validate.hpp"
 
 namespace moe {
 namespace {
 
-constexpr int BM = 256;
-constexpr int BN = 256;
 constexpr int kRowBytes = 128;                    // one K tile of one operand row
 constexpr int kTileBytes = BM * kRowBytes;        // 32 KB
-
-// Tiles of the two-workgroups-per-CU kernels: kMidN columns, and 1 to
-// kMidMaxH units of kMidUnit rows, chosen per tile.
-constexpr int kMidUnit = 32;
-constexpr int kMidMaxH = 6;
-constexpr int kMidN = 128;
-constexpr int kMidDwH = 4;      // its units in the bf16 weight-gradient products
 constexpr int kGroupM = 4;      // M tiles per scheduling group
 constexpr int kXcds = 8;
-constexpr int kSplitFloor = 512;  // smallest K chunk of a split dW product
-constexpr int kKc = 64;           // split chunks are multiples of this many rows
-constexpr int kSplitItems = 256;  // work items the split aims at: one 256x256 tile per CU
 constexpr int64_t kMaxOperandRowBytes = (int64_t(1) << 23) - 64;  // 256 rows < 2^31 bytes
 // dx_disp up to this size is produced last in the backward (MI355X has a
 // 256 MB last-level cache; measured on a 268 MB dx_disp, T = 32768 tokens of
@@ -65,17 +55,6 @@ constexpr int64_t kMaxOperandRowBytes = (int64_t(1) << 23) - 64;  // 256 rows < 
 constexpr int64_t kDxLastBytes = int64_t(512) << 20;
 
 enum Act { ACT_RELU = 0, ACT_GELU = 1, ACT_SWIGLU = 2 };
-
-// Device-side schedule written by schedule_kernel.
-struct Sched {
-  int n_mtiles;    // (expert, m0) tiles of BM rows
-  int n_mid[2];    // tiles of the two-workgroups-per-CU kernel, per list
-  int n_segs;      // (expert, k range) segments of the dW products
-  int n_slots;     // partial-sum slots used
-  int rows[kMaxE];    // clamped rows per expert
-  int slot0[kMaxE];   // first partial slot of expert e (split experts)
-  int nsplit[kMaxE];  // K segments of expert e
-};
 
 // ---------------------------------------------------------------------------
 // activations (shared by forward epilogue, backward epilogue and transposes)
@@ -114,103 +93,12 @@ __device__ __forceinline__ float sigm(float h) { return rcp_fast(1.f + exp_fast(
 // ---------------------------------------------------------------------------
 // schedule
 // ---------------------------------------------------------------------------
-// Inclusive prefix sum over the 64 lanes of a wavefront.
-__device__ __forceinline__ int wave_incl_scan(int v) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int u = __shfl_up(v, o, 64);
-    if (lane >= o) v += u;
-  }
-  return v;
-}
-
-// Entry of a mid tile list: tile i of the n tiles an expert's `rows` rows are
-// spread over: x = expert | height in units << 8, y = first row.
-__device__ __forceinline__ int2 mid_tile(int rows, int n, int i, int e) {
-  const int units = (rows + kMidUnit - 1) / kMidUnit;
-  const int h = units / n, more = units - h * n;
-  return make_int2(e | ((h + (i < more ? 1 : 0)) << 8), (i * h + min(i, more)) * kMidUnit);
-}
-
-// Time (ns) of the two-workgroups-per-CU kernel on `tiles` tiles of at most h
-// units of rows and `steps` K steps each: rounds of `slots` tiles, each as
-// long as its K steps and its prologue and epilogue, which the other
-// workgroup of the CU overlaps in part.  Measured on 1024- to 8192-row
-// products (K = 512 .. 8192): a K step of both workgroups of a CU takes 0.87
-// us at h = 4 and 1.21 us at h = 6 with operands in the caches, about a tenth
-// more in a layer; a round of K = 512 at h = 4 takes 3.2 us more than its 8
-// steps.  A last round that leaves at least one of the two places of every
-// CU empty takes about 0.65 of a full one.  fp32 (K steps of 32): the
-// 16 h MFMAs of a step and wave, 64 cycles each, for both workgroups.
-struct StepCost {
-  int fixed, per_unit;   // ns per K step, ns per K step and unit of rows
-};
-constexpr StepCost kStep16 = {210, 185}, kStepF32 = {60, 890};
-__host__ __device__ inline int64_t mid_time(int64_t tiles, int h, int slots, int steps,
-                                            const StepCost& c) {
-  const int64_t full = tiles / slots, rem = tiles - full * slots;
-  return (20 * full + (rem == 0 ? 0 : 2 * rem <= slots ? 13 : 20)) *
-         (static_cast<int64_t>(steps) * (c.fixed + c.per_unit * h) + 3200) / 20;
-}
-
-// First index g < E whose inclusive prefix exceeds t.
-__device__ __forceinline__ int find_expert(const int* incl, int E, int t) {
-  int lo = 0, hi = E - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi) >> 1;
-    if (incl[mid] > t) hi = mid;
-    else lo = mid + 1;
-  }
-  return lo;
-}
-
-// Clamps every expert's rows to its region and to rows_alloc, and the tile
-// counts to the host bounds the workspace was sized for, so no later kernel
-// can index out of bounds.  Lane g of every wavefront is expert g; the
-// wavefronts number the experts' tiles and segments in expert order by prefix
-// sums, one list each, and then all threads write the lists, each entry
-// finding its expert by bisection.
-//  * mtile: 256-row tiles (wavefront kMidMaxH).  mtile_mid[i], i = 0, 1 (the
-//    products with N = f and with N = d columns): the tiles of the
-//    two-workgroups-per-CU kernel.  Its rounds on the persistent grid decide
-//    their height: for each largest height h (wavefront h - 1) the experts
-//    need ceil(units / h) tiles of at most h units, and the h whose rounds
-//    take the least time wins, so a few rows more than a whole number of
-//    tiles make tiles a little higher rather than one more round of tiles.
-//    An expert's units are spread evenly over its tiles.
-//  * the weight-gradient products (last wavefront) split an expert's rows
-//    into K segments only when few experts carry most rows: an expert's rows
-//    over the share of all 256x256 tile work that one of kSplitItems CUs
-//    would get, rounded, is its number of segments.  A segment costs the
-//    write and the read of its partial sums: 8 experts of 2048 rows, 1024 x
-//    2816 and 5632 x 1024 gradients, took 154 + 77 and 264 + 77 us (products
-//    + reductions) in two segments each, 123 and 212 us in one; 15,650 of
-//    16,384 rows in one of 64 experts, 4096 x 1024, 343 + 54 us in eight
-//    segments, 325 + 29 us in four.
-// Should a bound be exceeded (inconsistent offsets), one thread instead walks
-// the experts in order and cuts the lists where the bounds stop them.
-struct SchedArgs {
-  int E;
-  int64_t rows_alloc;
-  int max_mtiles, max_mid, max_segs, tmn_min, max_slots;
-  int nt[2], steps[2];   // column tiles and K steps of the products of the two mid lists
-  int slots_mid;         // workgroups of the mid kernel's persistent grid
-  StepCost cost;
-};
-constexpr int kSchedWaves = kMidMaxH + 2;
-
-__global__ __launch_bounds__(64 * kSchedWaves) void schedule_kernel(
-    const int32_t* __restrict__ offsets, const int32_t* __restrict__ rows, const SchedArgs A,
-    Sched* __restrict__ s, int2* __restrict__ mtile, int2* __restrict__ mtile_mid,
-    int4* __restrict__ seg) {
-  __shared__ int ti[kMaxE], si[kMaxE], mid_incl[kMidMaxH][kMaxE], rw[kMaxE], q0s[kMaxE];
-  __shared__ int64_t cost[2][kMidMaxH];
-  __shared__ int fit_rows, fit_segs;
-  const int E = A.E;
-  const int g = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
-  // rows of expert g, clamped to its region and to rows_alloc
+// Every expert's rows are clamped to its region and to rows_alloc, and the
+// tile counts to the host bounds the workspace was sized for, so no later
+// kernel can index out of bounds.
+__global__ __launch_bounds__(64 * kSchedTasks) void schedule_kernel(
+    const int32_t* __restrict__ offsets, const int32_t* __restrict__ rows, const SchedArgs A) {
+  const int g = threadIdx.x & 63, E = A.E;
   int m = 0;
   if (g < E) {
     const int64_t off = offsets[g];
@@ -220,141 +108,7 @@ __global__ __launch_bounds__(64 * kSchedWaves) void schedule_kernel(
     r = min(r, A.rows_alloc - off);
     m = static_cast<int>(max(r, int64_t(0)));
   }
-  if (wave < kMidMaxH) {
-    const int h = wave + 1;
-    const int units = (m + kMidUnit - 1) / kMidUnit;
-    const int n = (units + h - 1) / h;
-    int hm = n ? (units + n - 1) / n : 0;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) hm = max(hm, __shfl_xor(hm, o, 64));
-    const int incl = wave_incl_scan(n);
-    const int tot = __shfl(incl, 63, 64);
-    mid_incl[wave][g] = incl;
-    if (g < 2)
-      cost[g][wave] = mid_time(static_cast<int64_t>(tot) * A.nt[g], hm, A.slots_mid, A.steps[g], A.cost);
-  } else if (wave == kMidMaxH) {
-    ti[g] = wave_incl_scan((m + BM - 1) / BM);
-    rw[g] = m;
-    // the rows of consistent regions add up to at most rows_alloc; then no
-    // 32-bit sum here overflows
-    int64_t sum = m;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
-    if (g == 0) fit_rows = sum <= A.rows_alloc;
-  } else {
-    const int64_t kw = (static_cast<int64_t>(m) + kKc - 1) / kKc * kKc;
-    int64_t kwork = kw;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) kwork += __shfl_xor(kwork, o, 64);
-    const int64_t kc = (kwork * A.tmn_min + kSplitItems - 1) / kSplitItems;
-    const int kci = static_cast<int>(min(max(kc, static_cast<int64_t>(kSplitFloor)),
-                                         static_cast<int64_t>(1 << 29)));
-    const int q = m / kci;
-    const int nsp = g < E ? max(1, q + (2 * (m - q * kci) >= kci ? 1 : 0)) : 0;
-    const int segs_incl = wave_incl_scan(nsp);
-    const int slots_incl = wave_incl_scan(nsp > 1 ? nsp : 0);
-    const int slots_total = __shfl(slots_incl, 63, 64);
-    si[g] = segs_incl;
-    q0s[g] = nsp > 1 ? slots_incl - nsp : -1;
-    if (g == 63) {
-      fit_segs = segs_incl <= A.max_segs && slots_total <= A.max_slots;
-      s->n_slots = slots_total;
-    }
-  }
-  __syncthreads();
-  // the heights: the least time, the larger height on a tie
-  int best[2];
-#pragma unroll
-  for (int l = 0; l < 2; ++l) {
-    best[l] = 0;
-#pragma unroll
-    for (int h = 1; h < kMidMaxH; ++h)
-      if (cost[l][h] <= cost[l][best[l]]) best[l] = h;
-  }
-  const int* mi2[2] = {mid_incl[best[0]], mid_incl[best[1]]};
-  const bool fits = fit_rows && fit_segs && ti[E - 1] <= A.max_mtiles &&
-                    mi2[0][E - 1] <= A.max_mid && mi2[1][E - 1] <= A.max_mid;
-  const int max_mtiles = A.max_mtiles, max_mid = A.max_mid, max_segs = A.max_segs,
-            max_slots = A.max_slots, tmn_min = A.tmn_min;
-  const int64_t rows_alloc = A.rows_alloc;
-  const int tid = threadIdx.x, nthreads = 64 * kSchedWaves;
-  if (fits) {
-    if (tid < E) {
-      s->rows[tid] = rw[tid];
-      s->nsplit[tid] = si[tid] - (tid ? si[tid - 1] : 0);
-      s->slot0[tid] = q0s[tid];
-    }
-    if (tid == 0) {
-      s->n_mtiles = ti[E - 1];
-      s->n_mid[0] = mi2[0][E - 1];
-      s->n_mid[1] = mi2[1][E - 1];
-      s->n_segs = si[E - 1];
-    }
-    for (int t = tid; t < ti[E - 1]; t += nthreads) {
-      const int e = find_expert(ti, E, t);
-      mtile[t] = make_int2(e, (t - (e ? ti[e - 1] : 0)) * BM);
-    }
-#pragma unroll
-    for (int l = 0; l < 2; ++l)
-      for (int t = tid; t < mi2[l][E - 1]; t += nthreads) {
-        const int e = find_expert(mi2[l], E, t);
-        const int first = e ? mi2[l][e - 1] : 0;
-        mtile_mid[l * max_mid + t] = mid_tile(rw[e], mi2[l][e] - first, t - first, e);
-      }
-    for (int t = tid; t < si[E - 1]; t += nthreads) {
-      const int e = find_expert(si, E, t);
-      const int first = e ? si[e - 1] : 0, n = si[e] - first, i = t - first;
-      // equal segments, in whole K steps; the last ones may be short or empty
-      const int64_t len = ((rw[e] + n - 1) / n + kKc - 1) / kKc * kKc;
-      const int64_t me = rw[e];
-      seg[t] = make_int4(e, static_cast<int>(min(i * len, me)),
-                         n > 1 ? static_cast<int>(min((i + 1) * len, me)) : rw[e],
-                         n > 1 ? q0s[e] + i : -1);
-    }
-    return;
-  }
-  if (tid != 0) return;
-  int nm = 0, nmid = 0;
-  int64_t kwork_c = 0;
-  for (int e = 0; e < E; ++e) {
-    const int64_t off = offsets[e];
-    int64_t me = rows[e];
-    if (off < 0 || off >= rows_alloc) me = 0;
-    me = min(me, static_cast<int64_t>(offsets[e + 1]) - off);
-    me = min(me, rows_alloc - off);
-    me = max(me, int64_t(0));
-    me = min(me, static_cast<int64_t>(max_mtiles - nm) * BM);
-    me = min(me, static_cast<int64_t>(max_mid - nmid) * kMidMaxH * kMidUnit);
-    const int mi = static_cast<int>(me);
-    s->rows[e] = mi;
-    for (int m0 = 0; m0 < mi; m0 += BM) mtile[nm++] = make_int2(e, m0);
-    const int n = (mi + kMidMaxH * kMidUnit - 1) / (kMidMaxH * kMidUnit);
-    for (int i = 0; i < n; ++i, ++nmid)
-      mtile_mid[nmid] = mtile_mid[max_mid + nmid] = mid_tile(mi, n, i, e);
-    kwork_c += (mi + kKc - 1) / kKc * kKc;
-  }
-  s->n_mtiles = nm;
-  s->n_mid[0] = s->n_mid[1] = nmid;
-  int64_t kcc = (kwork_c * tmn_min + kSplitItems - 1) / kSplitItems;
-  kcc = (kcc + kKc - 1) / kKc * kKc;
-  kcc = max(kcc, static_cast<int64_t>(kSplitFloor));
-  int ns = 0, slots = 0;
-  for (int e = 0; e < E; ++e) {
-    const int kp = s->rows[e];
-    int ne = kp > kcc ? static_cast<int>((kp + kcc - 1) / kcc) : 1;
-    if (ne > 1 && (slots + ne > max_slots || ns + ne > max_segs)) ne = 1;
-    if (ns + ne > max_segs) ne = 0;
-    s->nsplit[e] = ne;
-    s->slot0[e] = ne > 1 ? slots : -1;
-    for (int i = 0; i < ne; ++i) {
-      const int k0 = static_cast<int>(min(static_cast<int64_t>(i) * kcc, static_cast<int64_t>(kp)));
-      const int k1 = static_cast<int>(min(static_cast<int64_t>(i + 1) * kcc, static_cast<int64_t>(kp)));
-      seg[ns++] = make_int4(e, ne > 1 ? k0 : 0, ne > 1 ? k1 : kp, ne > 1 ? slots + i : -1);
-    }
-    if (ne > 1) slots += ne;
-  }
-  s->n_segs = ns;
-  s->n_slots = slots;
+  build_schedule<kSchedTasks>(m, A);
 }
 
 // ---------------------------------------------------------------------------
@@ -1858,18 +1612,20 @@ bool make_plan(moe_dtype dt, moe_act act, int E, int d, int f, int64_t rows_allo
 
 // nt0, nt1: column tiles (of kMidN columns) of the call's products with N = f
 // (K = d) and with N = d (K = k1), for the heights of the two mid tile lists.
-moe_status launch_schedule(hipStream_t s, const FfnPlan& pl, const int32_t* offsets,
-                           const int32_t* rows, int nt0, int nt1, int k1, char* ws) {
+SchedArgs sched_args(const FfnPlan& pl, int nt0, int nt1, int k1, char* ws) {
   const bool f32 = pl.es == 4;
   const int ks = f32 ? kF32Step : 64;
+  return {pl.E, pl.rows_alloc, pl.max_mtiles, pl.max_mid, pl.max_segs, pl.tmn_min, pl.max_slots,
+          {nt0, nt1}, {cdiv(pl.d, ks), cdiv(k1, ks)}, 2 * persistent_grid(),
+          f32 ? kStepF32 : kStep16, reinterpret_cast<Sched*>(ws + pl.o_sched),
+          reinterpret_cast<int2*>(ws + pl.o_mtile), reinterpret_cast<int2*>(ws + pl.o_mid),
+          reinterpret_cast<int4*>(ws + pl.o_seg)};
+}
+
+moe_status launch_schedule(hipStream_t s, const SchedArgs& a, const int32_t* offsets,
+                           const int32_t* rows) {
   MOE_TIMED("ffn_schedule", s);
-  const SchedArgs a = {pl.E, pl.rows_alloc, pl.max_mtiles, pl.max_mid, pl.max_segs, pl.tmn_min,
-                       pl.max_slots, {nt0, nt1}, {cdiv(pl.d, ks), cdiv(k1, ks)},
-                       2 * persistent_grid(), f32 ? kStepF32 : kStep16};
-  schedule_kernel<<<1, 64 * kSchedWaves, 0, s>>>(
-      offsets, rows, a, reinterpret_cast<Sched*>(ws + pl.o_sched),
-      reinterpret_cast<int2*>(ws + pl.o_mtile), reinterpret_cast<int2*>(ws + pl.o_mid),
-      reinterpret_cast<int4*>(ws + pl.o_seg));
+  schedule_kernel<<<1, 64 * kSchedTasks, 0, s>>>(offsets, rows, a);
   MOE_LAUNCH_CHECK();
   return MOE_OK;
 }
@@ -2053,26 +1809,43 @@ extern "C" moe_status moe_set_dx_weight_copy(int mode) {
   return MOE_OK;
 }
 
-extern "C" moe_status moe_expert_ffn_fwd(void* stream, moe_dtype dt, moe_act act, int E, int d,
-                                         int f, const int32_t* offsets, const int32_t* rows,
-                                         int64_t rows_alloc, const void* x_disp, const void* w1,
-                                         const void* w3, const void* w2, void* h_save,
-                                         void* y_disp, void* workspace, size_t workspace_bytes) {
+namespace moe {
+
+moe_status ffn_fwd_check(const FfnFwd& a, size_t workspace_bytes) {
   FfnPlan pl;
-  if (!make_plan(dt, act, E, d, f, rows_alloc, pl)) return MOE_EINVAL;
-  if (!offsets || !rows || !w1 || !w2) return MOE_EINVAL;
-  if (act == MOE_SWIGLU && !w3) return MOE_EINVAL;
-  if (rows_alloc > 0 && (!x_disp || !y_disp)) return MOE_EINVAL;
-  if (!aligned16(w1) || !aligned16(w2) || (w3 && !aligned16(w3)) ||
-      (x_disp && !aligned16(x_disp)) || (y_disp && !aligned16(y_disp)) ||
-      (h_save && !aligned16(h_save)))
+  if (!make_plan(a.dt, a.act, a.E, a.d, a.f, a.rows_alloc, pl)) return MOE_EINVAL;
+  if (!a.offsets || !a.rows || !a.w1 || !a.w2) return MOE_EINVAL;
+  if (a.act == MOE_SWIGLU && !a.w3) return MOE_EINVAL;
+  if (a.rows_alloc > 0 && (!a.x_disp || !a.y_disp)) return MOE_EINVAL;
+  if (!aligned16(a.w1) || !aligned16(a.w2) || (a.w3 && !aligned16(a.w3)) ||
+      (a.x_disp && !aligned16(a.x_disp)) || (a.y_disp && !aligned16(a.y_disp)) ||
+      (a.h_save && !aligned16(a.h_save)))
     return MOE_EINVAL;
-  if (rows_alloc == 0) return MOE_OK;
-  if (!workspace || workspace_bytes < pl.total_fwd || !aligned16(workspace)) return MOE_EWORKSPACE;
-  hipStream_t s = static_cast<hipStream_t>(stream);
-  char* ws = static_cast<char*>(workspace);
-  MOE_TRY(launch_schedule(s, pl, offsets, rows, cdiv(f, act == MOE_SWIGLU ? kMidN / 2 : kMidN),
-                          cdiv(d, kMidN), f, ws));
+  if (a.rows_alloc == 0) return MOE_OK;
+  if (!a.workspace || workspace_bytes < pl.total_fwd || !aligned16(a.workspace)) return MOE_EWORKSPACE;
+  return MOE_OK;
+}
+
+SchedArgs ffn_fwd_sched(const FfnFwd& a) {
+  FfnPlan pl;
+  make_plan(a.dt, a.act, a.E, a.d, a.f, a.rows_alloc, pl);
+  return sched_args(pl, cdiv(a.f, a.act == MOE_SWIGLU ? kMidN / 2 : kMidN), cdiv(a.d, kMidN), a.f,
+                    static_cast<char*>(a.workspace));
+}
+
+moe_status ffn_fwd_launch(hipStream_t s, const FfnFwd& a, bool scheduled) {
+  if (a.rows_alloc == 0) return MOE_OK;
+  FfnPlan pl;
+  make_plan(a.dt, a.act, a.E, a.d, a.f, a.rows_alloc, pl);
+  if (!scheduled) MOE_TRY(launch_schedule(s, ffn_fwd_sched(a), a.offsets, a.rows));
+  char* ws = static_cast<char*>(a.workspace);
+  const moe_dtype dt = a.dt;
+  const moe_act act = a.act;
+  const int d = a.d, f = a.f;
+  const int32_t* offsets = a.offsets;
+  const int64_t rows_alloc = a.rows_alloc;
+  const void *x_disp = a.x_disp, *w1 = a.w1, *w3 = a.w3, *w2 = a.w2;
+  void *h_save = a.h_save, *y_disp = a.y_disp;
   const int64_t es = static_cast<int64_t>(pl.es);
   const int64_t plane = rows_alloc * f * es;   // one [rows_alloc, f] plane of h_save
   const bool sw = act == MOE_SWIGLU;
@@ -2113,6 +1886,19 @@ extern "C" moe_status moe_expert_ffn_fwd(void* stream, moe_dtype dt, moe_act act
   return MOE_OK;
 }
 
+}  // namespace moe
+
+extern "C" moe_status moe_expert_ffn_fwd(void* stream, moe_dtype dt, moe_act act, int E, int d,
+                                         int f, const int32_t* offsets, const int32_t* rows,
+                                         int64_t rows_alloc, const void* x_disp, const void* w1,
+                                         const void* w3, const void* w2, void* h_save,
+                                         void* y_disp, void* workspace, size_t workspace_bytes) {
+  const FfnFwd a = {dt, act, E, d, f, offsets, rows, rows_alloc, x_disp, w1, w3, w2, h_save,
+                    y_disp, workspace};
+  MOE_TRY(ffn_fwd_check(a, workspace_bytes));
+  return ffn_fwd_launch(static_cast<hipStream_t>(stream), a, false);
+}
+
 extern "C" moe_status moe_expert_ffn_bwd(void* stream, moe_dtype dt, moe_act act, int E, int d,
                                          int f, const int32_t* offsets, const int32_t* rows,
                                          int64_t rows_alloc, const void* x_disp,
@@ -2133,7 +1919,7 @@ extern "C" moe_status moe_expert_ffn_bwd(void* stream, moe_dtype dt, moe_act act
   if (!workspace || workspace_bytes < pl.total_bwd || !aligned16(workspace)) return MOE_EWORKSPACE;
   hipStream_t s = static_cast<hipStream_t>(stream);
   char* ws = static_cast<char*>(workspace);
-  MOE_TRY(launch_schedule(s, pl, offsets, rows, cdiv(f, kMidN), cdiv(d, kMidN), pl.F, ws));
+  MOE_TRY(launch_schedule(s, sched_args(pl, cdiv(f, kMidN), cdiv(d, kMidN), pl.F, ws), offsets, rows));
   const int64_t es = static_cast<int64_t>(pl.es);
   const bool sw = act == MOE_SWIGLU;
   const int F = pl.F;

@@ -18,6 +18,8 @@
 #include <type_traits>
 
 #include "common.hpp"
+#include "route.hpp"
+#include "sched.hpp"
 #include "validate.hpp"
 
 namespace moe {
@@ -66,12 +68,6 @@ __global__ __launch_bounds__(256) void count_kernel(const int32_t* __restrict__ 
   if (threadIdx.x < E && h[threadIdx.x]) atomicAdd(&counts[threadIdx.x], h[threadIdx.x]);
 }
 
-// The capacity rule of a call: Eq. 4 (num / den = alpha) or, when dynamic,
-// ceil(num / den * count), in exact 64-bit integer arithmetic, clamped to
-// [cap_min, T]; regions start at multiples of align rows.
-struct CapRule {
-  int dynamic, num, den, cap_min, align;
-};
 __device__ __forceinline__ int capacity_of(const CapRule& c, int T, int k, int E, int count) {
   int64_t v;
   if (c.dynamic) {
@@ -431,7 +427,9 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(
 // wavefront per choice, and copies their rows.  Up to kTinyAssign
 // assignments every workgroup counts the ids itself instead of reading
 // histograms, and a workgroup takes four tokens.  The first rows are loaded
-// before the routing they do not depend on.
+// before the routing they do not depend on.  One workgroup more, if asked,
+// derives the fills as the others do and builds the expert products' schedule
+// from them, which saves that kernel's launch.
 constexpr int kTinyAssign = 2048;     // 8 ids per thread
 constexpr int kMaxHist = 16384;       // histogram entries every workgroup reads (64 KB)
 constexpr int kMaxPairs = kMaxK * kMaxE;
@@ -482,6 +480,7 @@ struct RouteArgs {
   int32_t *capacity, *offsets, *counts, *fill, *dest_row, *src;
   uint4* x_disp;
   int32_t* status;
+  SchedArgs sched;       // built by workgroup nchunk, where the grid has it
 };
 
 template <int CT>
@@ -505,7 +504,8 @@ __global__ __launch_bounds__(256) void route_fused_kernel(const RouteArgs a) {
         if (v + 64 * w < a.nvec)
           val[u][w] = a.x[static_cast<size_t>(min(first + 4 * u, a.T - 1)) * a.nvec + v + 64 * w];
   };
-  load(t0 + wave, lane);
+  const bool scheduler = chunk == a.nchunk;   // has no tokens
+  if (!scheduler) load(t0 + wave, lane);
   for (int i = tid; i < P; i += 256) tot[i] = bef[i] = 0;
   for (int i = tid; i < CT * kMaxK; i += 256) (&dst[0][0])[i] = -1;
   __syncthreads();
@@ -573,6 +573,10 @@ __global__ __launch_bounds__(256) void route_fused_kernel(const RouteArgs a) {
     }
   }
   __syncthreads();
+  if (scheduler) {
+    build_schedule<4>(lane < E ? fillv[lane] : 0, a.sched);
+    return;
+  }
   // ranks: one wavefront per choice, lane = token
   for (int j = wave; j < k; j += 4) {
     const int t = t0 + lane;
@@ -595,7 +599,7 @@ __global__ __launch_bounds__(256) void route_fused_kernel(const RouteArgs a) {
   // rows that hold no assignment: past the kept ones of their region, or past
   // the last region
   for (int64_t r = static_cast<int64_t>(chunk) * 256 + tid; r < a.rows_alloc;
-       r += static_cast<int64_t>(gridDim.x) * 256) {
+       r += static_cast<int64_t>(a.nchunk) * 256) {
     int lo = 0, hi = E - 1;   // last expert whose region starts at or before r
     while (lo < hi) {
       const int mid = (lo + hi + 1) >> 1;
@@ -1202,42 +1206,61 @@ extern "C" size_t moe_route_workspace_bytes(int T, int E, int k) {
              : general;
 }
 
+namespace moe {
+
+moe_status route_check(const Route& a, size_t workspace_bytes) {
+  const moe_status st = dispatch_args_ok(a.dt, a.T, a.d, a.E, a.k, a.x, a.ids, a.capacity,
+                                         a.offsets, a.rows_alloc, a.counts, a.fill, a.dest_row,
+                                         a.src, a.x_disp, a.status);
+  if (st != MOE_OK) return st;
+  if (!cap_rule_ok(a.T, a.E, a.k, a.rule.num, a.rule.den, a.rule.cap_min, a.rule.align))
+    return MOE_EINVAL;
+  return !a.workspace || workspace_bytes < moe_route_workspace_bytes(a.T, a.E, a.k) ? MOE_EWORKSPACE
+                                                                                     : MOE_OK;
+}
+
+moe_status route_launch(hipStream_t s, const Route& r, const SchedArgs* sched, bool* scheduled) {
+  const int T = r.T, E = r.E, k = r.k;
+  const int ct = route_chunk_tokens(T, E, k);
+  if (scheduled) *scheduled = sched && ct;
+  if (ct == 0)
+    return dispatch_launch(s, r.dt, T, r.d, E, k, r.x, r.ids, &r.rule, r.capacity, r.offsets,
+                           r.rows_alloc, r.counts, r.fill, r.dest_row, r.src, r.x_disp, r.status,
+                           r.workspace);
+  const bool tiny = T * k <= kTinyAssign;
+  const int nchunk = nblocks(T, tiny ? 4 : ct);
+  int32_t* hist = nullptr;
+  if (!tiny) {
+    hist = static_cast<int32_t*>(r.workspace);
+    MOE_TIMED("route_hist", s);
+    (ct == 32 ? route_chunk_hist_kernel<32> : route_chunk_hist_kernel<64>)<<<
+        nblocks(nchunk, 4), 256, 0, s>>>(r.ids, T, E, k, nchunk, hist, r.status);
+    MOE_LAUNCH_CHECK();
+  }
+  const RouteArgs a = {static_cast<const uint4*>(r.x), r.ids, hist, T, E, k,
+                       static_cast<int>(static_cast<int64_t>(r.d) * esize(r.dt) / 16), nchunk,
+                       r.rule, r.rows_alloc, r.capacity, r.offsets, r.counts, r.fill, r.dest_row,
+                       r.src, static_cast<uint4*>(r.x_disp), r.status,
+                       sched ? *sched : SchedArgs{}};
+  MOE_TIMED("dispatch_gather", s);
+  (tiny ? route_fused_kernel<4> : ct == 32 ? route_fused_kernel<32> : route_fused_kernel<64>)<<<
+      nchunk + (sched ? 1 : 0), 256, 0, s>>>(a);
+  MOE_LAUNCH_CHECK();
+  return MOE_OK;
+}
+
+}  // namespace moe
+
 extern "C" moe_status moe_route(void* stream, moe_dtype dt, int T, int d, int E, int k,
                                 const void* x, const int32_t* ids, int dynamic, int num, int den,
                                 int cap_min, int row_align, int64_t rows_alloc, int32_t* capacity,
                                 int32_t* offsets, int32_t* counts, int32_t* fill,
                                 int32_t* dest_row, int32_t* src, void* x_disp, int32_t* status,
                                 void* workspace, size_t workspace_bytes) {
-  const moe_status st = dispatch_args_ok(dt, T, d, E, k, x, ids, capacity, offsets, rows_alloc,
-                                         counts, fill, dest_row, src, x_disp, status);
-  if (st != MOE_OK) return st;
-  if (!cap_rule_ok(T, E, k, num, den, cap_min, row_align)) return MOE_EINVAL;
-  if (!workspace || workspace_bytes < moe_route_workspace_bytes(T, E, k)) return MOE_EWORKSPACE;
-  hipStream_t s = static_cast<hipStream_t>(stream);
-  const CapRule rule = {dynamic != 0, num, den, cap_min, row_align};
-  const int ct = route_chunk_tokens(T, E, k);
-  if (ct == 0)
-    return dispatch_launch(s, dt, T, d, E, k, x, ids, &rule, capacity, offsets, rows_alloc, counts,
-                           fill, dest_row, src, x_disp, status, workspace);
-  const bool tiny = T * k <= kTinyAssign;
-  const int nchunk = nblocks(T, tiny ? 4 : ct);
-  int32_t* hist = nullptr;
-  if (!tiny) {
-    hist = static_cast<int32_t*>(workspace);
-    MOE_TIMED("route_hist", s);
-    (ct == 32 ? route_chunk_hist_kernel<32> : route_chunk_hist_kernel<64>)<<<
-        nblocks(nchunk, 4), 256, 0, s>>>(ids, T, E, k, nchunk, hist, status);
-    MOE_LAUNCH_CHECK();
-  }
-  const RouteArgs a = {static_cast<const uint4*>(x), ids, hist, T, E, k,
-                       static_cast<int>(static_cast<int64_t>(d) * esize(dt) / 16), nchunk, rule,
-                       rows_alloc, capacity, offsets, counts, fill, dest_row, src,
-                       static_cast<uint4*>(x_disp), status};
-  MOE_TIMED("dispatch_gather", s);
-  (tiny ? route_fused_kernel<4> : ct == 32 ? route_fused_kernel<32> : route_fused_kernel<64>)<<<
-      nchunk, 256, 0, s>>>(a);
-  MOE_LAUNCH_CHECK();
-  return MOE_OK;
+  const Route r = {dt, T, d, E, k, x, ids, {dynamic != 0, num, den, cap_min, row_align}, rows_alloc,
+                   capacity, offsets, counts, fill, dest_row, src, x_disp, status, workspace};
+  const moe_status st = route_check(r, workspace_bytes);
+  return st != MOE_OK ? st : route_launch(static_cast<hipStream_t>(stream), r, nullptr, nullptr);
 }
 
 // ---- allocation-free dispatch ------------------------------------------------

@@ -203,6 +203,28 @@ class MoELayer:
             B.moe_dispatch_bwd(self.dx_disp, self.dest_row, self.E, None, None, self.dx)
 
     # ---- whole layer ---------------------------------------------------------
+    def _fusable(self, x, w1, capacity, rows, counts_from_batch=True, ids=None, w_g=None):
+        """Whether the forward is one library call: capacities from this
+        batch, kept rows, and tensors of the layer's own shapes (the separate
+        calls take each shape from the tensors they get)."""
+        return (rows == "fill" and capacity[0] != "policy" and
+                (capacity[0] == "static" or counts_from_batch) and
+                x.shape == (self.T, self.d) and w1.shape == (self.E, self.f, self.d) and
+                (w_g is None or w_g.shape == (self.E, self.d)) and
+                (ids is None or ids.shape == (self.T, self.k)))
+
+    def _fused(self, x, w1, w3, w2, ids, weights, y, *, capacity, renorm=0, w_g=None, bias=None):
+        """The forward in one library call: gate (ids None) or cached ids,
+        count, capacity, dispatch, FFN over the kept rows, combine (y given)."""
+        kind, num, den = capacity
+        B.moe_layer_fwd(x, w_g, bias, w1, w3, w2, ids, weights, act=self.act, k=self.k,
+                        renorm=renorm, dynamic=kind != "static", num=num, den=den,
+                        rows_alloc=self.rows_alloc, logits=self.logits, ids=self.ids,
+                        capacity=self.capacity, offsets=self.offsets, counts=self.counts,
+                        fill=self.fill, dest_row=self.dest_row, src=self.src, status=self.status,
+                        x_disp=self.x_disp, h_save=self.h_save, y_disp=self.y_disp, y=y,
+                        route_ws=self.ws_dispatch, ffn_ws=self.ws_fwd, row_align=self.row_align)
+
     def _capacity_dispatch(self, x, capacity, ids, counts_from_batch):
         kind, num, den = capacity
         if kind == "policy":
@@ -217,7 +239,7 @@ class MoELayer:
                 capacity=("dynamic", 1, 1), counts_from_batch=True, rows="fill",
                 balance: Optional[float] = None):
         """gate (or cached ids) -> [count ->] capacity -> dispatch -> FFN -> combine
-        (count, capacity and dispatch in one library call where they follow each other).
+        (one library call unless the capacities or the rows come from elsewhere).
 
         capacity = ("static", num, den) | ("dynamic", num, den) | ("policy",
         1, 1); a dynamic rule uses this batch's counts when counts_from_batch,
@@ -226,6 +248,13 @@ class MoELayer:
         balance = lambda adds the Eq. 3 balance term (self.balance_loss) and
         its gradient to the gate backward."""
         self._balance_on = False
+        if ((ids is None) == (w_g is not None) and
+                self._fusable(x, w1, capacity, rows, counts_from_batch, ids, w_g)):
+            self._fused(x, w1, w3, w2, ids, self.weights if ids is None or weights is None
+                        else weights, self.y, capacity=capacity, renorm=renorm, w_g=w_g, bias=bias)
+            if balance is not None:
+                self.balance(balance)
+            return self.y
         if ids is None:
             self.gate(x, w_g, bias, renorm)
             ids, weights = self.ids, self.weights
@@ -266,8 +295,11 @@ class MoELayer:
             B.moe_cache_update(self.ids, cached, cache_out, unchanged)
             gate_done = torch.cuda.Event()
             gate_done.record(gs)
-        self._capacity_dispatch(x, capacity, cached, True)
-        self.ffn_fwd(w1, w3, w2, rows=rows)
+        if self._fusable(x, w1, capacity, rows, ids=cached):
+            self._fused(x, w1, w3, w2, cached, None, None, capacity=capacity)
+        else:
+            self._capacity_dispatch(x, capacity, cached, True)
+            self.ffn_fwd(w1, w3, w2, rows=rows)
         main.wait_event(gate_done)
         self.combine(self.cached_weights)
         return self.y

@@ -209,3 +209,37 @@ def test_policy_rejects_bad_arguments():
     assert not h.value
     assert L.moe_policy_begin(None, None, FAKE, FAKE, None, None) == EINVAL
     assert L.moe_policy_end(None, None, FAKE) == EINVAL
+
+
+def test_layer_fwd_argument_errors():
+    """Every refusal of the calls moe_layer_fwd stands for, before anything is
+    enqueued (no GPU here: a launch would return MOE_EHIP)."""
+    import ctypes
+    L = B.lib()
+    R = 40
+
+    def args(**kw):
+        a = B.LayerFwdArgs(B.MOE_BF16, B.MOE_SWIGLU, 10, 64, 4, 2, 128, 1, 1, 11, 10, 0, 1, R)
+        for n, t in B.LayerFwdArgs._fields_:
+            if t is ctypes.c_void_p:
+                setattr(a, n, FAKE)
+        a.cached_ids = None
+        a.route_ws_bytes = L.moe_route_workspace_bytes(10, 4, 2)
+        a.ffn_ws_bytes = L.moe_ffn_fwd_workspace_bytes(B.MOE_BF16, B.MOE_SWIGLU, 4, 64, 128, R)
+        for n, v in kw.items():
+            setattr(a, n, v)
+        return L.moe_layer_fwd(None, ctypes.byref(a))
+
+    assert L.moe_layer_fwd(None, None) == EINVAL
+    for bad in (dict(dtype=7), dict(act=9), dict(E=65), dict(k=5), dict(d=60), dict(f=12),
+                dict(T=-1), dict(num=0), dict(den=0), dict(cap_min=-1), dict(row_align=0),
+                dict(rows_alloc=-1), dict(x=None), dict(w_g=None), dict(w1=None), dict(w3=None),
+                dict(w2=None), dict(logits=None), dict(weights=None), dict(ids=None),
+                dict(capacity=None), dict(offsets=None), dict(counts=None), dict(fill=None),
+                dict(dest_row=None), dict(src=None), dict(status=None), dict(x_disp=None),
+                dict(y_disp=None), dict(x=FAKE.value + 8), dict(w2=FAKE.value + 2), dict(y=FAKE.value + 8),
+                dict(h_save=FAKE.value + 8), dict(cached_ids=FAKE, weights=None)):
+        assert args(**bad) == EINVAL, bad
+    for short in (dict(route_ws_bytes=16), dict(ffn_ws_bytes=16), dict(route_ws=None),
+                  dict(ffn_ws=None)):
+        assert args(**short) == EWORKSPACE, short

@@ -231,3 +231,57 @@ def test_padded_static_baseline_weight_gradients_equal_method(act):
     rt = RTOL["bf16"]
     assert_close(to_np(out["capacity"]["dw1"]), bw["dW1"], rt, "dW1")
     assert_close(to_np(out["capacity"]["dw2"]), bw["dW2"], rt, "dW2")
+
+
+# moe_layer_fwd against the separate calls, bit for bit: schedule built inside
+# the one- and two-launch routing and by its own kernel, gate and cached picks
+# (some invalid), with and without the combine and the saved planes
+@pytest.mark.parametrize("T,d,E,k,f,act,dt", [
+    (5, 64, 4, 2, 128, "swiglu", "bf16"),
+    (300, 136, 13, 3, 264, "gelu_tanh", "bf16"),
+    (900, 72, 33, 2, 96, "relu", "f32"),
+    (3000, 64, 64, 8, 64, "swiglu", "bf16"),      # general routing, own schedule kernel
+])
+@pytest.mark.parametrize("cached", [False, True])
+@pytest.mark.parametrize("rule", [("static", 5, 4), ("dynamic", 11, 10)])
+def test_layer_fwd_matches_separate_calls(T, d, E, k, f, act, dt, cached, rule):
+    g = torch.Generator(device="cuda").manual_seed(T + E)
+    td = torch.bfloat16 if dt == "bf16" else torch.float32
+    rand = lambda *s, std=1.0: (torch.randn(*s, device="cuda", generator=g) * std).to(td)
+    x, w_g, w1, w2 = rand(T, d), rand(E, d, std=0.1), rand(E, f, d, std=0.05), rand(E, d, f, std=0.05)
+    w3 = rand(E, f, d, std=0.05) if act == "swiglu" else None
+    bias = torch.randn(E, device="cuda", generator=g)
+    ids = cw = None
+    if cached:
+        ids = torch.rand(T, E, device="cuda", generator=g).topk(k, dim=1).indices.to(torch.int32)
+        ids[::11, 0] = E
+        cw = torch.rand(T, k, device="cuda", generator=g)
+    kind, num, den = rule
+    R = rows_alloc_for(kind, T, k, E, num, den)
+
+    def layer():
+        L = MoELayer(T, d, E, k, f, act, td, R, backward=True)
+        for n in ("x_disp", "y_disp", "y", "h_save"):
+            getattr(L, n).fill_(3.0)
+        return L
+
+    A, S = layer(), layer()
+    A.forward(x, w1, w3, w2, w_g=None if cached else w_g, bias=None if cached else bias, renorm=1,
+              ids=ids, weights=cw, capacity=rule)
+    if not cached:
+        S.gate(x, w_g, bias, 1)
+    picks, wts = (ids, cw) if cached else (S.ids, S.weights)
+    if kind == "static":
+        S.capacity_static(num, den)
+    else:
+        S.count(picks)
+        S.capacity_dynamic(num, den)
+    S.dispatch(x, picks)
+    S.ffn_fwd(w1, w3, w2)
+    S.combine(wts)
+    torch.cuda.synchronize()
+    names = ["counts", "capacity", "offsets", "fill", "dest_row", "src", "status", "x_disp",
+             "y_disp", "h_save", "y"] + ([] if cached else ["logits", "ids", "weights"])
+    for n in names:
+        a, b = getattr(A, n), getattr(S, n)
+        assert torch.equal(a, b), n

@@ -28,7 +28,7 @@ struct Sched {
   int n_slots;     // partial-sum slots used
   int rows[kMaxE];    // clamped rows per expert
   int slot0[kMaxE];   // first partial slot of expert e (split experts)
-  int nsplit[kMaxE];  // K segments of expert e
+  int nsplit[kMaxE];  // K segments of expert e (0: no rows, its gradients are zero)
 };
 
 // Inclusive prefix sum over the 64 lanes of a wavefront.
@@ -121,7 +121,8 @@ constexpr int kSchedTasks = kMidMaxH + 2;
 //    2816 and 5632 x 1024 gradients, took 154 + 77 and 264 + 77 us (products
 //    + reductions) in two segments each, 123 and 212 us in one; 15,650 of
 //    16,384 rows in one of 64 experts, 4096 x 1024, 343 + 54 us in eight
-//    segments, 325 + 29 us in four.
+//    segments, 325 + 29 us in four.  Experts without rows get no segment:
+//    split_reduce_kernel writes their zeros.
 // Should a list be longer than the workspace has room for (inconsistent
 // offsets), one thread walks the experts in order and cuts the lists there.
 template <int WAVES>
@@ -166,7 +167,7 @@ __device__ __forceinline__ void build_schedule(int m, const SchedArgs& A) {
       const int kci = static_cast<int>(min(max(kc, static_cast<int64_t>(kSplitFloor)),
                                            static_cast<int64_t>(1 << 29)));
       const int q = m / kci;
-      const int nsp = g < E ? max(1, q + (2 * (m - q * kci) >= kci ? 1 : 0)) : 0;
+      const int nsp = m > 0 ? max(1, q + (2 * (m - q * kci) >= kci ? 1 : 0)) : 0;
       const int segs_incl = wave_incl_scan(nsp);
       const int slots_incl = wave_incl_scan(nsp > 1 ? nsp : 0);
       const int slots_total = __shfl(slots_incl, 63, 64);
@@ -250,7 +251,7 @@ __device__ __forceinline__ void build_schedule(int m, const SchedArgs& A) {
   int ns = 0, slots = 0;
   for (int e = 0; e < E; ++e) {
     const int kp = s->rows[e];
-    int ne = kp > kcc ? static_cast<int>((kp + kcc - 1) / kcc) : 1;
+    int ne = kp > kcc ? static_cast<int>((kp + kcc - 1) / kcc) : (kp > 0 ? 1 : 0);
     if (ne > 1 && (slots + ne > A.max_slots || ns + ne > A.max_segs)) ne = 1;
     if (ns + ne > A.max_segs) ne = 0;
     s->nsplit[e] = ne;

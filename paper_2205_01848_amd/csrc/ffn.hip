@@ -1624,14 +1624,38 @@ bool make_plan(moe_dtype dt, moe_act act, int E, int d, int f, int64_t rows_allo
   return true;
 }
 
+// Cache lines per 128-byte row segment, in sixteenths, of rows `pitch` bytes
+// apart: 1 where every segment starts on a line, else 2 for all but those
+// that do.
+int lines16(int64_t pitch) {
+  const int64_t g = pitch & -pitch;   // largest power of two in the pitch
+  return g >= 128 ? 16 : 32 - static_cast<int>(g / 8);
+}
+
+// bf16 K step of the two-workgroups-per-CU kernel (both workgroups): A rows
+// pa bytes apart, B K-contiguous with rows pb apart or K-major (64 k-rows of
+// 256 bytes: 2 lines, or up to 3).
+StepCost step16(int64_t pa, int64_t pb, bool b_km) {
+  // 2 x 32 x lines16 / 16 lines a unit, 1000 / 640 ns a line
+  return {210, 185, b_km ? (pb % 128 ? 600 : 400) : 25 * lines16(pb), 100 * lines16(pa) / 16};
+}
+
+// And of the 256x256 kernel, ns.
+int big_step16(int64_t pa, int64_t pb, bool b_km) {
+  const int lines = 16 * lines16(pa) + (b_km ? (pb % 128 ? 320 : 256) : 16 * lines16(pb));
+  return std::max(1400, lines * 25 / 16);
+}
+
 // nt0, nt1: column tiles (of kMidN columns) of the call's products with N = f
-// (K = d) and with N = d (K = k1), for the heights of the two mid tile lists.
-SchedArgs sched_args(const FfnPlan& pl, int nt0, int nt1, int k1, char* ws) {
+// (K = d) and with N = d (K = k1), c0, c1: their K steps' times, for the
+// heights of the two mid tile lists.
+SchedArgs sched_args(const FfnPlan& pl, int nt0, int nt1, int k1, const StepCost& c0,
+                     const StepCost& c1, char* ws) {
   const bool f32 = pl.es == 4;
   const int ks = f32 ? kF32Step : 64;
   return {pl.E, pl.rows_alloc, pl.max_mtiles, pl.max_mid, pl.max_segs, pl.tmn_min, pl.max_slots,
           {nt0, nt1}, {cdiv(pl.d, ks), cdiv(k1, ks)}, 2 * persistent_grid(),
-          f32 ? kStepF32 : kStep16, reinterpret_cast<Sched*>(ws + pl.o_sched),
+          {f32 ? kStepF32 : c0, f32 ? kStepF32 : c1}, reinterpret_cast<Sched*>(ws + pl.o_sched),
           reinterpret_cast<int2*>(ws + pl.o_mtile), reinterpret_cast<int2*>(ws + pl.o_mid),
           reinterpret_cast<int4*>(ws + pl.o_seg)};
 }
@@ -1663,38 +1687,42 @@ int g_tile_mode = 0;
 // other's MFMAs, but read more operand bytes per flop.  The host knows N, K
 // and the row budget, not the per-expert rows, so it takes every expert to
 // hold rows_alloc / E rows and half a tile's raggedness, and compares the two
-// kernels' estimated times: rounds of 256x256 tiles of 1.4 us per K step
-// (1.2 where at most half the CUs have one) and 10 us of prologue and
-// epilogue, 13 with an activation, against the least mid_time over the
-// heights.  (Whole products, big against mid, us, same box: 16 experts of
-// 1024 +- 30 rows, 512 -> 2048 84 / 60, 2048 -> 512 61 / 45; 16 of 512 +- 20
-// rows, 1024 -> 4096 104 / 93, 4096 -> 1024 110 / 87; 32 of 2048, 2048 ->
-// 8192 1885 / 2089, 8192 -> 2048 1773 / 2105.)  Weight gradients (K not known
-// on the host) compare rounds, a round of 128x128 tiles taking 0.65 of one of
-// 256x256 tiles.
-bool use_mid_tiles(const FfnPlan& pl, moe_dtype dt, bool vark, bool gated, bool act, int N,
-                   int M_out, int K) {
+// kernels' estimated times: rounds of 256x256 tiles of 1.4 us per K step (1.2
+// where at most half the CUs have one; longer where it touches more cache
+// lines) and 10 us of prologue and epilogue, 13 with an activation, against
+// 6/5 of the least mid_time over the heights: that is how much further the
+// measured times of these tiles lie above the estimate, the most in long
+// products (50 experts of 393 rows, 1120 -> 2 x 6536: 850 / 1026 us).  Whole products, 256x256 against these
+// tiles, us, same box: 16 experts of 1024 +- 30 rows, 512 -> 2048 84 / 60, 2048
+// -> 512 61 / 45; 16 of 512 +- 20 rows, 1024 -> 4096 104 / 93, 4096 -> 1024 110 /
+// 87; 32 of 2048, 2048 -> 8192 1885 / 2089, 8192 -> 2048 1773 / 2105; 50 of 393
+// rows, 6536 -> 1120 (rows off 128-byte lines) 395 / 579.  Weight gradients (K
+// not known on the host) compare rounds, a round of 128x128 tiles taking 0.65
+// of one of 256x256 tiles.
+bool use_mid_tiles(const FfnPlan& pl, moe_dtype dt, bool vark, bool gated, bool act, bool b_km,
+                   const GemmParams& p) {
   if (dt == MOE_F32) return true;
   if (g_tile_mode == 1) return false;
   if (g_tile_mode == 2) return true;
   const int G = persistent_grid();
   if (vark) {
-    const int64_t big = static_cast<int64_t>(pl.E) * cdiv(M_out, BM) * cdiv(N, BN);
-    const int64_t mid = static_cast<int64_t>(pl.E) * cdiv(M_out, kMidDwH * kMidUnit) * cdiv(N, kMidN);
+    const int64_t big = static_cast<int64_t>(pl.E) * cdiv(p.M_out, BM) * cdiv(p.N, BN);
+    const int64_t mid = static_cast<int64_t>(pl.E) * cdiv(p.M_out, kMidDwH * kMidUnit) * cdiv(p.N, kMidN);
     return 13 * ((mid + 2 * G - 1) / (2 * G)) < 20 * ((big + G - 1) / G);
   }
-  const int steps = cdiv(K, 64);
+  const int steps = cdiv(p.K, 64);
   const int64_t per = cdiv(pl.rows_alloc, pl.E);
-  const int64_t big = pl.E * (2 * per + BM) / (2 * BM) * cdiv(N, gated ? BN / 2 : BN);
-  const int64_t t_big = (big + G - 1) / G * ((2 * big <= G ? 1200 : 1400) * static_cast<int64_t>(steps) +
-                                             (act ? 13000 : 10000));
+  const int64_t big = pl.E * (2 * per + BM) / (2 * BM) * cdiv(p.N, gated ? BN / 2 : BN);
+  const int step = 2 * big <= G ? 1200 : big_step16(p.lda, p.ldb, b_km);
+  const int64_t t_big = (big + G - 1) / G * (static_cast<int64_t>(step) * steps + (act ? 13000 : 10000));
+  const StepCost c = step16(p.lda, p.ldb, b_km);
   int64_t t_mid = 0;
   for (int h = 1; h <= kMidMaxH; ++h) {
     const int64_t n = (2 * per + kMidUnit + 2 * kMidUnit * h - 1) / (2 * kMidUnit * h);
-    const int64_t t = mid_time(n * pl.E * cdiv(N, gated ? kMidN / 2 : kMidN), h, 2 * G, steps, kStep16);
+    const int64_t t = mid_time(n * pl.E * cdiv(p.N, gated ? kMidN / 2 : kMidN), h, 2 * G, steps, c);
     if (h == 1 || t < t_mid) t_mid = t;
   }
-  return t_mid < t_big;
+  return 6 * t_mid < 5 * t_big;
 }
 
 // dX with a transposed copy of [W1; W3] (moe_set_dx_weight_copy: 0
@@ -1724,7 +1752,7 @@ template <int MODE, int PASS>
 moe_status launch_gemm(hipStream_t s, moe_dtype dt, const FfnPlan& pl, char* ws, GemmParams p) {
   constexpr bool VARK = MODE == M_DW, GATED = MODE == M_FWD1_SWIGLU;
   constexpr bool ACTIVE = MODE != M_STORE && MODE != M_DW;
-  const bool mid = use_mid_tiles(pl, dt, VARK, GATED, ACTIVE, p.N, p.M_out, VARK ? 0 : p.K);
+  const bool mid = use_mid_tiles(pl, dt, VARK, GATED, ACTIVE, b_layout(PASS) == L_KM, p);
   const int tn = mid ? kMidN : BN;
   p.ntiles = cdiv(p.N, GATED ? tn / 2 : tn);
   p.dw_h = kMidDwH;
@@ -1844,6 +1872,7 @@ SchedArgs ffn_fwd_sched(const FfnFwd& a) {
   FfnPlan pl;
   make_plan(a.dt, a.act, a.E, a.d, a.f, a.rows_alloc, pl);
   return sched_args(pl, cdiv(a.f, a.act == MOE_SWIGLU ? kMidN / 2 : kMidN), cdiv(a.d, kMidN), a.f,
+                    step16(a.d * 2ll, a.d * 2ll, false), step16(a.f * 2ll, a.f * 2ll, false),
                     static_cast<char*>(a.workspace));
 }
 
@@ -1933,7 +1962,9 @@ extern "C" moe_status moe_expert_ffn_bwd(void* stream, moe_dtype dt, moe_act act
   if (!workspace || workspace_bytes < pl.total_bwd || !aligned16(workspace)) return MOE_EWORKSPACE;
   hipStream_t s = static_cast<hipStream_t>(stream);
   char* ws = static_cast<char*>(workspace);
-  MOE_TRY(launch_schedule(s, sched_args(pl, cdiv(f, kMidN), cdiv(d, kMidN), pl.F, ws), offsets, rows));
+  MOE_TRY(launch_schedule(s, sched_args(pl, cdiv(f, kMidN), cdiv(d, kMidN), pl.F,
+                                        step16(d * 2ll, f * 2ll, true),
+                                        step16(pl.F * 2ll, d * 2ll, true), ws), offsets, rows));
   const int64_t es = static_cast<int64_t>(pl.es);
   const bool sw = act == MOE_SWIGLU;
   const int F = pl.F;

@@ -58,22 +58,30 @@ __device__ __forceinline__ int2 mid_tile(int rows, int n, int i, int e) {
 // Time (ns) of the two-workgroups-per-CU kernel on `tiles` tiles of at most h
 // units of rows and `steps` K steps each: rounds of `slots` tiles, each as
 // long as its K steps and its prologue and epilogue, which the other
-// workgroup of the CU overlaps in part.  Measured on 1024- to 8192-row
-// products (K = 512 .. 8192): a K step of both workgroups of a CU takes 0.87
-// us at h = 4 and 1.21 us at h = 6 with operands in the caches, about a tenth
-// more in a layer; a round of K = 512 at h = 4 takes 3.2 us more than its 8
-// steps.  A last round that leaves at least one of the two places of every
-// CU empty takes about 0.65 of a full one.  fp32 (K steps of 32): the
-// 16 h MFMAs of a step and wave, 64 cycles each, for both workgroups.
+// workgroup of the CU overlaps in part.  A K step takes the longer of
+//  * its MFMAs, operand reads and waits: 0.87 us at h = 4 and 1.21 us at h = 6
+//    for both workgroups of a CU with operands in the caches, about a tenth
+//    more in a layer (1024- to 8192-row products, K = 512 .. 8192); fp32 (K
+//    steps of 32): the 16 h MFMAs of a step and wave, 64 cycles each;
+//  * the cache lines its loads touch, about 640 per us and CU: a row's 128
+//    bytes are one line where the row pitch is a multiple of 128 bytes and up
+//    to two elsewhere (152,000 rows, K = 12064, N = 536: 2.0 us per step at h = 6,
+//    the product 3276 us against 2356 us on 256x256 tiles, which touch 0.6
+//    times as many lines per MFMA).
+// A round of K = 512 at h = 4 takes 3.2 us more than its 8 steps.  A last round
+// that leaves at least one of the two places of every CU empty takes about
+// 0.65 of a full one.
 struct StepCost {
-  int fixed, per_unit;   // ns per K step, ns per K step and unit of rows
+  int fixed, per_unit;               // ns per K step, ns per K step and unit of rows
+  int lines_fixed, lines_per_unit;   // the same for the cache lines
 };
-constexpr StepCost kStep16 = {210, 185}, kStepF32 = {60, 890};
+constexpr StepCost kStepF32 = {60, 890, 0, 0};
 __host__ __device__ inline int64_t mid_time(int64_t tiles, int h, int slots, int steps,
                                             const StepCost& c) {
   const int64_t full = tiles / slots, rem = tiles - full * slots;
+  const int a = c.fixed + c.per_unit * h, b = c.lines_fixed + c.lines_per_unit * h;
   return (20 * full + (rem == 0 ? 0 : 2 * rem <= slots ? 13 : 20)) *
-         (static_cast<int64_t>(steps) * (c.fixed + c.per_unit * h) + 3200) / 20;
+         (static_cast<int64_t>(steps) * (a > b ? a : b) + 3200) / 20;
 }
 
 // First index g < E whose inclusive prefix exceeds t.
@@ -93,7 +101,7 @@ struct SchedArgs {
   int max_mtiles, max_mid, max_segs, tmn_min, max_slots;
   int nt[2], steps[2];   // column tiles and K steps of the products of the two mid lists
   int slots_mid;         // workgroups of the mid kernel's persistent grid
-  StepCost cost;
+  StepCost cost[2];      // of the two mid lists' products
   Sched* s;              // outputs: the schedule and its lists
   int2 *mtile, *mtile_mid;
   int4* seg;
@@ -148,7 +156,7 @@ __device__ __forceinline__ void build_schedule(int m, const SchedArgs& A) {
       const int tot = __shfl(incl, 63, 64);
       mid_incl[task][g] = incl;
       if (g < 2)
-        cost[g][task] = mid_time(static_cast<int64_t>(tot) * A.nt[g], hm, A.slots_mid, A.steps[g], A.cost);
+        cost[g][task] = mid_time(static_cast<int64_t>(tot) * A.nt[g], hm, A.slots_mid, A.steps[g], A.cost[g]);
     } else if (task == kMidMaxH) {
       ti[g] = wave_incl_scan(ceil_units(m, BM));
       rw[g] = m;

@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 
 #include "../../include/moe.h"
 
@@ -149,9 +150,10 @@ __device__ __forceinline__ void mma_split(floatx4& c, const Split8& a, const uin
 
 // Eight lanes (8i .. 8i+7 of a wavefront) share one token's experts: lane
 // `sub` of them holds experts sub, sub + 8, .., at most kGroupE of them.  A
-// thread per token walks up to 64 experts several times over in series; the
-// group takes an eighth of each walk and three lane exchanges.  Every kernel
-// that evaluates the gate's softmax uses this one order of its sum.
+// thread per token evaluates up to 64 exponentials in series; the group takes
+// an eighth of them each and adds them in expert order, as a thread per token
+// does.  Every kernel that evaluates the gate's softmax uses that order, so
+// the same logits give the same probabilities bit for bit everywhere.
 constexpr int kGroupE = 8;
 __device__ __forceinline__ float group8_sum(float v) {
 #pragma unroll
@@ -163,8 +165,22 @@ __device__ __forceinline__ float group8_max(float v) {
   for (int o = 1; o < 8; o <<= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
   return v;
 }
+// The value of the group's lane J, in all its lanes (row_newbcast copies one
+// lane to its row of 16, a group being half a row: two bank masks).
+template <int J> __device__ __forceinline__ float group8_lane(float v) {
+  const int x = __float_as_int(v);
+  const int lo = __builtin_amdgcn_update_dpp(x, x, 0x150 + J, 0xF, 0x3, false);
+  return __int_as_float(__builtin_amdgcn_update_dpp(lo, x, 0x158 + J, 0xF, 0xC, false));
+}
+// f(integral_constant J) for the group's lanes J = 0 .. 7 in order
+template <typename F> __device__ __forceinline__ void for_group8(F&& f) {
+  f(std::integral_constant<int, 0>{}); f(std::integral_constant<int, 1>{});
+  f(std::integral_constant<int, 2>{}); f(std::integral_constant<int, 3>{});
+  f(std::integral_constant<int, 4>{}); f(std::integral_constant<int, 5>{});
+  f(std::integral_constant<int, 6>{}); f(std::integral_constant<int, 7>{});
+}
 // z[i] = exp(l[sub + 8 i] - m) (0 past E), m the largest logit, s the sum of
-// all z.
+// all z in expert order.
 __device__ __forceinline__ void group8_softmax(const float* l, int E, int sub, float (&z)[kGroupE],
                                                float& m, float& s) {
   m = -INFINITY;
@@ -183,9 +199,8 @@ __device__ __forceinline__ void group8_softmax(const float* l, int E, int sub, f
       continue;
     }
     z[i] = sub + 8 * i < E ? expf(z[i] - m) : 0.f;
-    s += z[i];
+    for_group8([&](auto j) { s += group8_lane<decltype(j)::value>(z[i]); });
   }
-  s = group8_sum(s);
 }
 
 __device__ __forceinline__ int ceil_div_i(int a, int b) { return (a + b - 1) / b; }

@@ -477,57 +477,62 @@ __global__ __launch_bounds__(256) void gate_fwd_f32_kernel(
 }
 
 // ---- backward ---------------------------------------------------------------
-// dlogits, eight lanes per token.
+// dlogits, eight lanes per token.  Sums over experts run in expert order and
+// sums over picks in pick order, as one thread per token would form them.
 __global__ __launch_bounds__(256) void gate_bwd_dlogits_kernel(
     const float* __restrict__ logits, const int32_t* __restrict__ ids,
     const float* __restrict__ dweights, const float* __restrict__ coef, int T, int E, int k,
     int renorm, float* __restrict__ dlogits) {
   const int t = blockIdx.x * 32 + (threadIdx.x >> 3), sub = threadIdx.x & 7;
   const size_t tt = min(t, T - 1);
-  float p[kGroupE], m, s;
-  group8_softmax(logits + tt * E, E, sub, p, m, s);
+  float p[kGroupE], dp[kGroupE], m, s;
+  const float* l = logits + tt * E;
+  group8_softmax(l, E, sub, p, m, s);
   const float inv = 1.f / s;
-#pragma unroll
-  for (int i = 0; i < kGroupE; ++i) p[i] *= inv;
-  // picks of each of the lane's experts and the sum of their dweights.  An id
-  // outside [0, E) (a bad cached id) is not a pick: its weight is 0 and it
-  // takes no part in the normalisation, as in moe_cached_weights.
-  float dw[kGroupE], hits[kGroupE];
-#pragma unroll
-  for (int i = 0; i < kGroupE; ++i) dw[i] = hits[i] = 0.f;
-  const int32_t* id = ids + tt * k;
-  for (int j = 0; j < k; ++j) {
-    const int e = id[j];
-    const float g = dweights[tt * k + j];
-#pragma unroll
-    for (int i = 0; i < kGroupE; ++i)
-      if (e == sub + 8 * i && e < E) {
-        dw[i] += g;
-        hits[i] += 1.f;
-      }
-  }
-  float S = 0.f, dot = 0.f;
-  if (renorm) {
-#pragma unroll
-    for (int i = 0; i < kGroupE; ++i)
-      if (hits[i] > 0.f) S += hits[i] * p[i];
-    S = group8_sum(S);
-#pragma unroll
-    for (int i = 0; i < kGroupE; ++i)
-      if (hits[i] > 0.f) dot += dw[i] * (p[i] / S);
-    dot = group8_sum(dot);
-  }
-  float pd = 0.f, dp[kGroupE];
 #pragma unroll
   for (int i = 0; i < kGroupE; ++i) {
     const int e = sub + 8 * i;
-    dp[i] = 0.f;
-    if (e >= E) continue;
-    if (coef) dp[i] = coef[e];   // a dprobs term shared by every token
-    if (hits[i] > 0.f) dp[i] += renorm ? (dw[i] - hits[i] * dot) / S : dw[i];
-    pd += dp[i] * p[i];
+    p[i] *= inv;
+    dp[i] = coef && e < E ? coef[e] : 0.f;   // a dprobs term shared by every token
   }
-  pd = group8_sum(pd);
+  // Lane j takes pick j (k <= 8).  An id outside [0, E) (a bad cached id) is
+  // not a pick: its weight is 0 and it takes no part in the normalisation, as
+  // in moe_cached_weights.
+  int mine = sub < k ? ids[tt * k + sub] : -1;
+  if (mine >= E) mine = -1;
+  float g = mine >= 0 ? dweights[tt * k + sub] : 0.f;
+  if (renorm) {
+    const float pj = mine >= 0 ? expf(l[mine] - m) * inv : 0.f;
+    float S = 0.f, dot = 0.f;
+    for_group8([&](auto j) {
+      constexpr int J = decltype(j)::value;
+      if (J < k) S += group8_lane<J>(pj);
+    });
+    const float q = mine >= 0 ? pj / S : 0.f;
+    for_group8([&](auto j) {
+      constexpr int J = decltype(j)::value;
+      if (J < k) dot = __builtin_fmaf(group8_lane<J>(g), group8_lane<J>(q), dot);
+    });
+    g = (g - dot) / S;
+  }
+  for_group8([&](auto j) {
+    constexpr int J = decltype(j)::value;
+    if (J >= k) return;
+    const int e = __float_as_int(group8_lane<J>(__int_as_float(mine)));
+    const float gj = group8_lane<J>(g);
+#pragma unroll
+    for (int i = 0; i < kGroupE; ++i)
+      if (8 * i < E && e == sub + 8 * i) dp[i] += gj;
+  });
+  float pd = 0.f;
+#pragma unroll
+  for (int i = 0; i < kGroupE; ++i) {
+    if (8 * i >= E) continue;
+    for_group8([&](auto j) {
+      constexpr int J = decltype(j)::value;
+      if (J + 8 * i < E) pd = __builtin_fmaf(group8_lane<J>(dp[i]), group8_lane<J>(p[i]), pd);
+    });
+  }
   if (t >= T) return;
 #pragma unroll
   for (int i = 0; i < kGroupE; ++i) {

@@ -407,3 +407,21 @@ def test_gate_picks_with_nonfinite_logits(dt, d, E, k):
         logits, ids, w = _run_gate(x, wg, bias, k, 1, dt)
     for t in range(T):
         assert list(ids[t]) == _scan_picks(logits[t], k), t
+
+
+# The softmax's sum runs in expert order in every kernel: with exp(-17) =
+# 4.1e-8, less than half an ulp of 1, the terms after a first 1 are each
+# absorbed (any other order adds some of them up first)
+@pytest.mark.parametrize("dt", ["bf16", "f32"])
+@pytest.mark.parametrize("E,T,d", [(64, 100, 64), (24, 70001, 64), (8, 50, 2056), (40, 40000, 64)])
+def test_softmax_sums_in_expert_order(dt, E, T, d):
+    bias = np.full(E, -17.0)
+    bias[0] = 0.0
+    x, wg = np.zeros((T, d)), np.zeros((E, d))
+    logits, ids, w = _run_gate(x, wg, bias, 1, 0, dt)
+    assert (ids == 0).all() and (w == 1.0).all()
+    cw = torch.empty(T, 1, device=dev())
+    B.moe_cached_weights(torch.from_numpy(logits.astype(np.float32)).to(dev()),
+                         torch.zeros(T, 1, dtype=torch.int32, device=dev()), 0, cw)
+    torch.cuda.synchronize()
+    assert (to_np(cw) == 1.0).all()

@@ -66,6 +66,41 @@ __device__ __forceinline__ void finish_group8(const float* l, int E, int k, int 
   }
 }
 
+// The same by one lane per token, bit for bit.
+__device__ __forceinline__ void finish_token(const float* l, int E, int k, int renorm,
+                                             int32_t* ids_out, float* w_out) {
+  float m = -INFINITY;
+  for (int e = 0; e < E; ++e) m = fmaxf(m, l[e]);
+  float s = 0.f;
+  for (int e = 0; e < E; ++e) s += expf(l[e] - m);
+  uint64_t taken = 0;
+  float pe[kMaxK];
+  int id[kMaxK];
+  float sel = 0.f;
+#pragma unroll
+  for (int j = 0; j < kMaxK; ++j) {
+    if (j < k) {
+      int bi = -1;
+      float best = -INFINITY;
+      for (int e = 0; e < E; ++e) {
+        if ((taken >> e) & 1ull) continue;
+        if (bi < 0 || l[e] > best) { best = l[e]; bi = e; }
+      }
+      taken |= 1ull << bi;
+      id[j] = bi;
+      pe[j] = expf(l[bi] - m);
+      sel += pe[j];
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < kMaxK; ++j) {
+    if (j < k) {
+      ids_out[j] = id[j];
+      w_out[j] = renorm ? pe[j] / sel : pe[j] / s;
+    }
+  }
+}
+
 constexpr int kGateTile = 32;   // tokens per MFMA row tile
 constexpr int kGateWaves = 4;   // waves per workgroup
 constexpr int kGateStage = kGateTile * 128;   // one K step of a tile: 32 rows x 64 bf16
@@ -224,11 +259,23 @@ __global__ __launch_bounds__(256) void gate_fwd_bf16_kernel(
     if (tb + row < T) logits[static_cast<size_t>(tb + row) * E + e] = v;
   }
   __syncthreads();
-  for (int row = threadIdx.x >> 3; row < tiles * kGateTile; row += 32) {
-    const int tt = row / kGateTile, rr = row - tt * kGateTile;
-    const size_t t = tb + row;
-    finish_group8(&wpart(tt * S)[rr][0], E, k, renorm, threadIdx.x & 7, tb + row < T, ids + t * k,
+  // Eight lanes finish a token where one tile is all the workgroup has and the
+  // walk over the experts is long: with all four tiles a lane per token
+  // finishes in one turn what groups of eight take four for.  Lane per token /
+  // eight lanes, us: T = 4096, d = 1024, E = 64, k = 2 19.0 / 12.3, E = 8 6.8
+  // / 6.8; T = 70000, d = 512, E = 64 47.4 / 57.2, E = 8 18.3 / 24.6.
+  if (EB > 1 && S == kGateWaves) {
+    const int rr = threadIdx.x >> 3;   // one token tile: 32 rows, 32 groups
+    const size_t t = tb + rr;
+    finish_group8(&wpart(0)[rr][0], E, k, renorm, threadIdx.x & 7, tb + rr < T, ids + t * k,
                   weights + t * k);
+  } else {
+    const int row = threadIdx.x;
+    if (row < tiles * kGateTile && tb + row < T) {
+      const int tt = row / kGateTile, rr = row - tt * kGateTile;
+      const size_t t = tb + row;
+      finish_token(&wpart(tt * S)[rr][0], E, k, renorm, ids + t * k, weights + t * k);
+    }
   }
 }
 
@@ -255,7 +302,7 @@ inline int gate_split(int T) {
 // wave's next group, so one group (4 * NCH KB) stays in flight per wave;
 // every load is issued (out-of-range lanes read zeros) and the loops have
 // no branch but their own.  The logits of a batch of 32 tokens collect in
-// the wave's LDS, then eight lanes finish each of them.
+// the wave's LDS, then 32 lanes finish one token each.
 // Sum of value (lane >> 1) of v[0..31] over all 64 lanes, in lanes lane and
 // lane ^ 1.  Each step pairs a lane with a partner that holds the same
 // subset of values, keeps one half of that subset (the upper half in the
@@ -392,14 +439,12 @@ __global__ __launch_bounds__(256, 2) void gate_rows_bf16_kernel(
       if ((lane & 1) == 0) my[s * 32 + idx] = l;
       if ((lane & 1) == 0 && ve < E && tok < T) logits[static_cast<size_t>(tok) * E + ve] = l;
     }
-    // token slot (group s, token t) of the batch: its logits at slot * EC;
-    // eight lanes finish one
+    // token slot lane = (group s, token t) of the batch, its logits at lane * EC
     __builtin_amdgcn_wave_barrier();
-    for (int slot = lane >> 3; slot < kRowsBatch; slot += 8) {
-      const int tok = (gb + (slot / TPW) * nw) * TPW + slot % TPW;
-      finish_group8(my + slot * EC, E, k, renorm, lane & 7, tok < T,
-                    ids + static_cast<size_t>(tok) * k, weights + static_cast<size_t>(tok) * k);
-    }
+    const int tok = (gb + (lane / TPW) * nw) * TPW + lane % TPW;
+    if (lane < kRowsBatch && tok < T)
+      finish_token(my + lane * EC, E, k, renorm, ids + static_cast<size_t>(tok) * k,
+                   weights + static_cast<size_t>(tok) * k);
     __builtin_amdgcn_wave_barrier();
   }
 }
@@ -478,7 +523,9 @@ __global__ __launch_bounds__(256) void gate_fwd_f32_kernel(
 
 // ---- backward ---------------------------------------------------------------
 // dlogits, eight lanes per token.  Sums over experts run in expert order and
-// sums over picks in pick order, as one thread per token would form them.
+// sums over picks in pick order, as one thread per token would form them.  One
+// thread per token / this, us: T = 131072, E = 64, k = 8 58 / 33, T = 16384,
+// E = 64, k = 1 16 / 7.6, T = 4096, E = 64, k = 2 16 / 7.1, E <= 8 within 1.
 __global__ __launch_bounds__(256) void gate_bwd_dlogits_kernel(
     const float* __restrict__ logits, const int32_t* __restrict__ ids,
     const float* __restrict__ dweights, const float* __restrict__ coef, int T, int E, int k,

@@ -98,7 +98,10 @@ __device__ __forceinline__ float wave_sum(float v) {
 // next 8, the last 8: each the truncation of what the ones before leave), so
 // a product with a bf16 value is the sum of three exact bf16 products, and
 // three bf16 MFMAs with fp32 sums give what fp32 FMAs give, at 16 / 3 times
-// the rate of fp32 MFMAs.  An infinity keeps to the first part.
+// the rate of fp32 MFMAs.  An infinity keeps to the first part.  An infinity
+// on the bf16 side meets parts that are zero (those of 0.5, say), and 0 x inf
+// is NaN where the FMA gives inf: callers look for NaNs among their sums and form
+// those again with FMAs.
 struct Split8 {
   uint4 part[3];   // 8 values each, packed bf16
 };
@@ -146,6 +149,15 @@ __device__ __forceinline__ void mma_split(floatx4& c, const Split8& a, const uin
 #pragma unroll
   for (int i = 2; i >= 0; --i)
     c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a.part[i]), bv, c, 0, 0, 0);
+}
+// Whether one of the wavefront's sums is NaN.
+template <int N> __device__ __forceinline__ bool any_nan(const floatx4 (&c)[N]) {
+  bool bad = false;
+#pragma unroll
+  for (int j = 0; j < N; ++j)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) bad |= c[j][q] != c[j][q];
+  return __any(bad);
 }
 
 // Eight lanes (8i .. 8i+7 of a wavefront) share one token's experts: lane

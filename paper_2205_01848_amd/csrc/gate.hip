@@ -632,10 +632,6 @@ __global__ __launch_bounds__(256) void gate_bwd_dwg_partial_kernel(
   // token of the lane's i-th value among the 32
   auto tok = [&](int i) { return BF ? 8 * G + i : 4 * i + G; };
   floatx4 acc[EB][V];
-#pragma unroll
-  for (int b = 0; b < EB; ++b)
-#pragma unroll
-    for (int j = 0; j < V; ++j) acc[b][j] = floatx4{0.f, 0.f, 0.f, 0.f};
   struct Batch {
     uint4 x[8];
     float g[EB][8];
@@ -664,6 +660,10 @@ __global__ __launch_bounds__(256) void gate_bwd_dwg_partial_kernel(
       }
     }
   };
+#pragma unroll
+  for (int b = 0; b < EB; ++b)
+#pragma unroll
+    for (int j = 0; j < V; ++j) acc[b][j] = floatx4{0.f, 0.f, 0.f, 0.f};
   Batch cur, nxt;
   load(tb, cur);
 #pragma unroll 1
@@ -712,6 +712,23 @@ __global__ __launch_bounds__(256) void gate_bwd_dwg_partial_kernel(
     }
     const int e = 16 * b + 4 * G + wave;
     if (colok && e < E) {
+      if constexpr (BF) {
+        bool nan = false;
+#pragma unroll
+        for (int j = 0; j < V; ++j) nan |= v[j] != v[j];
+        if (nan) {   // non-finite inputs: these sums by FMAs (see split8)
+#pragma unroll
+          for (int j = 0; j < V; ++j) v[j] = 0.f;
+          const int t1 = min(Ttok, (chunk + 1) * 4 * TW);
+          for (int t = chunk * 4 * TW; t < t1; ++t) {
+            float f[V];
+            Elem<T>::load(*reinterpret_cast<const uint4*>(xp + static_cast<size_t>(t) * d), f);
+            const float g = dl[static_cast<size_t>(t) * E + e];
+#pragma unroll
+            for (int j = 0; j < V; ++j) v[j] = __builtin_fmaf(g, f[j], v[j]);
+          }
+        }
+      }
       float* o = out + static_cast<size_t>(e) * d + c0;
 #pragma unroll
       for (int j = 0; j < V; j += 4)

@@ -982,6 +982,22 @@ __global__ __launch_bounds__(256) void dispatch_bwd_wide_kernel(
 #pragma unroll
       for (int j = 0; j < V; ++j) mma_split(acc[j], g, w[s][j]);
     }
+    if (any_nan(acc)) {
+      // non-finite inputs: the wavefront's sums by FMAs (see split8)
+#pragma unroll
+      for (int j = 0; j < V; ++j) acc[j] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+      for (int e = 0; e < E; ++e) {
+        float f[V];
+        Elem<T>::load(wg[static_cast<size_t>(e) * nvec + vc], f);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const float g = dl[static_cast<size_t>(min(t0 + 4 * G + q, Ttok - 1)) * E + e];
+#pragma unroll
+          for (int j = 0; j < V; ++j) acc[j][q] = __builtin_fmaf(g, f[j], acc[j][q]);
+        }
+      }
+    }
     if (!colok) continue;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {

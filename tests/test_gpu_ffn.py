@@ -440,3 +440,59 @@ def test_dispatch_backward_wide_gate(T, d, E, k, shift):
     # both round once: where the fp32 sums fall on either side of a midpoint
     # the results are neighbouring bf16 values, at most 2^-7 apart (relative)
     assert_close(to_np(dx), ref, 2.0 ** -7, "dx")
+
+
+def _same_values(got, ref, rtol, name):
+    """Equal infinities and NaNs, the finite values within rtol of their scale."""
+    np.testing.assert_array_equal(np.isnan(got), np.isnan(ref), err_msg=name)
+    np.testing.assert_array_equal(np.where(np.isinf(got), got, 0), np.where(np.isinf(ref), ref, 0),
+                                  err_msg=name)
+    fin = np.isfinite(ref)
+    assert_close(got[fin], ref[fin], rtol, name)
+
+
+# An infinity times a dlogit with zero low parts (0.25, 0.5) is an infinity,
+# as in fp32 multiply-adds, also where the product runs on three bf16 parts
+@pytest.mark.parametrize("E", [2, 16, 40])
+@pytest.mark.parametrize("dt", ["bf16", "f32"])
+def test_gate_backward_infinite_x(dt, E):
+    T, d = 200, 72
+    rng = np.random.default_rng(E)
+    x = rng.integers(-2, 3, (T, d)) / 4.0
+    x[3, 5], x[150, 9], x[7, 40], x[190, 40], x[8, 41] = np.inf, -np.inf, np.inf, -np.inf, np.nan
+    x = _enc(x, dt)
+    ids = np.zeros((T, 1), np.int32)
+    logits = np.full((T, E), -np.inf, np.float32)
+    logits[:, :2] = 0.0                       # p = 1/2, 1/2, 0, ..
+    dl = torch.empty(T, E, device=dev())
+    dwg = torch.empty(E, d, device=dev())
+    ws = B.workspace(B.moe_gate_bwd_workspace_bytes(T, d, E), dev())
+    B.moe_gate_bwd(to_dev(x, dt), torch.from_numpy(logits).to(dev()), torch.from_numpy(ids).to(dev()),
+                   torch.ones(T, 1, device=dev()), 0, dl, dwg, ws)
+    torch.cuda.synchronize()
+    g = to_np(dl)
+    np.testing.assert_array_equal(g[:, :2], np.tile([0.25, -0.25], (T, 1)))
+    with np.errstate(invalid="ignore"):
+        ref = (g[:, :, None] * _dec(x, dt)[:, None, :]).sum(0)
+    assert np.isinf(ref[:2]).any() and np.isnan(ref[:2]).any()
+    _same_values(to_np(dwg), ref, 1e-5, "dw_g")
+
+
+@pytest.mark.parametrize("E", [12, 17, 64])
+def test_dispatch_backward_infinite_gate(E):
+    T, d, k = 150, 136, 2
+    rng = np.random.default_rng(E)
+    wg = rng.integers(1, 5, (E, d)) / 4.0
+    wg[3, 7], wg[4, 11], wg[E - 1, 130], wg[2, 60], wg[5, 60] = np.inf, -np.inf, np.inf, np.inf, -np.inf
+    dl = rng.choice([-0.5, 0.5, 1.0], (T, E))
+    dl[20, 1], dl[21, 3] = np.inf, np.nan
+    dest = rng.permutation(T * k).reshape(T, k).astype(np.int32)
+    dxd, wgb = _enc(rng.standard_normal((T * k, d)), "bf16"), _enc(wg, "bf16")
+    dx = torch.empty(T, d, dtype=torch.bfloat16, device=dev())
+    B.moe_dispatch_bwd(to_dev(dxd, "bf16"), torch.from_numpy(dest).to(dev()), E,
+                       torch.from_numpy(dl.astype(np.float32)).to(dev()), to_dev(wgb, "bf16"), dx)
+    torch.cuda.synchronize()
+    with np.errstate(invalid="ignore"):
+        ref = _dec(dxd, "bf16")[dest].sum(1) + (dl[:, :, None] * wg[None]).sum(1)
+    assert np.isinf(ref).any()
+    _same_values(to_np(dx), ref, 2.0 ** -7, "dx")

@@ -897,7 +897,8 @@ __global__ __launch_bounds__(256) void dispatch_bwd_kernel(
 // the fragments of eight column blocks (block j's column n stands for column
 // 8 n + j), so it ends with 8 consecutive columns of tokens 4 G + q and adds
 // and stores whole vectors.  The w_g fragments stay in registers over kMmTiles
-// token tiles; the column groups of a row run next to each other.
+// token tiles; the column groups of a row run next to each other (one grid
+// dimension: HIP allows 65,536 blocks in the others, 8.4M tokens here).
 constexpr int kMmTiles = 2;
 
 template <int KT, int KS>   // KS: steps of 32 experts
@@ -910,7 +911,9 @@ __global__ __launch_bounds__(256) void dispatch_bwd_wide_kernel(
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
   const int n = lane & 15, G = lane >> 4;
-  const int v = static_cast<int>(blockIdx.x) * 16 + n;
+  const int ncol = (nvec + 15) / 16;
+  const int tb = static_cast<int>(blockIdx.x) / ncol;
+  const int v = (static_cast<int>(blockIdx.x) - tb * ncol) * 16 + n;
   const bool colok = v < nvec;
   const int vc = min(v, nvec - 1);
   const uint4 zero = make_uint4(0u, 0u, 0u, 0u);
@@ -929,7 +932,7 @@ __global__ __launch_bounds__(256) void dispatch_bwd_wide_kernel(
   }
 #pragma unroll 1
   for (int tile = 0; tile < kMmTiles; ++tile) {
-    const int t0 = ((static_cast<int>(blockIdx.y) * kMmTiles + tile) * kRowWaves + wave) * 16;
+    const int t0 = ((tb * kMmTiles + tile) * kRowWaves + wave) * 16;
     if (t0 >= Ttok) break;
     // the rows of the lane's output tokens 4 G + q: their gathers are issued
     // ahead of the MFMAs while they fit in registers
@@ -1438,7 +1441,7 @@ extern "C" moe_status moe_dispatch_bwd(void* stream, moe_dtype dt, int T, int d,
     return MOE_OK;
   }
   if (dt == MOE_BF16 && E > 16) {
-    const dim3 grid(nblocks(nvec, 16), nblocks(T, kRowWaves * kMmTiles * 16));
+    const int grid = nblocks(nvec, 16) * nblocks(T, kRowWaves * kMmTiles * 16);
     with_pick_bound(k, [&](auto kt_tag) {
       constexpr int KT = decltype(kt_tag)::value;
       (E <= 32 ? dispatch_bwd_wide_kernel<KT, 1> : dispatch_bwd_wide_kernel<KT, 2>)<<<grid, 256, 0, s>>>(

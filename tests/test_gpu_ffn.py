@@ -496,3 +496,19 @@ def test_dispatch_backward_infinite_gate(E):
         ref = _dec(dxd, "bf16")[dest].sum(1) + (dl[:, :, None] * wg[None]).sum(1)
     assert np.isinf(ref).any()
     _same_values(to_np(dx), ref, 2.0 ** -7, "dx")
+
+
+def test_dispatch_backward_wide_gate_many_tokens():
+    """More than 65,536 blocks of tokens."""
+    T, d, E = 65537 * 128 + 5, 8, 17
+    g = torch.Generator(device="cuda").manual_seed(2)
+    dxd = torch.randn(T, d, device=dev(), generator=g).to(torch.bfloat16)
+    dl = torch.randn(T, E, device=dev(), generator=g)
+    wg = torch.randn(E, d, device=dev(), generator=g).to(torch.bfloat16)
+    dest = torch.arange(T - 1, -1, -1, dtype=torch.int32, device=dev()).view(T, 1)
+    dx = torch.full((T, d), float("nan"), dtype=torch.bfloat16, device=dev())
+    B.moe_dispatch_bwd(dxd, dest, E, dl, wg, dx)
+    torch.cuda.synchronize()
+    for a, b in ((0, 1000), (T // 2, T // 2 + 1000), (T - 1000, T)):
+        ref = dxd.flip(0)[a:b].double() + dl[a:b].double() @ wg.double()
+        assert_close(to_np(dx[a:b]), ref.cpu().numpy(), 2.0 ** -7, f"dx {a}")

@@ -888,9 +888,9 @@ __global__ __launch_bounds__(256) void dispatch_bwd_kernel(
   }
 }
 
-// The same for wide gates (E > 16) of bf16 layers, whose E multiply-adds per
+// The same for wide gates (E > 16) of bf16 layers, where E multiply-adds per
 // element take longer than the memory traffic (T = 16384, d = 1024, E = 64, k
-// = 1: 51 us, here 36 us): dl . w_g on bf16 matrix cores, dl as three bf16
+// = 1: 51 us, here 36 us; see wide_gate_pays): dl . w_g on bf16 matrix cores, dl as three bf16
 // parts (split8).  A wavefront takes 16 tokens by 128 columns: lane l = 16 G +
 // n supplies token n, experts 32 s + 8 G .. +7 of step s, and of each of those
 // experts columns 8 n .. +7, which an 8 x 8 transpose in registers turns into
@@ -1411,6 +1411,29 @@ extern "C" moe_status moe_combine_bwd(void* stream, moe_dtype dt, int T, int d, 
   return MOE_OK;
 }
 
+// Whether dispatch_bwd_wide_kernel is the faster one (bf16, E > 16).  It has
+// the multiply-adds on matrix cores but takes 256 bytes of a row at a time
+// where the other takes 1 KB, so it moves rows at 3.6 to 4 TB/s against 4.9
+// (2.7 against 4.4 where its gathers no longer fit in registers, k > 2).  A
+// multiply-add costs the other about 1/22 ps, more where the last 64 vectors
+// of a row are partly filled, and a row element moved 0.4 ps: the line lies at
+// about 10 experts per row moved (13 past the last-level cache), 20 with a
+// second step of 32 experts, 17 for k > 2.  Below 16 MB both wait on
+// latencies, the other on E of them in series.
+// Other / wide kernel, us: T = 65536, d = 1024: E = 17, k = 2 75 / 100, E = 24,
+// k = 1 74 / 77, E = 32, k = 1 89 / 78, E = 64, k = 2 165 / 137, k = 3 179 /
+// 209; T = 8192, d = 2048, E = 32, k = 2 32 / 24; T = 65536, d = 64, E = 17, k =
+// 2 32 / 11; T = 2000, d = 64, E = 20: k = 2 18 / 7.9, k = 8 9.7 / 14; T =
+// 2000, d = 1000, E = 24, k = 3 9.8 / 13.
+static bool wide_gate_pays(int T, int d, int E, int k) {
+  constexpr int64_t MB = 1 << 20;
+  const int64_t bytes = static_cast<int64_t>(T) * d * 2 * (k + 1);
+  if (bytes < 16 * MB) return k <= 2 || (k <= 4 && bytes < 4 * MB);
+  const int64_t nvec = d / 8, lanes = (nvec + 63) / 64 * 64;
+  const int per_row = k > 2 ? 17 : E > 32 ? 20 : bytes >= 256 * MB ? 13 : 10;
+  return E * lanes > per_row * (k + 1) * nvec;
+}
+
 extern "C" moe_status moe_dispatch_bwd(void* stream, moe_dtype dt, int T, int d, int E, int k,
                                        int64_t rows_alloc, const void* dx_disp,
                                        const int32_t* dest_row, const float* dlogits,
@@ -1440,7 +1463,7 @@ extern "C" moe_status moe_dispatch_bwd(void* stream, moe_dtype dt, int T, int d,
     MOE_LAUNCH_CHECK();
     return MOE_OK;
   }
-  if (dt == MOE_BF16 && E > 16) {
+  if (dt == MOE_BF16 && E > 16 && wide_gate_pays(T, d, E, k)) {
     const int grid = nblocks(nvec, 16) * nblocks(T, kRowWaves * kMmTiles * 16);
     with_pick_bound(k, [&](auto kt_tag) {
       constexpr int KT = decltype(kt_tag)::value;

@@ -416,10 +416,13 @@ def test_gate_backward_edges(dt, T, d, E, k):
 
 # dispatch backward of wide gates (more than 16 experts: dlogits as three bf16
 # parts on matrix cores): one and two steps of 32 experts, partial tiles of 16
-# tokens and 128 columns, every pick bound, dlogits off 16-byte alignment
+# tokens and 128 columns, every pick bound, dlogits off 16-byte alignment; both
+# sides of the choice between it and the kernel of narrow gates
 @pytest.mark.parametrize("T,d,E,k,shift", [(1, 8, 17, 1, 0), (16, 128, 32, 2, 1), (70, 136, 33, 3, 0),
                                            (700, 264, 64, 8, 3), (1030, 1032, 60, 2, 0),
-                                           (40, 120, 64, 1, 2)])
+                                           (40, 120, 64, 1, 2), (20011, 64, 33, 8, 1),
+                                           (20011, 64, 20, 7, 0), (9001, 264, 64, 4, 0),
+                                           (2000, 1000, 24, 3, 0)])
 def test_dispatch_backward_wide_gate(T, d, E, k, shift):
     rng = np.random.default_rng(T + d)
     R = T * k + 3

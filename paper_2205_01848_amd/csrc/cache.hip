@@ -65,16 +65,32 @@ __global__ __launch_bounds__(256) void cache_update_kernel(const int32_t* __rest
 // weights[t,j] = p[t, ids[t,j]] (renorm: divided by the sum over the picks)
 // with p = softmax(logits[t]), evaluated exactly as the gate evaluates its
 // own weights, so cached picks equal to the fresh ones give equal weights.
-// An id outside [0, E) gets weight 0 and is left out of the sum.
+// An id outside [0, E) gets weight 0 and is left out of the sum.  GROUP: eight
+// lanes share a token; with few experts and enough tokens to fill the chip a
+// lane per token does less (T = 131072, k = 2, one lane / eight, us: E = 4 3.2 /
+// 6.9, E = 12 5.6 / 8.4, E = 16 10.5 / 8.6, E = 64 66 / 16; T = 4096, E = 12 5.0
+// / 3.6).
+constexpr int kCachedLaneE = 12;
+constexpr int kCachedLaneT = 65536;
+template <bool GROUP>
 __global__ __launch_bounds__(256) void cached_weights_kernel(const float* __restrict__ logits,
                                                              const int32_t* __restrict__ ids,
                                                              int T, int E, int k, int renorm,
                                                              float* __restrict__ weights) {
-  const int t = blockIdx.x * 32 + (threadIdx.x >> 3), sub = threadIdx.x & 7;
+  const int t = GROUP ? blockIdx.x * 32 + (threadIdx.x >> 3) : blockIdx.x * 256 + threadIdx.x;
   const float* l = logits + static_cast<size_t>(min(t, T - 1)) * E;
-  float z[kGroupE], m, s;
-  group8_softmax(l, E, sub, z, m, s);
-  if (t >= T || sub != 0) return;
+  float m, s;
+  if constexpr (GROUP) {
+    float z[kGroupE];
+    group8_softmax(l, E, threadIdx.x & 7, z, m, s);
+    if (t >= T || (threadIdx.x & 7) != 0) return;
+  } else {
+    if (t >= T) return;
+    m = -INFINITY;
+    for (int e = 0; e < E; ++e) m = fmaxf(m, l[e]);
+    s = 0.f;
+    for (int e = 0; e < E; ++e) s += expf(l[e] - m);
+  }
   float pe[kMaxK];
   float sel = 0.f;
 #pragma unroll
@@ -121,7 +137,11 @@ extern "C" moe_status moe_cached_weights(void* stream, int T, int E, int k, int 
   if (!logits || !ids || !weights) return MOE_EINVAL;
   hipStream_t s = static_cast<hipStream_t>(stream);
   MOE_TIMED("cached_weights", s);
-  cached_weights_kernel<<<(T + 31) / 32, 256, 0, s>>>(logits, ids, T, E, k, renorm, weights);
+  if (E > kCachedLaneE || T < kCachedLaneT)
+    cached_weights_kernel<true><<<(T + 31) / 32, 256, 0, s>>>(logits, ids, T, E, k, renorm, weights);
+  else
+    cached_weights_kernel<false><<<(T + 255) / 256, 256, 0, s>>>(logits, ids, T, E, k, renorm,
+                                                                 weights);
   MOE_LAUNCH_CHECK();
   return MOE_OK;
 }

@@ -414,7 +414,8 @@ def test_gate_picks_with_nonfinite_logits(dt, d, E, k, T):
 # 4.1e-8, less than half an ulp of 1, the terms after a first 1 are each
 # absorbed (any other order adds some of them up first)
 @pytest.mark.parametrize("dt", ["bf16", "f32"])
-@pytest.mark.parametrize("E,T,d", [(64, 100, 64), (24, 70001, 64), (8, 50, 2056), (40, 40000, 64)])
+@pytest.mark.parametrize("E,T,d", [(64, 100, 64), (24, 70001, 64), (8, 50, 2056), (40, 40000, 64),
+                                   (10, 66001, 64)])
 def test_softmax_sums_in_expert_order(dt, E, T, d):
     bias = np.full(E, -17.0)
     bias[0] = 0.0

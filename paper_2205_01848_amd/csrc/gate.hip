@@ -453,14 +453,20 @@ __global__ __launch_bounds__(256, 2) void gate_rows_bf16_kernel(
 // v_mfma_f32_16x16x4_f32 (token rows as A, expert rows of w_g as B).  Lane l =
 // 16 G + n reads 16 bytes of row n, k = 16 s + 4 G .. +3, and MFMA j of step s
 // takes its j-th value, so every k of the step enters one MFMA, of A and B
-// alike.  Wavefront w takes steps w, w + 4, .. (four steps are 256 contiguous
-// bytes of a row), kF32Steps of them loaded ahead; the four partial scores
-// are summed through LDS in order.  One thread per token instead leaves T / 64
-// wavefronts walking whole rows: T = 2048, d = 256, E = 8 took 55 us, now
-// 7.6 us.
+// alike.  The S wavefronts of a tile share its steps: wavefront w takes steps
+// w, w + S, .., kF32Steps of them loaded ahead, without branches (with a branch
+// around every load the loads waited for one another: T = 65536, d = 512, E = 8
+// 93 us, now 28); the S partial scores are summed through LDS in order.  Short
+// rows of long batches are scored by a wavefront alone, four tiles per
+// workgroup (T = 65536, d = 64: E = 4, k = 2 15.8 / 7.6 us with S = 4 / 1, E =
+// 64 47.8 / 26.8; T = 65536, d = 512, E = 4 27 / 29).  One thread per token
+// instead leaves T / 64 wavefronts walking whole rows: T = 2048, d = 256, E = 8
+// 30 us against 5.3, T = 65536, d = 64, E = 4 10.4 against 7.6.
+constexpr int kF32WholeD = 128;     // S = 1 up to this d ..
+constexpr int kF32WholeT = 16384;   // .. from this T on
 constexpr int kF32Tok = 16;
 constexpr int kF32Steps = 4;
-template <int EB>
+template <int EB, int S>   // blocks of 16 experts; wavefronts that share a tile's steps (4 or 1)
 __global__ __launch_bounds__(256) void gate_fwd_f32_kernel(
     const float* __restrict__ x, const float* __restrict__ wg,
     const float* __restrict__ bias, int T, int d, int E, int k, int renorm,
@@ -470,24 +476,30 @@ __global__ __launch_bounds__(256) void gate_fwd_f32_kernel(
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = lane & 15, G = lane >> 4;
-  const int t0 = blockIdx.x * kF32Tok;
+  constexpr int TILES = 4 / S, TOK = TILES * kF32Tok;
+  const int tb = blockIdx.x * TOK, t0 = tb + wave / S * kF32Tok;
   const int nsteps = (d + 15) / 16;
   const float* xr = x + static_cast<size_t>(min(t0 + n, T - 1)) * d;
+  const float* wr[EB];
+#pragma unroll
+  for (int b = 0; b < EB; ++b) wr[b] = wg + static_cast<size_t>(min(16 * b + n, E - 1)) * d;
+  auto keep = [](const float4& v, bool ok) {
+    return make_float4(ok ? v.x : 0.f, ok ? v.y : 0.f, ok ? v.z : 0.f, ok ? v.w : 0.f);
+  };
   floatx4 acc[EB];
 #pragma unroll
   for (int b = 0; b < EB; ++b) acc[b] = floatx4{0.f, 0.f, 0.f, 0.f};
-  for (int s0 = wave; s0 < nsteps; s0 += 4 * kF32Steps) {
+  for (int s0 = wave % S; s0 < nsteps; s0 += S * kF32Steps) {
     float4 a[kF32Steps], w[kF32Steps][EB];
 #pragma unroll
     for (int u = 0; u < kF32Steps; ++u) {
-      const int kk = 16 * (s0 + 4 * u) + 4 * G;   // d is a multiple of 8: whole or past the end
-      const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
-      a[u] = kk < d ? *reinterpret_cast<const float4*>(xr + kk) : zero;
+      // past the row's end (d is a multiple of 8: whole or past) and past E
+      // the load is of something valid and the value zero: no branches
+      const int kk = 16 * (s0 + S * u) + 4 * G, kc = min(kk, d - 4);
+      a[u] = keep(*reinterpret_cast<const float4*>(xr + kc), kk < d);
 #pragma unroll
       for (int b = 0; b < EB; ++b)
-        w[u][b] = kk < d && 16 * b + n < E
-                      ? *reinterpret_cast<const float4*>(wg + static_cast<size_t>(16 * b + n) * d + kk)
-                      : zero;
+        w[u][b] = keep(*reinterpret_cast<const float4*>(wr[b] + kc), kk < d && 16 * b + n < E);
     }
 #pragma unroll
     for (int u = 0; u < kF32Steps; ++u)
@@ -505,19 +517,28 @@ __global__ __launch_bounds__(256) void gate_fwd_f32_kernel(
 #pragma unroll
     for (int q = 0; q < 4; ++q) part[wave][4 * G + q][16 * b + n] = acc[b][q];
   __syncthreads();
-  for (int i = tid; i < kF32Tok * E; i += 256) {
-    const int r = i / E, e = i - r * E;
-    float v = part[0][r][e];
-    for (int w = 1; w < 4; ++w) v += part[w][r][e];
+  for (int i = tid; i < TOK * E; i += 256) {
+    const int row = i / E, e = i - row * E;
+    const int tile = row / kF32Tok, r = row - tile * kF32Tok;
+    float v = part[tile * S][r][e];
+#pragma unroll
+    for (int w = 1; w < S; ++w) v += part[tile * S + w][r][e];
     v += bias ? bias[e] : 0.f;
-    part[0][r][e] = v;
-    if (t0 + r < T) logits[static_cast<size_t>(t0 + r) * E + e] = v;
+    part[tile * S][r][e] = v;
+    if (tb + row < T) logits[static_cast<size_t>(tb + row) * E + e] = v;
   }
   __syncthreads();
-  if (tid < 8 * kF32Tok) {
-    const int r = tid >> 3;
-    const size_t t = t0 + r;
-    finish_group8(&part[0][r][0], E, k, renorm, tid & 7, t0 + r < T, ids + t * k, weights + t * k);
+  if (S > 1 || EB > 1) {
+    for (int row = tid >> 3; row < TOK && tid < 8 * TOK; row += 32) {
+      const size_t t = tb + row;
+      finish_group8(&part[row / kF32Tok * S][row % kF32Tok][0], E, k, renorm, tid & 7, tb + row < T,
+                    ids + t * k, weights + t * k);
+    }
+  } else {
+    const int row = tid >> 2;   // one lane of every four
+    const size_t t = tb + row;
+    if ((tid & 3) == 0 && tb + row < T)
+      finish_token(&part[row / kF32Tok][row % kF32Tok][0], E, k, renorm, ids + t * k, weights + t * k);
   }
 }
 
@@ -821,9 +842,15 @@ extern "C" moe_status moe_gate_topk(void* stream, moe_dtype dt, int T, int d,
     else go(I2{}, std::integral_constant<int, 8>{}, I2{});
   } else {
     auto go = [&](auto eb) {
-      gate_fwd_f32_kernel<decltype(eb)::value><<<dim3((T + kF32Tok - 1) / kF32Tok), 256, 0, s>>>(
-          static_cast<const float*>(x), static_cast<const float*>(w_g), bias, T, d, E, k, renorm,
-          logits, ids, weights);
+      constexpr int EB = decltype(eb)::value;
+      if (d <= kF32WholeD && T >= kF32WholeT)
+        gate_fwd_f32_kernel<EB, 1><<<dim3((T + 4 * kF32Tok - 1) / (4 * kF32Tok)), 256, 0, s>>>(
+            static_cast<const float*>(x), static_cast<const float*>(w_g), bias, T, d, E, k, renorm,
+            logits, ids, weights);
+      else
+        gate_fwd_f32_kernel<EB, 4><<<dim3((T + kF32Tok - 1) / kF32Tok), 256, 0, s>>>(
+            static_cast<const float*>(x), static_cast<const float*>(w_g), bias, T, d, E, k, renorm,
+            logits, ids, weights);
     };
     switch ((E + 15) / 16) {
       case 1: go(std::integral_constant<int, 1>{}); break;

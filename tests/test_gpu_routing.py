@@ -53,6 +53,8 @@ def _run_gate(x_np, wg_np, b_np, k, renorm, dt):
     (777, 1800, 12, 3, 0, "bf16"),
     (129, 64, 4, 1, 0, "f32"),
     (300, 40, 64, 4, 1, "f32"),
+    (16390, 72, 20, 2, 1, "f32"),     # a wavefront per tile of 16 tokens
+    (16399, 128, 5, 1, 0, "f32"),
 ])
 def test_gate_exact_logits_and_ties(T, d, E, k, renorm, dt):
     rng = np.random.default_rng(T + d + E)
@@ -394,7 +396,8 @@ def _scan_picks(l, k):
 @pytest.mark.parametrize("dt,d,E,k,T", [("f32", 64, 3, 2, 75), ("f32", 40, 64, 8, 75),
                                         ("bf16", 64, 20, 4, 75), ("bf16", 2056, 8, 3, 75),
                                         ("bf16", 128, 33, 8, 75), ("bf16", 64, 20, 4, 33001),
-                                        ("bf16", 64, 33, 8, 66001)])
+                                        ("bf16", 64, 33, 8, 66001), ("f32", 72, 13, 3, 16399),
+                                        ("f32", 128, 33, 8, 16385)])
 def test_gate_picks_with_nonfinite_logits(dt, d, E, k, T):
     rng = np.random.default_rng(E + k)
     x = rng.integers(-2, 3, (T, d)) / 4.0

@@ -1076,6 +1076,22 @@ __global__ __launch_bounds__(kThreads16, 1) void ffn_gemm16_kernel(const GemmPar
   }
 }
 
+// Item of this workgroup in a round of the two-workgroups-per-CU kernels'
+// persistent grid, or -1 when it has none left.  Whole rounds give XCD b % 8 a
+// contiguous run of items; the last, partial one is spread over all XCDs the
+// same way, on as many workgroups as it has items, so it takes a CU each as
+// far as they go.  (The grid follows the most tiles the schedule could list;
+// with the runs of a whole round the items of a short one would all fall to
+// the first XCDs: 4 experts of 306 rows, K = 2504, N = 1000, 112 tiles on two of
+// the eight 44 us, now 29; of 1021 rows, 192 tiles of 192 rows 65 / 38.)
+__device__ __forceinline__ int round_item(int round, int n_items) {
+  const int b = blockIdx.x, first = round * static_cast<int>(gridDim.x), left = n_items - first;
+  const int G = min(static_cast<int>(gridDim.x), (left + kXcds - 1) / kXcds * kXcds);
+  if (left <= 0 || b >= G) return -1;
+  const int L = first + (b % kXcds) * (G / kXcds) + b / kXcds;
+  return L < n_items ? L : -1;
+}
+
 // One tile of the two-workgroups-per-CU kernels: var-M tiles of the heights
 // the schedule chose, weight-gradient tiles of p.dw_h units of rows.
 struct MidTile {
@@ -1156,12 +1172,9 @@ __global__ __launch_bounds__(kThreads16, 2) void ffn_gemm16_mid_kernel(const Gem
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
   const int wm = wave >> 1, wn = wave & 1;
   const int n_items = mid_items<MODE>(p);
-  const int G = gridDim.x;
-  const int lbase = (blockIdx.x % kXcds) * (G / kXcds) + blockIdx.x / kXcds;
-
   for (int round = 0;; ++round) {
-    const int L = round * G + lbase;
-    if (L >= n_items) break;
+    const int L = round_item(round, n_items);
+    if (L < 0) break;
     MidTile t;
     mid_operands<MODE, PASS, 2>(p, L, t);
     auto run = [&](auto hc) {
@@ -1356,11 +1369,9 @@ __global__ __launch_bounds__(kThreads16, 2) void ffn_gemm_f32_kernel(const GemmP
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
   const int n_items = mid_items<MODE>(p);
-  const int G = gridDim.x;
-  const int lbase = (blockIdx.x % kXcds) * (G / kXcds) + blockIdx.x / kXcds;
   for (int round = 0;; ++round) {
-    const int L = round * G + lbase;
-    if (L >= n_items) break;
+    const int L = round_item(round, n_items);
+    if (L < 0) break;
     MidTile t;
     mid_operands<MODE, PASS, 4>(p, L, t);
     auto run = [&](auto hc) {

@@ -1635,28 +1635,6 @@ bool make_plan(moe_dtype dt, moe_act act, int E, int d, int f, int64_t rows_allo
   return true;
 }
 
-// Cache lines per 128-byte row segment, in sixteenths, of rows `pitch` bytes
-// apart: 1 where every segment starts on a line, else 2 for all but those
-// that do.
-int lines16(int64_t pitch) {
-  const int64_t g = pitch & -pitch;   // largest power of two in the pitch
-  return g >= 128 ? 16 : 32 - static_cast<int>(g / 8);
-}
-
-// bf16 K step of the two-workgroups-per-CU kernel (both workgroups): A rows
-// pa bytes apart, B K-contiguous with rows pb apart or K-major (64 k-rows of
-// 256 bytes: 2 lines, or up to 3).
-StepCost step16(int64_t pa, int64_t pb, bool b_km) {
-  // 2 x 32 x lines16 / 16 lines a unit, 1000 / 640 ns a line
-  return {210, 185, b_km ? (pb % 128 ? 600 : 400) : 25 * lines16(pb), 100 * lines16(pa) / 16};
-}
-
-// And of the 256x256 kernel, ns.
-int big_step16(int64_t pa, int64_t pb, bool b_km) {
-  const int lines = 16 * lines16(pa) + (b_km ? (pb % 128 ? 320 : 256) : 16 * lines16(pb));
-  return std::max(1400, lines * 25 / 16);
-}
-
 // nt0, nt1: column tiles (of kMidN columns) of the call's products with N = f
 // (K = d) and with N = d (K = k1), c0, c1: their K steps' times, for the
 // heights of the two mid tile lists.
@@ -1693,23 +1671,9 @@ GemmParams base_params(const FfnPlan& pl, const int32_t* offsets, char* ws) {
 // 256x256 kernel only, 2 the two-workgroups-per-CU kernel only).
 int g_tile_mode = 0;
 
-// The two-workgroups-per-CU kernel's smaller tiles leave fewer CUs idle in
-// the last round and overlap one tile's prologue and epilogue with the
-// other's MFMAs, but read more operand bytes per flop.  The host knows N, K
-// and the row budget, not the per-expert rows, so it takes every expert to
-// hold rows_alloc / E rows and half a tile's raggedness, and compares the two
-// kernels' estimated times: rounds of 256x256 tiles of 1.4 us per K step (1.2
-// where at most half the CUs have one; longer where it touches more cache
-// lines) and 10 us of prologue and epilogue, 13 with an activation, against
-// 6/5 of the least mid_time over the heights: that is how much further the
-// measured times of these tiles lie above the estimate, the most in long
-// products (50 experts of 393 rows, 1120 -> 2 x 6536: 850 / 1026 us).  Whole products, 256x256 against these
-// tiles, us, same box: 16 experts of 1024 +- 30 rows, 512 -> 2048 84 / 60, 2048
-// -> 512 61 / 45; 16 of 512 +- 20 rows, 1024 -> 4096 104 / 93, 4096 -> 1024 110 /
-// 87; 32 of 2048, 2048 -> 8192 1885 / 2089, 8192 -> 2048 1773 / 2105; 50 of 393
-// rows, 6536 -> 1120 (rows off 128-byte lines) 395 / 579.  Weight gradients (K
-// not known on the host) compare rounds, a round of 128x128 tiles taking 0.65
-// of one of 256x256 tiles.
+// mid_pays (tiles.hpp) for the forward and the data gradients; the weight
+// gradients (K not known on the host) compare rounds, a round of 128x128 tiles
+// taking 0.65 of one of 256x256 tiles.
 bool use_mid_tiles(const FfnPlan& pl, moe_dtype dt, bool vark, bool gated, bool act, bool b_km,
                    const GemmParams& p) {
   if (dt == MOE_F32) return true;
@@ -1721,19 +1685,7 @@ bool use_mid_tiles(const FfnPlan& pl, moe_dtype dt, bool vark, bool gated, bool 
     const int64_t mid = static_cast<int64_t>(pl.E) * cdiv(p.M_out, kMidDwH * kMidUnit) * cdiv(p.N, kMidN);
     return 13 * ((mid + 2 * G - 1) / (2 * G)) < 20 * ((big + G - 1) / G);
   }
-  const int steps = cdiv(p.K, 64);
-  const int64_t per = cdiv(pl.rows_alloc, pl.E);
-  const int64_t big = pl.E * (2 * per + BM) / (2 * BM) * cdiv(p.N, gated ? BN / 2 : BN);
-  const int step = 2 * big <= G ? 1200 : big_step16(p.lda, p.ldb, b_km);
-  const int64_t t_big = (big + G - 1) / G * (static_cast<int64_t>(step) * steps + (act ? 13000 : 10000));
-  const StepCost c = step16(p.lda, p.ldb, b_km);
-  int64_t t_mid = 0;
-  for (int h = 1; h <= kMidMaxH; ++h) {
-    const int64_t n = (2 * per + kMidUnit + 2 * kMidUnit * h - 1) / (2 * kMidUnit * h);
-    const int64_t t = mid_time(n * pl.E * cdiv(p.N, gated ? kMidN / 2 : kMidN), h, 2 * G, steps, c);
-    if (h == 1 || t < t_mid) t_mid = t;
-  }
-  return 6 * t_mid < 5 * t_big;
+  return mid_pays({pl.E, pl.rows_alloc, p.N, p.K, gated, act, b_km, p.lda, p.ldb}, G);
 }
 
 // dX with a transposed copy of [W1; W3] (moe_set_dx_weight_copy: 0

@@ -4,18 +4,11 @@
 #pragma once
 
 #include "common.hpp"
+#include "tiles.hpp"
 #include "validate.hpp"
 
 namespace moe {
 
-constexpr int BM = 256;                           // 256x256 tiles
-constexpr int BN = 256;
-// Tiles of the two-workgroups-per-CU kernels: kMidN columns, and 1 to
-// kMidMaxH units of kMidUnit rows, chosen per tile.
-constexpr int kMidUnit = 32;
-constexpr int kMidMaxH = 6;
-constexpr int kMidN = 128;
-constexpr int kMidDwH = 4;      // its units in the bf16 weight-gradient products
 constexpr int kSplitFloor = 512;  // smallest K chunk of a split dW product
 constexpr int kKc = 64;           // split chunks are multiples of this many rows
 constexpr int kSplitItems = 256;  // work items the split aims at: one 256x256 tile per CU
@@ -53,35 +46,6 @@ __device__ __forceinline__ int2 mid_tile(int rows, int n, int i, int e) {
   const int units = ceil_units(rows, kMidUnit);
   const int h = units / n, more = units - h * n;
   return make_int2(e | ((h + (i < more ? 1 : 0)) << 8), (i * h + min(i, more)) * kMidUnit);
-}
-
-// Time (ns) of the two-workgroups-per-CU kernel on `tiles` tiles of at most h
-// units of rows and `steps` K steps each: rounds of `slots` tiles, each as
-// long as its K steps and its prologue and epilogue, which the other
-// workgroup of the CU overlaps in part.  A K step takes the longer of
-//  * its MFMAs, operand reads and waits: 0.87 us at h = 4 and 1.21 us at h = 6
-//    for both workgroups of a CU with operands in the caches, about a tenth
-//    more in a layer (1024- to 8192-row products, K = 512 .. 8192); fp32 (K
-//    steps of 32): the 16 h MFMAs of a step and wave, 64 cycles each;
-//  * the cache lines its loads touch, about 640 per us and CU: a row's 128
-//    bytes are one line where the row pitch is a multiple of 128 bytes and up
-//    to two elsewhere (152,000 rows, K = 12064, N = 536: 2.0 us per step at h = 6,
-//    the product 3276 us against 2356 us on 256x256 tiles, which touch 0.6
-//    times as many lines per MFMA).
-// A round of K = 512 at h = 4 takes 3.2 us more than its 8 steps.  A last round
-// that leaves at least one of the two places of every CU empty takes about
-// 0.65 of a full one.
-struct StepCost {
-  int fixed, per_unit;               // ns per K step, ns per K step and unit of rows
-  int lines_fixed, lines_per_unit;   // the same for the cache lines
-};
-constexpr StepCost kStepF32 = {60, 890, 0, 0};
-__host__ __device__ inline int64_t mid_time(int64_t tiles, int h, int slots, int steps,
-                                            const StepCost& c) {
-  const int64_t full = tiles / slots, rem = tiles - full * slots;
-  const int a = c.fixed + c.per_unit * h, b = c.lines_fixed + c.lines_per_unit * h;
-  return (20 * full + (rem == 0 ? 0 : 2 * rem <= slots ? 13 : 20)) *
-         (static_cast<int64_t>(steps) * (a > b ? a : b) + 3200) / 20;
 }
 
 // First index g < E whose inclusive prefix exceeds t.

@@ -1925,9 +1925,13 @@ extern "C" moe_status moe_expert_ffn_bwd(void* stream, moe_dtype dt, moe_act act
   if (!workspace || workspace_bytes < pl.total_bwd || !aligned16(workspace)) return MOE_EWORKSPACE;
   hipStream_t s = static_cast<hipStream_t>(stream);
   char* ws = static_cast<char*>(workspace);
+  // dX reads [W1; W3] from a transposed copy (K-contiguous) when the rule
+  // or the caller's setting asks for it and the workspace has room for it
+  const bool wt = use_wt13(pl, dt) && workspace_bytes >= pl.total_bwd_wt;
   MOE_TRY(launch_schedule(s, sched_args(pl, cdiv(f, kMidN), cdiv(d, kMidN), pl.F,
                                         step16(d * 2ll, f * 2ll, true),
-                                        step16(pl.F * 2ll, d * 2ll, true), ws), offsets, rows));
+                                        step16(pl.F * 2ll, (wt ? pl.F : d) * 2ll, !wt), ws),
+                          offsets, rows));
   const int64_t es = static_cast<int64_t>(pl.es);
   const bool sw = act == MOE_SWIGLU;
   const int F = pl.F;
@@ -1940,9 +1944,6 @@ extern "C" moe_status moe_expert_ffn_bwd(void* stream, moe_dtype dt, moe_act act
   const char* h1 = act == MOE_RELU ? abuf : static_cast<const char*>(h_save);
   const char* h3 = sw ? h1 + plane : nullptr;
 
-  // dX reads [W1; W3] from a transposed copy (K-contiguous) when the rule
-  // or the caller's setting asks for it and the workspace has room for it
-  const bool wt = use_wt13(pl, dt) && workspace_bytes >= pl.total_bwd_wt;
   char* wt13 = ws + pl.o_wt13;
   if (wt) MOE_TRY(launch_transpose_w(s, E, w1, sw ? w3 : nullptr, f, sw ? f : 0, d, wt13));
 

@@ -2,10 +2,9 @@
 backward against the CPU oracle, through the C ABI.
 
 The bf16 cases run on both GEMM kernels (moe_set_gemm_tiles: 1 = 256x256
-tiles, 2 = 128x128 tiles, two workgroups per CU) and with dX reading the
+tiles, 2 = 128-column tiles, two workgroups per CU) and with dX reading the
 weights K-major or from their transposed copy (moe_set_dx_weight_copy); f32
-cases run with the small-layer forward kernel (mode 0) and without it
-(mode 1).
+has one kernel, on 128-column tiles.
 
 ReLU cases use dyadic inputs (x, dy in {-2..2}/4, weights in {-2..2}/16):
 every GEMM partial sum is exactly representable in fp32, so the kernels and
@@ -20,6 +19,7 @@ import oracle as O
 import workloads as W
 from gpu_util import RTOL, assert_close, dev, to_dev, to_np, torch_dtype
 from paper_2205_01848_amd import binding as B
+from tiles_util import heights, used_heights
 
 pytestmark = pytest.mark.gpu
 
@@ -98,7 +98,8 @@ def _gpu_run(rows, cap, off, R, P, act, dt, E, d, f, rows_kind):
     wsb = B.workspace(B.moe_ffn_bwd_workspace_bytes(code, a, E, d, f, R), dev())
     B.moe_expert_ffn_bwd(a, i32(off), r_dev, x, h, w1, w3, w2, dy, dx, dw1, dw3, dw2, wsb)
     torch.cuda.synchronize()
-    return dict(h=to_np(h).reshape(n_h, R, f), y=to_np(y), dx=to_np(dx), dw1=to_np(dw1),
+    (hH, hY), (hA, hX) = used_heights(ws, E, R), used_heights(wsb, E, R)
+    return dict(heights=[hH, hY, hA, hX], h=to_np(h).reshape(n_h, R, f), y=to_np(y), dx=to_np(dx), dw1=to_np(dw1),
                 dw3=None if dw3 is None else to_np(dw3), dw2=to_np(dw2))
 
 
@@ -127,11 +128,8 @@ CASES = [
 
 
 # (dtype, tile mode, dX weight copy): bf16 on both kernels, each with dX
-# reading the weights K-major (1) and from the transposed copy (2); f32 with
-# its small-layer forward kernel (mode 0: one wavefront per 32x32 block) and
-# on 256x256 tiles only (mode 1)
-DT_TILES = [("f32", 0, 0), ("f32", 1, 0), ("bf16", 1, 1), ("bf16", 2, 1), ("bf16", 1, 2),
-            ("bf16", 2, 2)]
+# reading the weights K-major (1) and from the transposed copy (2)
+DT_TILES = [("f32", 0, 0), ("bf16", 1, 1), ("bf16", 2, 1), ("bf16", 1, 2), ("bf16", 2, 2)]
 
 
 @pytest.mark.parametrize("dt,tiles,wcopy", DT_TILES)
@@ -235,7 +233,7 @@ def test_padded_static_rows_match_on_filled_rows(tiles):
 
 @pytest.mark.parametrize("act", ["relu", "gelu_tanh", "swiglu"])
 def test_tile_kernels_bit_identical(act):
-    """The 256x256 and the 128x128 kernels add every output's products in the
+    """The 256x256 and the 128-column kernels add every output's products in the
     same order (K steps of 64 in order, two MFMA k-halves per step, the same
     split-K segments), so on random bf16 inputs every output is identical bit
     for bit, and the automatic choice equals both; dX is the same whether it
@@ -259,21 +257,101 @@ def test_tile_kernels_bit_identical(act):
     assert np.isfinite(gs[0]["dw1"]).all()
 
 
-# heights of the 128-column tiles: 8 column tiles (16 for the gated forward),
-# so 2048 h rows fill one round of tiles of h units of 32 rows; the uneven
-# split leaves tiles of h and of fewer units, the second expert a partial one
-@pytest.mark.parametrize("h,act", [(1, "relu"), (2, "swiglu"), (3, "gelu_tanh"), (4, "relu"),
-                                   (5, "swiglu"), (6, "gelu_tanh")])
-def test_tile_heights_bit_identical(h, act):
-    E, d, f = 3, 72, 1000
-    n = 1900 * h if act != "swiglu" else 950 * h
-    rows, cap, off, R, P = _problem(E, d, f, [n + 17, 0, 33], [0, 1, 2], act, "bf16", False, 80 + h)
+def _cus():
+    n = torch.cuda.get_device_properties(0).multi_processor_count
+    return -(-n // 8) * 8
+
+
+def _heights(act, dt, d, f, n):
+    """Rows of three experts, a partial tile and none among them, and the
+    largest tile heights (units of 32 rows) the rule gives H, Y, dA and dX."""
+    rows = [n + 17, 0, 33]
+    return rows, heights(rows, d, f, act == "swiglu", dt == "f32", cus=_cus())
+
+
+# Shapes whose H, Y, dA and dX run on 128-column tiles of the given largest
+# heights: together 1 to 6 for each of the four, plain and gated
+BF16_HEIGHTS = [
+    ("relu", 136, 136, 20, [1, 1, 1, 1]), ("gelu_tanh", 136, 136, 4200, [2, 2, 2, 2]),
+    ("relu", 136, 136, 8200, [3, 3, 3, 3]), ("gelu_tanh", 136, 136, 12200, [4, 4, 4, 4]),
+    ("relu", 136, 136, 16600, [5, 5, 5, 5]), ("gelu_tanh", 264, 264, 13800, [6, 6, 6, 6]),
+    ("swiglu", 136, 136, 20, [1, 1, 1, 1]), ("swiglu", 136, 136, 4200, [2, 2, 2, 2]),
+    ("swiglu", 136, 136, 5400, [3, 2, 2, 2]), ("swiglu", 136, 136, 8200, [4, 3, 3, 3]),
+    ("swiglu", 136, 136, 12200, [5, 4, 4, 4]), ("swiglu", 136, 136, 16600, [4, 5, 5, 5]),
+    ("swiglu", 264, 136, 13800, [6, 6, 4, 6]), ("swiglu", 136, 264, 13800, [5, 4, 6, 4])]
+
+
+@pytest.mark.parametrize("act,d,f,n,want", BF16_HEIGHTS)
+def test_tile_heights_bit_identical(act, d, f, n, want):
+    E = 3
+    rows, rule = _heights(act, "bf16", d, f, n)
+    rows, cap, off, R, P = _problem(E, d, f, rows, [0, 1, 2], act, "bf16", False, n)
     gs = [_gpu(rows, cap, off, R, P, act, "bf16", E, d, f, tiles=t) for t in (1, 2)]
+    assert gs[1]["heights"] == rule
+    if _cus() == 256:
+        assert rule == want
     valid = np.concatenate([np.arange(off[e], off[e] + rows[e]) for e in range(E)])
     np.testing.assert_array_equal(gs[0]["h"][:, valid], gs[1]["h"][:, valid])
     for name in ("y", "dx"):
         np.testing.assert_array_equal(gs[0][name][valid], gs[1][name][valid], err_msg=name)
     assert np.isfinite(gs[0]["dx"][valid]).all()
+
+
+# the same for fp32 (the oracle: dyadic ReLU exactly), SwiGLU with odd heights,
+# whose two row groups of waves share the last row block
+F32_HEIGHTS = [
+    ("relu", 136, 136, 20, [1, 1, 1, 1]), ("relu", 136, 136, 8200, [3, 3, 3, 3]),
+    ("relu", 136, 136, 12200, [2, 2, 2, 2]), ("relu", 136, 136, 16600, [5, 5, 5, 5]),
+    ("relu", 264, 264, 16600, [4, 4, 4, 4]), ("relu", 136, 520, 16200, [6, 2, 6, 2]),
+    ("relu", 520, 136, 16200, [2, 6, 2, 6]),
+    ("swiglu", 136, 136, 20, [1, 1, 1, 1]), ("swiglu", 136, 136, 8200, [2, 3, 3, 3]),
+    ("swiglu", 136, 136, 5400, [3, 1, 1, 1]), ("swiglu", 136, 136, 12600, [5, 2, 2, 2]),
+    ("swiglu", 136, 136, 16600, [4, 5, 5, 3]), ("swiglu", 264, 264, 16600, [6, 4, 4, 4]),
+    ("swiglu", 520, 136, 16200, [3, 6, 2, 6]), ("swiglu", 520, 136, 13000, [3, 5, 2, 5]),
+    ("swiglu", 136, 520, 16200, [3, 2, 6, 2])]
+
+
+@pytest.mark.parametrize("act,d,f,n,want", F32_HEIGHTS)
+def test_f32_tile_heights(act, d, f, n, want):
+    E = 3
+    rows, rule = _heights(act, "f32", d, f, n)
+    rows, cap, off, R, P = _problem(E, d, f, rows, [0, 1, 2], act, "f32", act == "relu", n)
+    valid, fw, bw = _oracle(rows, off, P, act, "f32", E)
+    g = _gpu(rows, cap, off, R, P, act, "f32", E, d, f)
+    assert g["heights"] == rule
+    if _cus() == 256:
+        assert rule == want
+    _compare(g, valid, fw, bw, act, "f32", exact=act == "relu")
+
+
+# fp32 weight-gradient tiles of 32, 64 and 128 rows (the host takes the highest
+# that still gives each of the 512 places one: E ceil(M / rows) ceil(N / 128)),
+# one expert's rows split into K segments
+@pytest.mark.parametrize("act,E,d,f,units", [("relu", 8, 136, 136, 1), ("swiglu", 8, 136, 200, 1),
+                                             ("relu", 64, 200, 264, 2), ("swiglu", 64, 200, 264, 2),
+                                             ("relu", 64, 264, 520, 4), ("swiglu", 48, 264, 520, 4)])
+def test_f32_weight_gradient_tiles(act, E, d, f, units):
+    places = 2 * _cus()
+    for M, N in ((d, f), (2 * f if act == "swiglu" else f, d)):
+        h = 4
+        while h > 1 and E * -(-M // (32 * h)) * -(-N // 128) < places:
+            h //= 2
+        if _cus() == 256:
+            assert h == units or act == "swiglu"
+    rng = np.random.default_rng(E + d)
+    rows = rng.integers(0, 30, E)
+    rows[E // 2], rows[3], rows[0] = 1700, 0, 33
+    rows, cap, off, R, P = _problem(E, d, f, rows, [0] * E, act, "f32", act == "relu", 7)
+    valid, fw, bw = _oracle(rows, off, P, act, "f32", E)
+    g = _gpu(rows, cap, off, R, P, act, "f32", E, d, f)
+    if act == "relu":
+        _compare(g, valid, fw, bw, act, "f32", exact=True)
+    # each expert on its own scale: a gradient of 1700 rows is about ten times one
+    # of 15, so the rms of all experts (a sixth of the large one's) would hold the
+    # large one's sums to a sixth of the tolerance
+    for name, ref in (("dw1", "dW1"), ("dw2", "dW2")) + ((("dw3", "dW3"),) if act == "swiglu" else ()):
+        for e in range(E):
+            assert_close(g[name][e], bw[ref][e], RTOL["f32"], f"{ref}[{e}]")
 
 
 # ---- combine, combine backward, dispatch backward -----------------------------

@@ -203,11 +203,19 @@ class MoELayer:
             B.moe_dispatch_bwd(self.dx_disp, self.dest_row, self.E, None, None, self.dx)
 
     # ---- whole layer ---------------------------------------------------------
+    def _own_steps(self):
+        """Whether every step of the forward is this class's own.  A subclass,
+        an instance or a patched class with a step of its own (a timer, a hook)
+        gets the steps called one by one."""
+        c = type(self)
+        return ((c.gate, c.count, c.capacity_static, c.capacity_dynamic, c.dispatch, c.ffn_fwd,
+                 c.combine) == _OWN_STEPS and self.__dict__.keys().isdisjoint(_STEPS))
+
     def _fusable(self, x, w1, capacity, rows, counts_from_batch=True, ids=None, w_g=None):
-        """Whether the forward is one library call: capacities from this
-        batch, kept rows, and tensors of the layer's own shapes (the separate
-        calls take each shape from the tensors they get)."""
-        return (rows == "fill" and capacity[0] != "policy" and
+        """Whether the forward is one library call: the class's own steps,
+        capacities from this batch, kept rows, and tensors of the layer's own
+        shapes (the separate calls take each shape from the tensors they get)."""
+        return (rows == "fill" and capacity[0] != "policy" and self._own_steps() and
                 (capacity[0] == "static" or counts_from_batch) and
                 x.shape == (self.T, self.d) and w1.shape == (self.E, self.f, self.d) and
                 (w_g is None or w_g.shape == (self.E, self.d)) and
@@ -229,17 +237,23 @@ class MoELayer:
         kind, num, den = capacity
         if kind == "policy":
             self.dispatch(x, ids)   # capacity and offsets uploaded by a CapacityPolicy
-        elif kind == "static" or counts_from_batch:
+        elif (kind == "static" or counts_from_batch) and self._own_steps():
             self.route(x, ids, kind != "static", num, den)
         else:
-            self.capacity_dynamic(num, den)
+            if kind == "static":
+                self.capacity_static(num, den)
+            else:
+                if counts_from_batch:
+                    self.count(ids)
+                self.capacity_dynamic(num, den)
             self.dispatch(x, ids)
 
     def forward(self, x, w1, w3, w2, *, w_g=None, bias=None, renorm=0, ids=None, weights=None,
                 capacity=("dynamic", 1, 1), counts_from_batch=True, rows="fill",
                 balance: Optional[float] = None):
         """gate (or cached ids) -> [count ->] capacity -> dispatch -> FFN -> combine
-        (one library call unless the capacities or the rows come from elsewhere).
+        (one library call, which calls none of the step methods, unless the
+        capacities or the rows come from elsewhere or a step is overridden).
 
         capacity = ("static", num, den) | ("dynamic", num, den) | ("policy",
         1, 1); a dynamic rule uses this batch's counts when counts_from_batch,
@@ -320,3 +334,7 @@ class MoELayer:
         self.ffn_bwd(w1, w3, w2, rows=rows)
         self.dispatch_bwd(w_g)
         return self.dx
+
+
+_STEPS = ("gate", "count", "capacity_static", "capacity_dynamic", "dispatch", "ffn_fwd", "combine")
+_OWN_STEPS = tuple(getattr(MoELayer, n) for n in _STEPS)

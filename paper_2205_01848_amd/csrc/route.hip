@@ -1206,16 +1206,34 @@ static moe_status dispatch_launch(hipStream_t s, moe_dtype dt, int T, int d, int
 // Tokens per chunk of the fused kernels (32 or 64), or 0 for the general path
 // (chunks of kChunk assignments, a scan and a gather of their own): the
 // histogram entries every workgroup sums bound the batch.  The smaller chunk
-// gives the row copies more workgroups.  Past the bound every workgroup would
-// read over 64 KB of histograms for about 50 KB of rows.  The two kernels
-// against the six (fill, count, capacity, histogram, rank, gather): T = 8192,
-// k = 2, E = 16, d = 512: 14 us against 32 us; T = 16384, k = 1, E = 64, d =
-// 1024: 23 us against 42 us; T = 32, k = 2, E = 8, d = 4096 (one kernel): 5.6
-// us against 29 us.
+// gives the row copies more workgroups.  The two kernels against the six (fill,
+// count, capacity, histogram, rank, gather): T = 8192, k = 2, E = 16, d = 512:
+// 14 us against 32 us; T = 16384, k = 1, E = 64, d = 1024: 23 us against 42 us;
+// T = 32, k = 2, E = 8, d = 4096 (one kernel): 5.6 us against 29 us; at the
+// bound with short rows, T = 262144, k = 1, E = 2, d = 64: 54 us against 92 us,
+// T = 1048576, k = 1, E = 1, d = 8: 121 us against 314 us.
 static int route_chunk_tokens(int T, int E, int k) {
   for (int ct = 32; ct <= 64; ct *= 2)
     if (T > 0 && static_cast<int64_t>(nblocks(T, ct)) * k * E <= kMaxHist) return ct;
   return 0;
+}
+
+constexpr bool route_tiny(int T, int k) { return static_cast<int64_t>(T) * k <= kTinyAssign; }
+
+// Whether the fused kernels are faster than the general path, where they are
+// possible.  A chunk is copied by one workgroup, the general path's rows by a
+// wavefront per token: long rows of many picks take the few workgroups of a
+// short batch longer, and past the last-level cache the gather alone keeps
+// more loads in flight.  Fused / general, us: T = 512, k = 8, E = 8, d = 256 20
+// / 19, d = 4096 55 / 25; T = 8192, k = 1, E = 1, d = 2048 21 / 21, d = 4096 43 /
+// 31; T = 32768, k = 2, E = 8, d = 1024 41 / 45, d = 2048 108 / 93.  Where the
+// expert products' schedule is built on the way, the general path pays that
+// kernel's launch too, about 5 us.
+static bool route_fused_pays(const Route& r, int ct, bool sched) {
+  const int64_t row = static_cast<int64_t>(r.d) * esize(r.dt) * (r.k + 1);   // moved per token
+  const int64_t chunk = row * (route_tiny(r.T, r.k) ? 4 : ct);
+  return chunk <= (sched ? 800 : 400) * 1024 &&
+         (chunk <= 200 * 1024 || row * r.T <= 300 * int64_t(1000000));
 }
 
 extern "C" size_t moe_route_workspace_bytes(int T, int E, int k) {
@@ -1241,12 +1259,13 @@ moe_status route_check(const Route& a, size_t workspace_bytes) {
 moe_status route_launch(hipStream_t s, const Route& r, const SchedArgs* sched, bool* scheduled) {
   const int T = r.T, E = r.E, k = r.k;
   const int ct = route_chunk_tokens(T, E, k);
-  if (scheduled) *scheduled = sched && ct;
-  if (ct == 0)
+  const bool fused = ct && route_fused_pays(r, ct, sched != nullptr);
+  if (scheduled) *scheduled = sched && fused;
+  if (!fused)
     return dispatch_launch(s, r.dt, T, r.d, E, k, r.x, r.ids, &r.rule, r.capacity, r.offsets,
                            r.rows_alloc, r.counts, r.fill, r.dest_row, r.src, r.x_disp, r.status,
                            r.workspace);
-  const bool tiny = T * k <= kTinyAssign;
+  const bool tiny = route_tiny(T, k);
   const int nchunk = nblocks(T, tiny ? 4 : ct);
   int32_t* hist = nullptr;
   if (!tiny) {

@@ -336,6 +336,9 @@ def test_policy_uploads_aligned_offsets():
     (8192, 16, 64, 2, "bf16"),
     (8193, 16, 64, 2, "f32"),          # general path
     (40000, 8, 64, 2, "bf16"),         # with the scan kernel
+    (512, 1032, 8, 8, "bf16"),         # rows too long for a workgroup per 32 tokens
+    (512, 672, 8, 8, "bf16"),          # and just short enough
+    (33000, 1032, 5, 3, "f32"),        # past the last-level cache
 ])
 @pytest.mark.parametrize("rule", ["static", "dynamic", "tight"])
 def test_route_matches_separate_calls(T, d, E, k, dt, rule):

@@ -307,10 +307,16 @@ typedef int intx4 __attribute__((ext_vector_type(4)));
 // the A and B sub-blocks at k = 8 G .. 8 G + 7 and holds rows 4 G .. 4 G + 3,
 // column c16 of the result.  Inline assembly keeps each accumulator in place
 // in its accumulation registers through the K loop (compiled MFMAs get their
-// accumulators shuffled between loop iterations).  Consecutive updates of one
-// accumulator are at least 63 MFMAs apart, and the fragments an MFMA reads
-// are not rewritten for at least 28 MFMAs, so no wait states are needed
-// inside the loop; the epilogue waits before it reads the accumulators.
+// accumulators shuffled between loop iterations).  The compiler inserts no
+// wait states around it, and none are needed inside the loops:
+//  * an accumulator updated again, 64 MFMAs later on 256x256 tiles and 4 RB
+//    later on the others (4 at the least), is read as the very registers the
+//    earlier MFMA writes, which the hardware forwards without wait states;
+//  * an MFMA has read its A and B registers before an LDS read issued after it
+//    can return into them (on the smallest tile the next stage's first A
+//    fragment is requested right behind the last MFMA that used the registers);
+//  * fragments read from LDS are waited for by the compiler, as operands.
+// The epilogue waits before it reads the accumulators.
 __device__ __forceinline__ void mfma16(floatx4& c, const uint4& a, const uint4& b) {
   asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0"
                : "+a"(c)
@@ -569,7 +575,8 @@ __device__ __forceinline__ void mainloop_mid(const TileOps& op, char* la0, char*
   static_assert(ALAY == L_KC || RB == 4, "K-major A tiles are 128 columns wide");
   constexpr int KSTEP = 64;
   constexpr int KMROW = 256;           // bytes per k-row of a KM tile
-  constexpr int NM = 4 * RB;           // MFMAs per k-half
+  constexpr int NM = 4 * RB;           // MFMAs per k-half: one per accumulator
+  static_assert(NM >= 4, "updates of one accumulator are at least 4 MFMAs apart");
   const int lane = (static_cast<int>(threadIdx.x) & 63) + zt;
   const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
   const int wm = wave >> 1, wn = wave & 1;

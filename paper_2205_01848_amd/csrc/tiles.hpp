@@ -97,7 +97,7 @@ struct VarM {
 // 256x256 tiles are one round and a tenth more for every round up to six: the
 // smaller tiles' operand bytes tell once their panels no longer stay in the
 // caches.  A budget of whole 256-row tiles per expert is read as a static
-// capacity of that size, filled: no raggedness, and 1.05 throughout.
+// capacity of that size, filled: no raggedness, and a factor from 1 to 1.18.
 // Fitted on 2900 products (1 to 64 experts of 1 to 20,000 rows, d and f from
 // 64 to 14336): the choice takes 0.6 % more than the better kernel on average;
 // with 6/5 throughout, 1400 ns a K-major step, raggedness always and the tiles
@@ -106,7 +106,7 @@ struct VarM {
 // 256x256 / smaller tiles, us: 4 experts of 2210 rows, 5000 -> 536 134 / 74; 4
 // of 4073, K-major 4096 -> 4096 592 / 510; 32 of 512 exactly, 4096 -> 1024 117
 // / 162; 8 of 16,000, 4096 -> 2 x 14336 23598 / 40342; 32 of about 2048, 8192
-// -> 2048 1809 / 2064.
+// -> 2048 1809 / 2064, K-major 2048 -> 8192 2342 / 2547.
 inline bool mid_pays(const VarM& p, int cus) {
   auto cdiv = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
   const int steps = static_cast<int>(cdiv(p.K, 64));
@@ -126,7 +126,8 @@ inline bool mid_pays(const VarM& p, int cus) {
     const int64_t t = mid_time(n * p.E * cdiv(p.N, p.gated ? kMidN / 2 : kMidN), h, 2 * cus, steps, c);
     if (h == 1 || t < t_mid) t_mid = t;
   }
-  return (whole ? 21 : 14 + 2 * (rounds < 6 ? rounds : 6)) * t_mid < 20 * t_big;
+  const int64_t r = rounds < 6 ? rounds : 6;
+  return (whole ? 47 + 3 * r : 35 + 5 * r) * t_mid < 50 * t_big;
 }
 
 }  // namespace moe

@@ -18,8 +18,9 @@ def test_few_rows_take_the_smaller_tiles(E, R, d, f, swiglu):
 @pytest.mark.parametrize("E,rows,d,f,swiglu", [(8, 16384, 4096, 14336, True), (32, 2048, 2048, 8192, False),
                                                (64, 2048, 4096, 4096, False)])
 def test_large_products_keep_the_large_tiles(E, rows, d, f, swiglu):
-    for p in T.products(d, f, swiglu)[:2]:
-        assert not T.pays(E, E * rows, p), p
+    for p in T.products(d, f, swiglu):
+        for R in (E * rows, E * rows + 5, E * rows * 21 // 20):
+            assert not T.pays(E, R, p), (p, R)
 
 
 @pytest.mark.parametrize("E,rows,d,f", [(32, 512, 1024, 4096), (64, 512, 1024, 4096), (16, 512, 2048, 2048)])

@@ -1588,6 +1588,7 @@ int h_save_planes(moe_act act) { return act == MOE_SWIGLU ? 3 : act == MOE_GELU_
 struct FfnPlan {
   int E, d, f, F;            // F = f (relu/gelu) or 2f (swiglu)
   int64_t rows_alloc;
+  int64_t rows_most;         // rows_alloc, or fewer (FfnFwd)
   size_t es;
   int max_mtiles, max_mid, max_segs, max_slots, tmn_min;
   int64_t slot_elems;
@@ -1601,7 +1602,7 @@ bool make_plan(moe_dtype dt, moe_act act, int E, int d, int f, int64_t rows_allo
     return false;
   if (act != MOE_RELU && act != MOE_GELU_TANH && act != MOE_SWIGLU) return false;
   pl.E = E; pl.d = d; pl.f = f; pl.F = act == MOE_SWIGLU ? 2 * f : f;
-  pl.rows_alloc = rows_alloc;
+  pl.rows_alloc = pl.rows_most = rows_alloc;
   pl.es = esize(dt);
   // every operand offset inside a 256-row tile (K-contiguous operands) or a
   // K step (K-major ones) stays below 2^31 bytes: buffer loads take 32-bit
@@ -1692,7 +1693,7 @@ bool use_mid_tiles(const FfnPlan& pl, moe_dtype dt, bool vark, bool gated, bool 
     const int64_t mid = static_cast<int64_t>(pl.E) * cdiv(p.M_out, kMidDwH * kMidUnit) * cdiv(p.N, kMidN);
     return 13 * ((mid + 2 * G - 1) / (2 * G)) < 20 * ((big + G - 1) / G);
   }
-  return mid_pays({pl.E, pl.rows_alloc, p.N, p.K, gated, act, b_km, p.lda, p.ldb}, G);
+  return mid_pays({pl.E, pl.rows_alloc, pl.rows_most, p.N, p.K, gated, act, b_km, p.lda, p.ldb}, G);
 }
 
 // dX with a transposed copy of [W1; W3] (moe_set_dx_weight_copy: 0
@@ -1850,6 +1851,7 @@ moe_status ffn_fwd_launch(hipStream_t s, const FfnFwd& a, bool scheduled) {
   if (a.rows_alloc == 0) return MOE_OK;
   FfnPlan pl;
   make_plan(a.dt, a.act, a.E, a.d, a.f, a.rows_alloc, pl);
+  pl.rows_most = a.rows_most;
   if (!scheduled) MOE_TRY(launch_schedule(s, ffn_fwd_sched(a), a.offsets, a.rows));
   char* ws = static_cast<char*>(a.workspace);
   const moe_dtype dt = a.dt;
@@ -1907,7 +1909,7 @@ extern "C" moe_status moe_expert_ffn_fwd(void* stream, moe_dtype dt, moe_act act
                                          const void* w3, const void* w2, void* h_save,
                                          void* y_disp, void* workspace, size_t workspace_bytes) {
   const FfnFwd a = {dt, act, E, d, f, offsets, rows, rows_alloc, x_disp, w1, w3, w2, h_save,
-                    y_disp, workspace};
+                    y_disp, workspace, rows_alloc};
   MOE_TRY(ffn_fwd_check(a, workspace_bytes));
   return ffn_fwd_launch(static_cast<hipStream_t>(stream), a, false);
 }

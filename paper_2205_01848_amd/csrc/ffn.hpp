@@ -13,6 +13,7 @@ struct FfnFwd {   // arguments of moe_expert_ffn_fwd
   int64_t rows_alloc;
   const void *x_disp, *w1, *w3, *w2;
   void *h_save, *y_disp, *workspace;
+  int64_t rows_most;   // at most this many rows hold a token: rows_alloc if not known
 };
 moe_status ffn_fwd_check(const FfnFwd& a, size_t workspace_bytes);
 // Arguments for a schedule of this call built elsewhere (a.rows_alloc > 0).

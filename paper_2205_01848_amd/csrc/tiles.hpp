@@ -78,6 +78,7 @@ inline int big_step16(int64_t pa, int64_t pb, bool b_km, bool few) {
 struct VarM {
   int E;
   int64_t rows_alloc;
+  int64_t rows;        // at most this many of them hold a token (rows_alloc if not known)
   int N, K;
   bool gated;          // W1 and W3 share a tile
   bool act;            // an activation or its derivative in the epilogue
@@ -88,8 +89,8 @@ struct VarM {
 // Whether the two-workgroups-per-CU kernel is the faster one on `cus` CUs.
 // Its smaller tiles leave fewer CUs idle in the last round and overlap one
 // tile's prologue and epilogue with the other's MFMAs, but read more operand
-// bytes per flop.  The host knows N, K and the row budget, not the rows per
-// expert, so it takes every expert to hold rows_alloc / E rows and half a
+// bytes per flop.  The host knows N, K and the rows at most, not the rows per
+// expert, so it takes every expert to hold rows / E rows and half a
 // tile's raggedness (but no fewer tiles than experts that can hold a row), and
 // compares the two kernels' estimated times: rounds of 256x256 tiles, each its
 // K steps and 10 us of prologue and epilogue, 13 with an activation, against
@@ -97,7 +98,12 @@ struct VarM {
 // 256x256 tiles are one round and a tenth more for every round up to six: the
 // smaller tiles' operand bytes tell once their panels no longer stay in the
 // caches.  A budget of whole 256-row tiles per expert is read as a static
-// capacity of that size, filled: no raggedness, and a factor from 1 to 1.18.
+// capacity of that size, filled, where the rows can fill it: no raggedness,
+// and a factor from 1 to 1.18.  The layer
+// forward passes its number of picks: a static capacity of twice that counts
+// as half filled and ragged (8 experts of 1024 rows, 1024 -> 4096: 75 / 41 us;
+// over 236 such products 1.005 of the better kernel's time, against 1.16 with
+// the capacity read as filled).
 // Fitted on 2900 products (1 to 64 experts of 1 to 20,000 rows, d and f from
 // 64 to 14336): the choice takes 0.6 % more than the better kernel on average;
 // with 6/5 throughout, 1400 ns a K-major step, raggedness always and the tiles
@@ -110,10 +116,10 @@ struct VarM {
 inline bool mid_pays(const VarM& p, int cus) {
   auto cdiv = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
   const int steps = static_cast<int>(cdiv(p.K, 64));
-  const int64_t per = cdiv(p.rows_alloc, p.E);
-  const bool whole = p.rows_alloc % (static_cast<int64_t>(BM) * p.E) == 0;
-  int64_t m = whole ? p.rows_alloc / BM : p.E * (2 * per + BM) / (2 * BM);
-  const int64_t least = p.rows_alloc < p.E ? p.rows_alloc : p.E;
+  const int64_t per = cdiv(p.rows, p.E);
+  const bool whole = p.rows == p.rows_alloc && p.rows % (static_cast<int64_t>(BM) * p.E) == 0;
+  int64_t m = whole ? p.rows / BM : p.E * (2 * per + BM) / (2 * BM);
+  const int64_t least = p.rows < p.E ? p.rows : p.E;
   if (m < least) m = least;
   const int64_t big = m * cdiv(p.N, p.gated ? BN / 2 : BN);
   const int64_t rounds = cdiv(big, cus);

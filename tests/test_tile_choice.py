@@ -30,3 +30,17 @@ def test_filled_whole_tiles_keep_the_large_tiles(E, rows, d, f):
     smaller ones."""
     for p in T.products(d, f, False)[1::2]:
         assert not T.pays(E, E * rows, p), p
+
+
+@pytest.mark.parametrize("E,rows,d,f", [(4, 2048, 1024, 4096), (8, 1024, 1024, 4096), (16, 1024, 2048, 2048),
+                                        (32, 1024, 1024, 4096)])
+def test_half_filled_whole_tiles_take_the_smaller_tiles(E, rows, d, f):
+    """A static capacity of twice a layer's picks holds about half its rows:
+    read as filled, H or Y kept the 256x256 kernel and took 1.5 to 1.8 times as
+    long."""
+    took = [T.pays(E, E * rows, p, most=E * rows // 2) and not T.pays(E, E * rows, p)
+            for p in T.products(d, f, False)[:2]]
+    assert any(took)
+    # picks that can fill the capacity change nothing
+    for p in T.products(d, f, False)[:2]:
+        assert T.pays(E, E * rows, p, most=E * rows) == T.pays(E, E * rows, p)

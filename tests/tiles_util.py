@@ -11,8 +11,8 @@ import numpy as np
 CSRC = os.path.join(os.path.dirname(os.path.abspath(__file__)), "..", "paper_2205_01848_amd", "csrc")
 SRC = '''#include "tiles.hpp"
 using namespace moe;
-extern "C" int pays(int E, int64_t R, int N, int K, int gated, int act, int km, int64_t pa, int64_t pb, int cus) {
-  return mid_pays({E, R, N, K, gated != 0, act != 0, km != 0, pa, pb}, cus);
+extern "C" int pays(int E, int64_t R, int64_t most, int N, int K, int gated, int act, int km, int64_t pa, int64_t pb, int cus) {
+  return mid_pays({E, R, most, N, K, gated != 0, act != 0, km != 0, pa, pb}, cus);
 }
 // the schedule's choice: least time, the larger height on a tie
 extern "C" int height(int E, const int* rows, int N, int K, int gated, int km, int64_t pa, int64_t pb, int f32, int cus) {
@@ -48,7 +48,7 @@ def lib():
                        check=True)
         _lib = ctypes.CDLL(so)
         i, l = ctypes.c_int, ctypes.c_int64
-        _lib.pays.argtypes = [i, l, i, i, i, i, i, l, l, i]
+        _lib.pays.argtypes = [i, l, l, i, i, i, i, i, l, l, i]
         _lib.height.argtypes = [i, ctypes.c_void_p, i, i, i, i, l, l, i, i]
     return _lib
 
@@ -60,9 +60,9 @@ def products(d, f, swiglu, es=2, wcopy=False):
             (f, d, 0, 1, 1, es * d, es * f), (d, F, 0, 0, int(not wcopy), es * F, es * (F if wcopy else d))]
 
 
-def pays(E, R, product, cus=256):
+def pays(E, R, product, cus=256, most=None):
     N, K, gated, act, km, pa, pb = product
-    return bool(lib().pays(E, R, N, K, gated, act, km, pa, pb, cus))
+    return bool(lib().pays(E, R, R if most is None else most, N, K, gated, act, km, pa, pb, cus))
 
 
 def heights(rows, d, f, swiglu, f32, wcopy=False, cus=256):
